@@ -503,14 +503,12 @@ def main():
                      "over the measured time")},
     }
     plan = sol.tuning(1)["fd_plan"][0]
-    if plan == 9:
-        kname = ("apply_P0 (plan 9): k_fd_xy_s (16-row blocks, modes 1,2) + k_fd_z_w (16 rows, "
-                 "mode 3 + scaling) + k_fd_xy_s (inverse), FP64 16x16x4 MFMA")
-    elif plan == 8:
-        kname = "apply_P0 (plan 8): k_mode_gemm (six mode products per component), FP64 MFMA"
+    if plan in (0, 8):
+        kname = (f"apply_P0 (plan {plan}): k_fd_row + k_fd_line (one direction per pass, parity-split "
+                 "products), FP64 16x16x4 MFMA")
     else:
-        kname = (f"apply_P0 (plan {plan}): k_fd_xy_w (modes 1,2) + k_fd_z_w (mode 3 + scaling) "
-                 "+ k_fd_xy_w (inverse), FP64 16x16x4 MFMA")
+        kname = (f"apply_P0 (plan {plan}): k_fd_plane (modes 1,2) + k_fd_line (mode 3 + scaling) + "
+                 "k_fd_plane (inverse), parity-split products, FP64 16x16x4 MFMA")
     roof = {
         "kernel": kname,
         "bound": "mfma", "achieved": achieved, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
@@ -731,7 +729,7 @@ def main():
     sec51 = []
     if not args.no_extra:
         # ---- the operator study of Sec. 5.1 at 256^3 (beyond the in-LDS
-        # tiles: P_0 as mode-product GEMMs)
+        # tiles: P_0 one direction per pass)
         for ps in (2, 3):
             sec51.append(sec51_leg(args.sec51_E, ps, HBM_PEAK_GBS, FP64_PEAK_TFLOPS))
             log(f"[bench] sec 5.1: {sec51[-1]}")

@@ -68,9 +68,8 @@ typedef enum {
  * Krylov method always runs in FP64): FP64; FP32 (FP32 MFMA, FP32 storage of
  * the intermediates); split BF16 (each FP32 operand as hi + lo BF16 halves,
  * three BF16 MFMA products accumulated in FP32: about 16 significant bits,
- * products good to ~1e-5 relative).  Split BF16 runs in the 16-wave and
- * row-block plans (odd fd_plan codes, no 2x2 blocks); the 4-wave plans and
- * the mode-product GEMMs take FP32 products for it. */
+ * products good to ~1e-5 relative).  Split BF16 runs in the plane plans
+ * (fd_plan 1 and 9); the direction passes take FP32 products for it. */
 enum { HP_PREC_FP64 = 0, HP_PREC_FP32 = 1, HP_PREC_BF16X3 = 2 };
 /* Krylov method. MINRES needs an exactly symmetric preconditioner (FP64). */
 enum { HP_MINRES = 0, HP_FGMRES = 1 };
@@ -113,17 +112,14 @@ typedef struct hp_opts {
     int op_kchunk;      /* operator kernels: i3-planes per workgroup, 0 = tuned/model */
     int op_order;       /* operator kernels: velocity workgroup order, -1 = tuned/model,
                            0 = tiles fastest, 1 = components fastest */
-    int fd_plan;        /* P_0 kernels: -1 = tuned/default; 0..7 = the in-LDS kernels
-                           (a whole direction, <= 128, in MFMA tiles): bit 0 = 16-wave
-                           kernels, bit 1 = 1D matrices staged in LDS (if they fit),
-                           bit 2 = 2x2 blocks of MFMA tiles per wave (16-wave plans,
-                           FP64/FP32); 8 = every mode product as a batched GEMM over
-                           HBM (FP64/FP32; the plan used whenever E + degree - 1 > 128,
-                           where split BF16 falls back to FP32 products); 9 = the in-LDS
-                           products with one 16-row block of a plane per 4-wave
-                           workgroup and 16 z rows per workgroup (small meshes: several
-                           times the workgroups of plans 0..7, the same result as the
-                           16-wave plans) */
+    int fd_plan;        /* P_0 kernels: -1 = tuned/default; 1 = modes 1 and 2 of an
+                           i3-plane in one workgroup's LDS and mode 3 on 32 columns per
+                           workgroup (directions E + degree - 1 <= 128); 9 = the same with
+                           16 columns (twice the workgroups, for small meshes); 0 = one
+                           direction per pass (<= 128; FP64/FP32); 8 = one direction per
+                           pass at any length (the plan used whenever E + degree - 1 > 128,
+                           where split BF16 falls back to FP32 products); 2..7 = the default
+                           (codes of former kernels) */
     int op_slabs;       /* operator: i3-slabs run one after the other (pressure chain
                            then velocity per slab), 0 = tuned/model */
     int schur_level;    /* eq. Pcq2 only: the fixed P_{V,l} inside B' P_{V,l}^{-1} B,
@@ -219,9 +215,9 @@ hp_status hp_get_tuning(const hp_ctx* ctx, int nrhs, hp_tuning* out);
  * fewer than 6 elements at the default 12.5), or, with opts.spectrum_gate,
  * when P_0 leaves the convergence interval (0, 2).  opts may be NULL
  * (defaults).  stream: a hipStream_t or NULL.  *out receives the context.
- * Fast diagonalisation holds a whole direction in MFMA tiles while
- * E + degree - 1 <= 128 and runs its mode products as batched GEMMs beyond
- * (opts.fd_plan = 8), so every call serves any mesh that fits in memory. */
+ * Fast diagonalisation holds a whole plane in LDS while E + degree - 1 <= 128
+ * and takes one direction per pass beyond (opts.fd_plan = 8), so every call
+ * serves any mesh that fits in memory. */
 hp_status hp_setup(int elements, int degree, double nu, const hp_opts* opts,
                    void* stream, hp_ctx** out);
 

@@ -30,8 +30,6 @@ constexpr int KMAX = 6;  // largest number of hyper-power updates
         if (e_ != hipSuccess) return HP_EHIP;          \
     } while (0)
 
-int pad16(int n) { return (n + 15) & ~15; }
-
 // ---- buffers -------------------------------------------------------------------
 struct Extra {
     // hyper-power temporaries
@@ -943,15 +941,6 @@ static void upload_band(const std::vector<double>& A, int n, int w, double* dst)
     (void)hipMemcpy(dst, b.data(), b.size() * sizeof(double), hipMemcpyHostToDevice);
 }
 
-template <typename T>
-static std::vector<T> padded(const std::vector<double>& A, int n, int np, bool transpose) {
-    std::vector<T> out((size_t)np * np, (T)0);
-    for (int i = 0; i < n; ++i)
-        for (int j = 0; j < n; ++j)
-            out[(size_t)i * np + j] = (T)(transpose ? A[(size_t)j * n + i] : A[(size_t)i * n + j]);
-    return out;
-}
-
 // ---- autotuner ----------------------------------------------------------------------
 constexpr int TUNE_PASSES = 2;  // passes over the candidate list (fastest kept)
 constexpr int TUNE_REPS = 5;    // timed launches per candidate and pass
@@ -1050,6 +1039,8 @@ hp_status autotune(hp_ctx* c) {
         for (int pass = 0; pass < TUNE_PASSES && st == HP_OK; ++pass)
             for (int plan = 0; plan <= FD_PLAN_LAST && st == HP_OK; ++plan) {
                 if (!fd_plan_valid(c, prec, plan)) continue;
+                // up to 128 the same launches as FD_PLAN_PASSES
+                if (plan == FD_PLAN_LINES && fd_plan_valid(c, prec, FD_PLAN_PASSES)) continue;
                 c->fd_force = plan;
                 const double t = time_launches(c, e0, e1, TUNE_REPS, [&]() {
                     return launch_P0(c, fx, fy, true, true, false, prec, 1);
@@ -1390,10 +1381,11 @@ hp_status hp_setup(int elements, int degree, double nu, const hp_opts* opts, voi
     c->N = c->off[4];
     // ---- tables
     const int p = degree, wN = p, wM = p - 1;
-    const int NNp = pad16(nN), NMp = pad16(nM);
+    const int nt = fd_half_tiles(nM);
+    const size_t nfrag = (size_t)2 * 256 * nt * nt;  // one fragment table
     size_t nb = (size_t)3 * nN * (2 * wN + 1) + (size_t)2 * nM * (2 * wM + 1);
     // (+32: the dense tables start on a 256-byte boundary, for vector loads)
-    size_t nfd = (size_t)2 * NNp * NNp + (size_t)3 * NMp * NMp + nN + nM + 32;
+    size_t nfd = 5 * nfrag + nN + nM + 32;
     if (alloc_device(&c->d_tables, nb + nfd) != HP_OK) { delete ce; return HP_ENOMEM; }
     double* tp = c->d_tables;
     c->band.ptr[BK_N] = tp; upload_band(c->tab.K_int, nN, wN, tp); tp += (size_t)nN * (2 * wN + 1);
@@ -1427,40 +1419,41 @@ hp_status hp_setup(int elements, int degree, double nu, const hp_opts* opts, voi
         tp += v.size();
         return r;
     };
-    // fast diagonalisation at any size: in-LDS kernels up to 128 per direction,
-    // mode-product GEMMs beyond
+    // fast diagonalisation: the half-size matrices as MFMA fragments, in FP64
+    // and FP32, and the eigenvalues
     c->fd_ok = true;
     {
-    tp += (32 - (size_t)(tp - c->d_tables) % 32) % 32;  // 256-byte alignment of the dense tables
-    c->fd64.UK = up64(padded<double>(c->tab.UK, nN, NNp, false));
-    c->fd64.UKt = up64(padded<double>(c->tab.UK, nN, NNp, true));
-    c->fd64.UT = up64(padded<double>(c->tab.UT, nM, NMp, false));
-    c->fd64.UTt = up64(padded<double>(c->tab.UT, nM, NMp, true));
-    c->fd64.Mi = up64(padded<double>(c->tab.Mcinv, nM, NMp, false));
-    c->fd64.lamK = up64(c->tab.lamK);
-    c->fd64.lamT = up64(c->tab.lamT);
-    c->fd64.nN = nN; c->fd64.nM = nM; c->fd64.NNp = NNp; c->fd64.NMp = NMp;
-    // FP32 copies of the dense FD tables
-    size_t n32 = (size_t)2 * NNp * NNp + (size_t)3 * NMp * NMp;
-    if (hipMalloc(reinterpret_cast<void**>(&c->d_tables32), n32 * sizeof(float)) != hipSuccess) {
-        hp_destroy(c);
-        return HP_ENOMEM;
-    }
-    float* fp = c->d_tables32;
-    auto up32 = [&](const std::vector<float>& v) {
-        (void)hipMemcpy(fp, v.data(), v.size() * sizeof(float), hipMemcpyHostToDevice);
-        const float* r = fp;
-        fp += v.size();
-        return r;
-    };
-    c->fd32.UK = up32(padded<float>(c->tab.UK, nN, NNp, false));
-    c->fd32.UKt = up32(padded<float>(c->tab.UK, nN, NNp, true));
-    c->fd32.UT = up32(padded<float>(c->tab.UT, nM, NMp, false));
-    c->fd32.UTt = up32(padded<float>(c->tab.UT, nM, NMp, true));
-    c->fd32.Mi = up32(padded<float>(c->tab.Mcinv, nM, NMp, false));
-    c->fd32.lamK = c->fd64.lamK;
-    c->fd32.lamT = c->fd64.lamT;
-    c->fd32.nN = nN; c->fd32.nM = nM; c->fd32.NNp = NNp; c->fd32.NMp = NMp;
+        tp += (32 - (size_t)(tp - c->d_tables) % 32) % 32;  // 256-byte alignment of the fragments
+        if (hipMalloc(reinterpret_cast<void**>(&c->d_tables32), 5 * nfrag * sizeof(float)) !=
+            hipSuccess) {
+            hp_destroy(c);
+            return HP_ENOMEM;
+        }
+        float* fp = c->d_tables32;
+        auto up = [&](const std::vector<double>& A, int n, FdPack kind, const double** p64,
+                      const float** p32) {
+            std::vector<double> v64;
+            std::vector<float> v32;
+            fd_pack(A, n, nt, kind, v64);
+            fd_pack(A, n, nt, kind, v32);
+            (void)hipMemcpy(tp, v64.data(), v64.size() * sizeof(double), hipMemcpyHostToDevice);
+            (void)hipMemcpy(fp, v32.data(), v32.size() * sizeof(float), hipMemcpyHostToDevice);
+            *p64 = tp;
+            *p32 = fp;
+            tp += v64.size();
+            fp += v32.size();
+        };
+        up(c->tab.UK, nN, FdPack::forward, &c->fd64.F[0], &c->fd32.F[0]);
+        up(c->tab.UK, nN, FdPack::inverse, &c->fd64.V[0], &c->fd32.V[0]);
+        up(c->tab.UT, nM, FdPack::forward, &c->fd64.F[1], &c->fd32.F[1]);
+        up(c->tab.UT, nM, FdPack::inverse, &c->fd64.V[1], &c->fd32.V[1]);
+        up(c->tab.Mcinv, nM, FdPack::symmetric, &c->fd64.Mi, &c->fd32.Mi);
+        c->fd64.lam[0] = up64(c->tab.lamK);
+        c->fd64.lam[1] = up64(c->tab.lamT);
+        for (int i = 0; i < 2; ++i) c->fd32.lam[i] = c->fd64.lam[i];
+        c->fd64.nN = c->fd32.nN = nN;
+        c->fd64.nM = c->fd32.nM = nM;
+        c->fd64.nt = c->fd32.nt = nt;
     }
     // ---- workspace: operator intermediates + FD temporaries
     const long long R = o.max_rhs;

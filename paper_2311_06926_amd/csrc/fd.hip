@@ -7,13 +7,38 @@
 //     A_cc^{-1} = (U3 (x) U2 (x) U1) diag(1 / (2 nu (l1 + l2 + l3))) (U3 (x) U2 (x) U1)^T.
 // Pressure: P_{Q,0}^{-1} = 2 nu (M^^{-1})^{(x)3} (dense 1D inverses).
 //
-// Each mode product is a dense contraction, run as 16x16x4 MFMA tiles
-// (FP64 or FP32 operands, same-precision accumulation):
-//   xy : one i3-plane (n1 x n2) staged in LDS: T = L X, Y = T R (modes 1, 2)
-//   z  : 64 (i1,i2)-rows x n3 staged in LDS: Y = X U3, scale, Z = Y U3^T
-//        (16 rows per wave)
-//        (mode 3 both ways, fused with the eigenvalue scaling)
-// Forward: L = U1^T, R = U2.  Inverse: L = U1, R = U2^T.
+// Parity split.  On the uniform mesh every 1D matrix commutes with the
+// reversal i -> n-1-i, so its eigenvectors are even or odd (setup1d.cpp
+// computes them in the two subspaces).  With the folds e_i = x_i + x_{n-1-i}
+// (the middle entry of an odd n once) and o_i = x_i - x_{n-1-i}, a transform
+// of length n is two products of half the length, U^T x = [F_e e | F_o o],
+// and back y_i = E_i + O_i, y_{n-1-i} = E_i - O_i with E = V_e c_e,
+// O = V_o c_o: half the products of the dense form.  M^^{-1} splits the same
+// way (fold, two half products, unfold).  Spectral vectors keep the order
+// [even modes | odd modes].
+//
+// The products run as 16x16x4 MFMA tiles (FP64 or FP32 operands, or split
+// BF16, see mm4).  The 1D matrices are stored as MFMA fragments: tile (u, t)
+// of a matrix is 64 x 4 values, lane l holding its four contraction values
+// contiguously, so a fragment is one fully coalesced 16- or 32-byte load per
+// lane from L2.  The contraction index of step i and lane group lk is
+// kmap(lk, i), which is also the row of element i of an MFMA result: a result
+// tile can therefore be the other operand of a following product as it lies
+// in registers.
+//   plane (n <= 128): one i3-plane per workgroup, modes 1 and 2: the plane is
+//     folded into LDS, a wave takes 16 outputs of direction 1 and one parity
+//     through both products without a further barrier or LDS pass;
+//   line: 16 CT columns x the whole direction 2 or 3: mode 3 forward, scaling
+//     and inverse in one pass, or one product;
+//   row: 16 CT lines of direction 1, one product.
+// P_0 is plane, line (mode 3), plane, or, one direction per pass, row, line,
+// line (mode 3), line, row.  Measured, FP64 (us; before: dense products, the
+// whole plane by 16 waves, from 129 per direction six batched GEMMs per
+// component): 32^3 degree 3 20.8 -> 19.1, 61^3 44 -> 30, 96^3 228 -> 124,
+// 192^3 2155 -> 1146, 256^3 degree 2 4930 -> 2750; FP32, 32 right-hand sides
+// at 48^3 degree 2: 676 -> 190.
+#include <algorithm>
+#include <climits>
 #include <type_traits>
 
 #include "hp_internal.h"
@@ -23,24 +48,30 @@ namespace hp {
 
 namespace {
 
-constexpr int FD_THREADS = 256;  // 4 waves
-constexpr int MAXB = 8;          // up to 128 per direction (8 tiles of 16)
+constexpr int FD_PLANE_MAX = 128;     // longest direction of the plane kernel
+constexpr size_t FD_LDS = 160 * 1024;
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
 
+// Operand layout of both 16x16x4 forms: lane l holds A[l%16][l/16] and
+// B[l/16][l%16].  Result element i of lane l is D[kmap(l/16, i)][l%16]; the
+// row map differs between the FP64 and FP32 instructions (measured).
 template <typename T>
 struct Mfma;
-// Operand layout of both 16x16x4 forms: lane l holds A[l%16][l/16] and
-// B[l/16][l%16].  Result element i of lane l is D[row(l/16, i)][l%16]; the
-// row map differs between the FP64 and FP32 instructions (measured).
 template <>
 struct Mfma<double> {
     using V = d4;
     static __device__ __forceinline__ V mma(double a, double b, V c) {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
-    static __device__ __forceinline__ int row(int lk, int i) { return lk + 4 * i; }
+    static __host__ __device__ constexpr int kmap(int lk, int i) { return lk + 4 * i; }
+    // MFMA steps of a 16-wide tile that holds `rem` contraction values (0, 1,
+    // 2 or 4: what tail_steps compiles)
+    static __device__ __forceinline__ int steps(int rem) {
+        return rem > 8 ? 4 : (rem > 4 ? 2 : (rem > 0 ? 1 : 0));
+    }
 };
 template <>
 struct Mfma<float> {
@@ -48,1758 +79,1327 @@ struct Mfma<float> {
     static __device__ __forceinline__ V mma(float a, float b, V c) {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
-    static __device__ __forceinline__ int row(int lk, int i) { return 4 * lk + i; }
+    static __host__ __device__ constexpr int kmap(int lk, int i) { return 4 * lk + i; }
+    static __device__ __forceinline__ int steps(int rem) {
+        return rem > 2 ? 4 : max(rem, 0);
+    }
 };
 
-// acc[b] += sum over k of the 16x16 tile product for output tiles b < nb:
-// one operand (`s`, this lane's value at k-step base kk) is shared by all
-// tiles, the other (`v(b, kk)`) differs per tile.  SHARED_A selects which of
-// the two is the MFMA A operand.  Operands are fetched 16 k-values (4 MFMA
-// k-steps) at a time and the next chunk is fetched while the current one
-// is multiplied, so the L2 latency of the matrix operand overlaps compute.
-template <typename T, bool SHARED_A, typename FS, typename FV>
-__device__ __forceinline__ void mfma_row(typename Mfma<T>::V (&acc)[MAXB], int nb, int K, FS s,
-                                         FV v) {
-    using M = Mfma<T>;
-    T sc[4], vc[4][MAXB];
+// Split-BF16 ("bf16x3") products for FP32 data: each operand is written as
+// hi + lo with hi = bf16(x), lo = bf16(x - hi) (round to nearest even), and
+// A B ~= A_hi B_hi + A_hi B_lo + A_lo B_hi, three 16x16x16 BF16 MFMAs per
+// 16-wide k step accumulated in FP32.  hi + lo keeps 16 significant bits of
+// each operand (relative error up to 2^-17), so a product is good to about
+// 1e-5 relative, not to FP32 rounding; the dropped lo*lo term is of the
+// same order.  A lane supplies the four values k = 16c + 4 lk + j, which is
+// kmap for FP32.
+struct Bf2 {
+    bf4 hi, lo;
+};
+__device__ __forceinline__ Bf2 split_bf16(f4 x) {
+    Bf2 r;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        sc[u] = s(4 * u);
-#pragma unroll
-        for (int b = 0; b < MAXB; ++b) vc[u][b] = (b < nb) ? v(b, 4 * u) : T(0);
+    for (int j = 0; j < 4; ++j) {
+        const __bf16 h = (__bf16)x[j];
+        r.hi[j] = h;
+        r.lo[j] = (__bf16)(x[j] - (float)h);
     }
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        T sn[4], vn[4][MAXB];
-        const bool more = k0 + 16 < K;
-        if (more) {
+    return r;
+}
+
+// acc += A B over the first N (of four) steps of a 16-wide contraction tile, a
+// and b the lane's four values of the two operands.
+template <typename T, bool SPLIT, int N>
+__device__ __forceinline__ void mm(typename Mfma<T>::V& acc, typename Mfma<T>::V a,
+                                   typename Mfma<T>::V b) {
+    if constexpr (SPLIT) {
+        const Bf2 x = split_bf16(a), y = split_bf16(b);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x.hi, y.hi, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x.hi, y.lo, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x.lo, y.hi, acc, 0, 0, 0);
+    } else {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                sn[u] = s(k0 + 16 + 4 * u);
-#pragma unroll
-                for (int b = 0; b < MAXB; ++b) vn[u][b] = (b < nb) ? v(b, k0 + 16 + 4 * u) : T(0);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int b = 0; b < MAXB; ++b)
-                if (b < nb) {
-                    if (SHARED_A) acc[b] = M::mma(sc[u], vc[u][b], acc[b]);
-                    else acc[b] = M::mma(vc[u][b], sc[u], acc[b]);
-                }
-        if (more) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                sc[u] = sn[u];
-#pragma unroll
-                for (int b = 0; b < MAXB; ++b) vc[u][b] = vn[u][b];
-            }
-        }
+        for (int i = 0; i < N; ++i) acc = Mfma<T>::mma(a[i], b[i], acc);
     }
 }
 
-struct XYArgs {
+// Of the nt contraction tiles of a half all but the last are full (he and ho of
+// nN and nM differ by at most one); fn gets the last one's step count as a
+// constant, so that no branch stands between the MFMAs (branches there made
+// the compiler copy the accumulators around: 112 spilled registers).
+template <typename F>
+__device__ __forceinline__ void tail_steps(int st, F fn) {
+    if (st == 4) fn(std::integral_constant<int, 4>{});
+    else if (st == 2) fn(std::integral_constant<int, 2>{});
+    else if (st == 1) fn(std::integral_constant<int, 1>{});
+}
+
+// 1 / x (x > 0, normal): the hardware estimate and two Newton steps, good to
+// about an ulp (a scaling by an eigenvalue sum needs no correctly rounded
+// division, which takes several times the instructions)
+__device__ __forceinline__ double recip(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+// One direction of one field: its length, the sizes of the even and odd
+// halves and the fragment table (forward F, inverse V; for the pressure both
+// are M^^{-1}): nt x nt tiles of the even half, then of the odd half, with
+// nt = half_tiles(nM) for every table.
+template <typename T>
+struct Dir {
+    int n, he, ho;
+    const T* tab;
+};
+template <typename T>
+__device__ __forceinline__ Dir<T> dir_of(const FDTables<T>& t, int f, int d, bool inverse) {
+    const int fam = f == 3 ? 2 : (d == f ? 0 : 1);
+    Dir<T> r;
+    r.n = fam == 0 ? t.nN : t.nM;
+    r.he = (r.n + 1) >> 1;
+    r.ho = r.n >> 1;
+    r.tab = fam == 2 ? t.Mi : (inverse ? t.V[fam] : t.F[fam]);
+    return r;
+}
+template <typename T>
+__device__ __forceinline__ typename Mfma<T>::V frag(const T* tab, int tile, int lane) {
+    return *reinterpret_cast<const typename Mfma<T>::V*>(tab + (tile * 64 + lane) * 4);
+}
+
+// Memory access through buffer resources: a base in scalar registers and a
+// 32-bit byte offset per lane.  Lanes without an element take the offset OOB,
+// beyond every buffer: their loads return zero and their stores are dropped.
+constexpr uint32_t OOB = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* base) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, 0x7ffffff8,
+                                             0x00020000);
+}
+template <typename T>
+__device__ __forceinline__ T bload(const T* base, uint32_t off) {
+    if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(buffer_at(base), (int)off, 0, 0));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(buffer_at(base), (int)off, 0, 0));
+}
+template <typename T>
+__device__ __forceinline__ void bstore(T* base, uint32_t off, T v) {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    if constexpr (sizeof(T) == 8)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), buffer_at(base), (int)off, 0, 0);
+    else
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), buffer_at(base), (int)off, 0, 0);
+}
+
+// Sum over the workgroup in a fixed order (wave trees, then the waves in
+// order); valid in thread 0.  red: one value per wave.
+__device__ __forceinline__ double wg_sum(double s, double* red) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    double t = 0.0;
+    if (threadIdx.x == 0)
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += red[w];
+    return t;
+}
+
+// ---- modes 1 and 2 of one i3-plane -----------------------------------------------------
+struct PlaneArgs {
     const void* in[4];
     void* out[4];
     long long sin[4], sout[4];  // per-rhs strides
     int dims[4][3];
-    int fields_lo, fields_hi;   // field range [lo, hi)
-    int inverse;                // 0: forward (U^T), 1: inverse (U)
-    int accumulate;             // final output: y += result
+    int fields_lo, nf;
+    int inverse;                // velocity: 0 forward (fold, F), 1 inverse (V, unfold)
+    int accumulate;             // inverse: y += result
     // FP64 output only: partial sums of (stored output) . dw per (field,
     // plane) to dpart[r * dp_stride + f * dp_planes + k] (dpart null: none)
     const double* dw[4];        // same layout and rhs stride as out
     double* dpart;
     long long dp_stride;
     int dp_planes;
-    // row-block kernel (k_fd_xy_s) only: row blocks per plane in its grid
-    // order, and the partial of row block b goes to slot + b dp_rb
-    int nrb;
-    long long dp_rb;
     // FP64 input only: for a field with inb[f] set, the input is
-    // ca in + cb inb + cc inc (the same layout as in, rhs strides sinb, sinc)
+    // ca in + cb inb + cc inc (the same layout as in, rhs strides sinb, sinc),
+    // formed in the operation order of the vector kernel k_axpbypcz
     const double* inb[4];
     const double* inc[4];
     long long sinb[4], sinc[4];
     double ca, cb, cc;
 };
 
-// Global-to-LDS staging and the write-outs run in batches: a thread issues
-// the loads of FD_BATCH elements before it uses any of them, so that their
-// latencies overlap (a load, its wait and the LDS write per element in turn
-// would add them up).  Indices past the end are clamped for the load and
-// their values dropped, so no load leaves the array.
-constexpr int FD_BATCH = 8;
-
-// Plane k of field f (n1 x n2 at x) into S, column-major with leading
-// dimension ld, zero padded to N1 x N2.  The forward input is x itself or,
-// when inb[f] is set, the combination ca x + cb inb + cc inc (the same
-// layout; terms with a zero coefficient are not read), formed in the
-// operation order of the vector kernel k_axpbypcz so that it equals reading
-// a materialised result.
-template <typename T, typename TI, int NTH>
-__device__ __forceinline__ void xy_stage(const XYArgs& a, int f, const TI* x, int r,
-                                         long long kofs, T* S, int ld, int n1, int n2, int N1,
-                                         int N2) {
-    const int n = n1 * n2;
-    // the combination's three loads are issued before its arithmetic
-    const double* xb = nullptr;
-    const double* xc = nullptr;
-    if constexpr (std::is_same<TI, double>::value) {
-        if (a.inb[f]) {
-            if (a.cb != 0.0) xb = a.inb[f] + (long long)r * a.sinb[f] + kofs;
-            if (a.cc != 0.0) xc = a.inc[f] + (long long)r * a.sinc[f] + kofs;
-        }
-    }
-    const bool comb = std::is_same<TI, double>::value && a.inb[f] != nullptr;
-    for (int base = 0; base < n; base += FD_BATCH * NTH) {
-        TI vx[FD_BATCH];
-        double vb[FD_BATCH], vc[FD_BATCH];
-#pragma unroll
-        for (int u = 0; u < FD_BATCH; ++u) vx[u] = x[min(base + u * NTH + (int)threadIdx.x, n - 1)];
-        if (xb)
-#pragma unroll
-            for (int u = 0; u < FD_BATCH; ++u)
-                vb[u] = xb[min(base + u * NTH + (int)threadIdx.x, n - 1)];
-        if (xc)
-#pragma unroll
-            for (int u = 0; u < FD_BATCH; ++u)
-                vc[u] = xc[min(base + u * NTH + (int)threadIdx.x, n - 1)];
-#pragma unroll
-        for (int u = 0; u < FD_BATCH; ++u) {
-            const int idx = base + u * NTH + (int)threadIdx.x;
-            if (idx < n) {
-                T v;
-                if (comb) {
-                    double c = a.ca * (double)vx[u];
-                    if (xb) c += a.cb * vb[u];
-                    if (xc) c += a.cc * vc[u];
-                    v = (T)c;
-                } else {
-                    v = (T)vx[u];
-                }
-                const int col = idx / n1;
-                S[col * ld + (idx - col * n1)] = v;
-            }
-        }
-    }
-    const int pr = N1 - n1;
-    for (int idx = threadIdx.x; idx < pr * N2; idx += NTH) {
-        const int col = idx / pr;
-        S[col * ld + n1 + (idx - col * pr)] = T(0);
-    }
-    for (int idx = threadIdx.x; idx < n1 * (N2 - n2); idx += NTH) {
-        const int c = idx / n1;
-        S[(n2 + c) * ld + (idx - c * n1)] = T(0);
-    }
-}
-
-// Rows [r0, r0 + ZR) of field f (rows of length n3 at stride `plane` in x,
-// none at or past `plane`) into S, row-major with leading dimension ld, zero
-// padded to N3 columns and for the missing rows.
-template <typename T, typename TI, int NTH, int ZR>
-__device__ __forceinline__ void z_stage(const TI* x, long long r0, long long plane, int n3,
-                                        int N3, T* S, int ld) {
-    const int n = ZR * n3;
-    for (int base = 0; base < n; base += FD_BATCH * NTH) {
-        T v[FD_BATCH];
-#pragma unroll
-        for (int u = 0; u < FD_BATCH; ++u) {
-            const int idx = base + u * NTH + (int)threadIdx.x;
-            const int kk = idx / ZR, row = idx - kk * ZR;
-            const bool ok = idx < n && r0 + row < plane;
-            const T e = (T)x[ok ? r0 + row + (long long)kk * plane : r0];
-            v[u] = ok ? e : T(0);
-        }
-#pragma unroll
-        for (int u = 0; u < FD_BATCH; ++u) {
-            const int idx = base + u * NTH + (int)threadIdx.x;
-            if (idx < n) {
-                const int kk = idx / ZR, row = idx - kk * ZR;
-                S[row * ld + kk] = v[u];
-            }
-        }
-    }
-    for (int idx = threadIdx.x; idx < ZR * (N3 - n3); idx += NTH) {
-        const int kk = idx / ZR, row = idx - kk * ZR;
-        S[row * ld + n3 + kk] = T(0);
-    }
-}
-
-// The final write-out of plane k of field f from the column-major plane S
-// (leading dimension ld): y = S, or y += S.  With a dot the workgroup also
-// sums (stored value) x dw over the plane, a fixed-order reduction whose
-// scratch reuses S once every read of it is done.
-template <typename T, typename TO, int NTH>
-__device__ __forceinline__ void xy_store(const XYArgs& a, T* S, int ld, int f, int r, int k,
-                                         int n1, int n2) {
-    TO* y = reinterpret_cast<TO*>(a.out[f]) + (long long)r * a.sout[f] + (long long)k * n1 * n2;
-    const int n = n1 * n2;
-    if constexpr (std::is_same<TO, double>::value) {
-        if (a.dpart) {
-            const double* w = a.dw[f] + (long long)r * a.sout[f] + (long long)k * n1 * n2;
-            double s = 0.0;
-            for (int base = 0; base < n; base += FD_BATCH * NTH) {
-                double yv[FD_BATCH], wv[FD_BATCH];
-#pragma unroll
-                for (int u = 0; u < FD_BATCH; ++u) {
-                    const int e = min(base + u * NTH + (int)threadIdx.x, n - 1);
-                    yv[u] = a.accumulate ? y[e] : 0.0;
-                    wv[u] = w[e];
-                }
-#pragma unroll
-                for (int u = 0; u < FD_BATCH; ++u) {
-                    const int idx = base + u * NTH + (int)threadIdx.x;
-                    if (idx < n) {
-                        const int col = idx / n1, row = idx - col * n1;
-                        double v = (double)S[col * ld + row];
-                        if (a.accumulate) v += yv[u];
-                        y[idx] = v;
-                        s += v * wv[u];
-                    }
-                }
-            }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-            __syncthreads();
-            double* red = reinterpret_cast<double*>(S);
-            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                double t = 0.0;
-                for (int wv = 0; wv < NTH / 64; ++wv) t += red[wv];
-                a.dpart[(long long)r * a.dp_stride + (long long)f * a.dp_planes + k] = t;
-            }
-            return;
-        }
-    }
-    if (a.accumulate) {
-        for (int base = 0; base < n; base += FD_BATCH * NTH) {
-            TO yv[FD_BATCH];
-#pragma unroll
-            for (int u = 0; u < FD_BATCH; ++u) yv[u] = y[min(base + u * NTH + (int)threadIdx.x, n - 1)];
-#pragma unroll
-            for (int u = 0; u < FD_BATCH; ++u) {
-                const int idx = base + u * NTH + (int)threadIdx.x;
-                if (idx < n) {
-                    const int col = idx / n1, row = idx - col * n1;
-                    y[idx] = yv[u] + (TO)S[col * ld + row];
-                }
-            }
-        }
-        return;
-    }
-    for (int idx = threadIdx.x; idx < n; idx += NTH) {
-        int col = idx / n1, row = idx - col * n1;
-        y[idx] = (TO)S[col * ld + row];
-    }
-}
-
+// Pitch of the folded plane in LDS: a row holds [even | odd] and is read up to
+// the end of the odd half's last MFMA step; odd, so that the 16 rows of an
+// operand fall in different banks.
 template <typename T>
-__device__ __forceinline__ const T* xy_left(const FDTables<T>& t, int f, int inverse) {
-    if (f == 3) return t.Mi;
-    if (inverse) return f == 0 ? t.UK : t.UT;
-    return f == 0 ? t.UKt : t.UTt;
-}
-template <typename T>
-__device__ __forceinline__ const T* xy_right(const FDTables<T>& t, int f, int inverse) {
-    if (f == 3) return t.Mi;
-    if (inverse) return f == 1 ? t.UKt : t.UTt;
-    return f == 1 ? t.UK : t.UT;
-}
-// the transpose of xy_right (M^^{-1} is symmetric)
-template <typename T>
-__device__ __forceinline__ const T* xy_right_t(const FDTables<T>& t, int f, int inverse) {
-    if (f == 3) return t.Mi;
-    if (inverse) return f == 1 ? t.UK : t.UT;
-    return f == 1 ? t.UKt : t.UTt;
+__host__ __device__ inline int plane_pitch(int n) {
+    const int he = (n + 1) >> 1, ho = n >> 1;
+    int w;
+    if (std::is_same<T, double>::value) {
+        const int a = (he + 3) & ~3, b = he + ((ho + 3) & ~3);
+        w = a > b ? a : b;
+    } else {
+        w = he + ((he + 15) & ~15);
+    }
+    return w | 1;
 }
 
-template <typename T, typename TI, typename TO, bool STAGE>
-__global__ __launch_bounds__(FD_THREADS) void k_fd_xy(XYArgs a, FDTables<T> t) {
+// NT: tiles per half direction (nM's).  Wave (a, u1): D1 = X^T L^T for the 16
+// outputs i' of parity a and tile u1 of direction 1 and every j (contraction
+// over i, operands LDS and fragments held in registers), then D2 = R^T D1 per
+// parity of direction 2 (contraction over j = the rows of D1, which lie in
+// the registers as the B operand).  Up to two tiles per half (n <= 64) the
+// two parities of direction 2 go to two waves, for shorter chains.
+// The fragments of the second product are loaded RING - 1 tiles ahead, the
+// first ones before the plane.
+// What bounds it: MFMA issue (64 cycles per FP64 instruction), and at small
+// meshes the latency of launch, staging and write-out.
+template <typename T, typename TI, typename TO, bool SPLIT, int NT>
+__global__ __launch_bounds__(NT <= 2 ? 256 * NT : 128 * NT)
+__attribute__((amdgpu_waves_per_eu(4))) void k_fd_plane(PlaneArgs a,
+                                                                             FDTables<T> t) {
     using M = Mfma<T>;
     using V = typename M::V;
+    constexpr int NB = NT <= 2 ? 1 : 2;   // parities of direction 2 per wave
+    constexpr int NTH = (NB == 1 ? 256 : 128) * NT;
+    constexpr int RING = 4, NF = NB * NT * NT;
     extern __shared__ unsigned char smem_raw[];
     T* S = reinterpret_cast<T*>(smem_raw);
-    const int nf = a.fields_hi - a.fields_lo;
-    const int f = a.fields_lo + (int)(blockIdx.y % nf);
-    const int r = (int)(blockIdx.y / nf);
+    const int f = a.fields_lo + (int)(blockIdx.y % a.nf);
+    const int r = (int)(blockIdx.y / a.nf);
     const int k = blockIdx.x;
-    const int n1 = a.dims[f][0], n2 = a.dims[f][1], n3 = a.dims[f][2];
-    if (k >= n3) return;
-    const int N1 = (n1 + 15) & ~15, N2 = (n2 + 15) & ~15;
-    const int ld = N1 + 1;  // column-major plane, padded leading dimension
-    const int nb1 = N1 >> 4, nb2 = N2 >> 4;
+    const int n1 = a.dims[f][0], n2 = a.dims[f][1];
+    if (k >= a.dims[f][2]) return;
+    const bool pres = f == 3;
+    const bool fold = !a.inverse, unfold = a.inverse || pres;
+    const Dir<T> d1 = dir_of(t, f, 0, a.inverse), d2 = dir_of(t, f, 1, a.inverse);
+    const int he1 = d1.he, ho1 = d1.ho, he2 = d2.he, ho2 = d2.ho;
+    const int ld = plane_pitch<T>(n1);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lr = lane & 15, lk = lane >> 4;
+    const int pa = wave & 1, u1 = (wave >> 1) % NT, b0 = NB == 1 ? wave / (2 * NT) : 0;
+    const int ha = pa ? ho1 : he1, offa = pa ? he1 : 0;
+    const bool mine = 16 * u1 < ha;
+    // this wave's fragments of L, and the first of R^T (tile w: parity
+    // b0 + w / NT^2, output tile (w / NT) % NT, contraction tile w % NT)
+    V bl[NT], fr[RING];
+    const T* tl = d1.tab + (pa * NT + u1) * NT * 256;
+    const T* tr = d2.tab + b0 * NT * NT * 256;
+    if (mine) {
+#pragma unroll
+        for (int q = 0; q < NT; ++q) bl[q] = frag(tl, q, lane);
+#pragma unroll
+        for (int w = 0; w < RING - 1; ++w)
+            if (w < NF) fr[w] = frag(tr, w, lane);
+    }
     const long long kofs = (long long)k * n1 * n2;
     const TI* x = reinterpret_cast<const TI*>(a.in[f]) + (long long)r * a.sin[f] + kofs;
-    // load plane (zero padded)
-    xy_stage<T, TI, FD_THREADS>(a, f, x, r, kofs, S, ld, n1, n2, N1, N2);
+    // a thread's groups (i, j): i, j of the first, advanced by NTH groups
+    const int ng = he1 * he2, dj = NTH / he1, di = NTH - dj * he1;
+    const int j00 = (int)threadIdx.x / he1, i00 = (int)threadIdx.x - j00 * he1;
+    // the offsets of the four mirror images of (i, j)
+    auto mirror = [&](int i, int j, int (&o)[4]) {
+        const int p0 = j * n1, p1 = (n2 - 1 - j) * n1, i1 = n1 - 1 - i;
+        o[0] = p0 + i;
+        o[1] = p0 + i1;
+        o[2] = p1 + i;
+        o[3] = p1 + i1;
+    };
+    auto next = [&](int& i, int& j) {
+        i += di;
+        j += dj;
+        if (i >= he1) {
+            i -= he1;
+            ++j;
+        }
+    };
+    if (fold) {
+        const double* xb = nullptr;
+        const double* xc = nullptr;
+        bool comb = false;
+        if constexpr (std::is_same<TI, double>::value) {
+            if (a.inb[f]) {
+                comb = true;
+                if (a.cb != 0.0) xb = a.inb[f] + (long long)r * a.sinb[f] + kofs;
+                if (a.cc != 0.0) xc = a.inc[f] + (long long)r * a.sinc[f] + kofs;
+            }
+        }
+        int i0 = i00, j0 = j00;
+        for (int base = threadIdx.x; base < ng; base += 2 * NTH) {
+            TI v[2][4];
+            double vb[2][4], vc[2][4];
+            int gi[2], gj[2];
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const bool on = base + g * NTH < ng;
+                gi[g] = on ? i0 : 0;
+                gj[g] = on ? j0 : 0;
+                next(i0, j0);
+                int o[4];
+                mirror(gi[g], gj[g], o);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[g][q] = x[o[q]];
+                if (xb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) vb[g][q] = xb[o[q]];
+                if (xc)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) vc[g][q] = xc[o[q]];
+            }
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                if (base + g * NTH >= ng) break;
+                if (comb) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        double c = a.ca * (double)v[g][q];
+                        if (xb) c += a.cb * vb[g][q];
+                        if (xc) c += a.cc * vc[g][q];
+                        v[g][q] = (TI)c;
+                    }
+                }
+                const int i = gi[g], j = gj[g];
+                const bool im = i >= ho1, jm = j >= ho2;  // the middle of an odd length
+                const TI ep = im ? v[g][0] : v[g][0] + v[g][1], op = v[g][0] - v[g][1];
+                const TI eq = im ? v[g][2] : v[g][2] + v[g][3], oq = v[g][2] - v[g][3];
+                S[j * ld + i] = (T)(jm ? ep : ep + eq);
+                if (!im) S[j * ld + he1 + i] = (T)(jm ? op : op + oq);
+                if (!jm) S[(he2 + j) * ld + i] = (T)(ep - eq);
+                if (!im && !jm) S[(he2 + j) * ld + he1 + i] = (T)(op - oq);
+            }
+        }
+    } else {
+        const int n = n1 * n2;
+        for (int base = threadIdx.x; base < n; base += 4 * NTH) {
+            TI v[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) v[g] = x[min(base + g * NTH, n - 1)];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int idx = base + g * NTH;
+                if (idx < n) {
+                    const int j = idx / n1;
+                    S[j * ld + (idx - j * n1)] = (T)v[g];
+                }
+            }
+        }
+    }
+    {
+        // the columns past n1 that a last MFMA step reads (times zeros)
+        const int pw = ld - n1;
+        for (int idx = threadIdx.x; idx < pw * n2; idx += NTH) {
+            const int j = idx / pw;
+            S[j * ld + n1 + (idx - j * pw)] = T(0);
+        }
+    }
     __syncthreads();
-    const T* L = xy_left(t, f, a.inverse);
-    const T* R = xy_right(t, f, a.inverse);
-    const int ldL = (f == 0) ? t.NNp : t.NMp;
-    const int ldR = (f == 1) ? t.NNp : t.NMp;
-    if (STAGE) {
-        // small directions: the two dense 1D matrices move to LDS once
-        T* Ls = S + N2 * ld;
-        T* Rs = Ls + N1 * N1;
-        for (int idx = threadIdx.x; idx < N1 * N1; idx += FD_THREADS) Ls[idx] = L[idx];
-        for (int idx = threadIdx.x; idx < N2 * N2; idx += FD_THREADS) Rs[idx] = R[idx];
-        L = Ls;
-        R = Rs;
+    V D1[NB][NT];
+    if (mine) {
+        int row[NB][NT];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int q = 0; q < NT; ++q) {
+                // rows past the half multiply zeros in the second product
+                row[b][q] = min((b0 + b ? he2 : 0) + 16 * q + lr, n2 - 1) * ld + offa;
+                D1[b][q] = V{0, 0, 0, 0};
+            }
+        auto tile = [&](int c, auto steps) {
+            constexpr int N = decltype(steps)::value;
+            V av[NB][NT];
+#pragma unroll
+            for (int i = 0; i < (SPLIT ? 4 : N); ++i)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int q = 0; q < NT; ++q)
+                        av[b][q][i] = S[row[b][q] + 16 * c + M::kmap(lk, i)];
+            if constexpr (SPLIT) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int q = 0; q < NT; ++q) mm<T, true, 4>(D1[b][q], av[b][q], bl[c]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < N; ++i)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+#pragma unroll
+                        for (int q = 0; q < NT; ++q)
+                            D1[b][q] = M::mma(av[b][q][i], bl[c][i], D1[b][q]);
+            }
+        };
+#pragma unroll
+        for (int c = 0; c + 1 < NT; ++c) tile(c, std::integral_constant<int, 4>{});
+        tail_steps(M::steps(ha - 16 * (NT - 1)), [&](auto st) { tile(NT - 1, st); });
+    }
+    TO* y = reinterpret_cast<TO*>(a.out[f]) + (long long)r * a.sout[f] + kofs;
+    if (unfold) __syncthreads();  // every wave is done with the input plane
+    if (mine) {
+        const int col = 16 * u1 + lr;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int hb = b0 + b ? ho2 : he2, offb = b0 + b ? he2 : 0;
+#pragma unroll
+            for (int u = 0; u < NT; ++u) {
+                V acc = {0, 0, 0, 0};
+#pragma unroll
+                for (int q = 0; q < NT; ++q) {
+                    const int w = (b * NT + u) * NT + q;
+                    if (w + RING - 1 < NF) fr[(w + RING - 1) % RING] = frag(tr, w + RING - 1, lane);
+                    if (q + 1 < NT)
+                        mm<T, SPLIT, 4>(acc, fr[w % RING], D1[b][q]);
+                    else
+                        tail_steps(M::steps(hb - 16 * q), [&](auto st) {
+                            mm<T, SPLIT, decltype(st)::value>(acc, fr[w % RING], D1[b][q]);
+                        });
+                }
+                if (col < ha)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int j = 16 * u + M::kmap(lk, i);
+                        if (j < hb) {
+                            if (unfold) S[(offb + j) * ld + offa + col] = acc[i];
+                            else y[(offb + j) * n1 + offa + col] = (TO)acc[i];
+                        }
+                    }
+            }
+        }
+    }
+    if (!unfold) return;
+    __syncthreads();
+    // y = unfold(S), or y += unfold(S): the four mirror images of (i, j)
+    const bool dot = std::is_same<TO, double>::value && a.dpart != nullptr;
+    const double* w = dot ? a.dw[f] + (long long)r * a.sout[f] + kofs : nullptr;
+    double sum = 0.0;
+    int i0 = i00, j0 = j00;
+    for (int base = threadIdx.x; base < ng; base += 2 * NTH) {
+        TO yv[2][4];
+        double wv[2][4];
+        int o[2][4], gi[2], gj[2];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const bool on = base + g * NTH < ng;
+            gi[g] = on ? i0 : 0;
+            gj[g] = on ? j0 : 0;
+            next(i0, j0);
+            mirror(gi[g], gj[g], o[g]);
+            if (a.accumulate)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) yv[g][q] = y[o[g][q]];
+            if (dot)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) wv[g][q] = w[o[g][q]];
+        }
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            if (base + g * NTH >= ng) break;
+            const int i = gi[g], j = gj[g];
+            const bool im = i >= ho1, jm = j >= ho2;
+            const T ee = S[j * ld + i], oe = im ? T(0) : S[j * ld + he1 + i];
+            const T eo = jm ? T(0) : S[(he2 + j) * ld + i];
+            const T oo = (im || jm) ? T(0) : S[(he2 + j) * ld + he1 + i];
+            const T pe = ee + oe, po = eo + oo, me = ee - oe, mo = eo - oo;
+            const T v[4] = {pe + po, me + mo, pe - po, me - mo};
+            const bool on[4] = {true, !im, !jm, !im && !jm};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (on[q]) {
+                    TO s = (TO)v[q];
+                    if (a.accumulate) s += yv[g][q];
+                    y[o[g][q]] = s;
+                    if (dot) sum += (double)s * wv[g][q];
+                }
+        }
+    }
+    if (dot) {
         __syncthreads();
+        const double s = wg_sum(sum, reinterpret_cast<double*>(smem_raw));
+        if (threadIdx.x == 0)
+            a.dpart[(long long)r * a.dp_stride + (long long)f * a.dp_planes + k] = s;
     }
-    // step 1: T = L X, in place by column blocks
-    for (int cb = wave; cb < nb2; cb += 4) {
-        V acc[MAXB];
-#pragma unroll
-        for (int b = 0; b < MAXB; ++b) acc[b] = V{0, 0, 0, 0};
-        mfma_row<T, false>(
-            acc, nb1, N1, [&](int kk) { return S[(cb * 16 + lr) * ld + kk + lk]; },
-            [&](int b, int kk) { return L[(b * 16 + lr) * ldL + kk + lk]; });
-#pragma unroll
-        for (int b = 0; b < MAXB; ++b)
-            if (b < nb1) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    S[(cb * 16 + lr) * ld + b * 16 + M::row(lk, i)] = acc[b][i];
-            }
-    }
-    __syncthreads();
-    // step 2: Y = T R by row blocks; result back into own rows of S
-    for (int rb = wave; rb < nb1; rb += 4) {
-        V acc[MAXB];
-#pragma unroll
-        for (int b = 0; b < MAXB; ++b) acc[b] = V{0, 0, 0, 0};
-        mfma_row<T, true>(
-            acc, nb2, N2, [&](int kk) { return S[(kk + lk) * ld + rb * 16 + lr]; },
-            [&](int b, int kk) { return R[(kk + lk) * ldR + b * 16 + lr]; });
-#pragma unroll
-        for (int b = 0; b < MAXB; ++b)
-            if (b < nb2) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    S[(b * 16 + lr) * ld + rb * 16 + M::row(lk, i)] = acc[b][i];
-            }
-    }
-    __syncthreads();
-    xy_store<T, TO, FD_THREADS>(a, S, ld, f, r, k, n1, n2);
 }
 
-constexpr int ZROWS = 64;      // (i1,i2)-rows per z workgroup: 16 per wave
-
-struct ZArgs {
+// ---- one direction per pass ----------------------------------------------------------------
+// A workgroup takes a tile: 16 CT columns or lines of one field, right-hand
+// side and, for direction 2, i3-plane; each XCD a contiguous range of the
+// tiles.  Wave w takes output tile u = w of both parities, so that the unfold
+// y = E +- O happens in registers; beyond one tile per wave the further ones
+// are dealt round-robin from a start that changes with the workgroup, so that
+// a short last round does not always load the same SIMD.  Eight waves from
+// nt = 8 on: two per SIMD (nine, one per tile at 257 per direction, left room
+// for one workgroup per CU only).  Several workgroups per CU overlap one's loads and stores with
+// another's products; looking ahead to the next tile in registers instead
+// (one resident workgroup walking several tiles) spilled and was slower.
+struct LineArgs {
     const void* in[4];
     void* out[4];
     long long sin[4], sout[4];
     int dims[4][3];
-    int fields_lo, fields_hi;
-    int accumulate;   // bit f set: field f is added to its output
+    int fields_lo, nf;
+    int dir;          // 0: row kernel, 1: direction 2, 2: direction 3
+    int inverse;      // one product: 0 forward (fold, F), 1 inverse (V, unfold)
+    int fused;        // direction 3: the velocity's forward product, scaling and inverse product
+    int accumulate;   // bit f: field f is added to its output
+    int ctiles, nbatch, ntiles;  // tiles per (field, rhs, plane), planes, tiles in all
     double two_nu;
     double omega;     // damping factor of P_0^{-1} (1: the plain base preconditioner)
+    double pscale;    // the pressure's product is multiplied by this
     // FP64 output, launches of one field only: partial sums of (stored
-    // output) . dw per workgroup to dpart[r * dp_stride + blockIdx.x]
+    // output) . dw per tile to dpart[r * dp_stride + tile]
     const double* dw;  // same layout and rhs stride as the output
     double* dpart;
     long long dp_stride;
 };
 
-// The final write-out of z rows [r0, r0 + ZR) of field f from the
-// row-major buffer Out (leading dimension ld): y = Out or y += Out; with a
-// dot also the workgroup's fixed-order sum of (stored value) x dw, whose
-// scratch reuses S once every read of the LDS buffers is done.
-template <typename T, typename TO, int NTH, int ZR = ZROWS>
-__device__ __forceinline__ void z_store(const ZArgs& a, const T* Out, T* S, int ld, int f, int r,
-                                        long long r0, long long plane, int n3) {
-    TO* y = reinterpret_cast<TO*>(a.out[f]) + (long long)r * a.sout[f];
-    const int n = ZR * n3;
-    const bool acc = (a.accumulate >> f) & 1;
-    if constexpr (std::is_same<TO, double>::value) {
-        if (a.dpart) {
-            const double* w = a.dw + (long long)r * a.sout[f];
-            double s = 0.0;
-            for (int base = 0; base < n; base += FD_BATCH * NTH) {
-                double yv[FD_BATCH], wv[FD_BATCH];
-#pragma unroll
-                for (int u = 0; u < FD_BATCH; ++u) {
-                    const int idx = base + u * NTH + (int)threadIdx.x;
-                    const int kk = idx / ZR, row = idx - kk * ZR;
-                    const long long o =
-                        idx < n && r0 + row < plane ? r0 + row + (long long)kk * plane : r0;
-                    yv[u] = acc ? y[o] : 0.0;
-                    wv[u] = w[o];
-                }
-#pragma unroll
-                for (int u = 0; u < FD_BATCH; ++u) {
-                    const int idx = base + u * NTH + (int)threadIdx.x;
-                    const int kk = idx / ZR, row = idx - kk * ZR;
-                    if (idx < n && r0 + row < plane) {
-                        const long long o = r0 + row + (long long)kk * plane;
-                        double v = (double)Out[row * ld + kk];
-                        if (acc) v += yv[u];
-                        y[o] = v;
-                        s += v * wv[u];
-                    }
-                }
-            }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-            __syncthreads();
-            double* red = reinterpret_cast<double*>(S);
-            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                double t = 0.0;
-                for (int wv = 0; wv < NTH / 64; ++wv) t += red[wv];
-                a.dpart[(long long)r * a.dp_stride + blockIdx.x] = t;
-            }
-            return;
-        }
-    }
-    if (acc) {
-        for (int base = 0; base < n; base += FD_BATCH * NTH) {
-            TO yv[FD_BATCH];
-#pragma unroll
-            for (int u = 0; u < FD_BATCH; ++u) {
-                const int idx = base + u * NTH + (int)threadIdx.x;
-                const int kk = idx / ZR, row = idx - kk * ZR;
-                yv[u] = y[idx < n && r0 + row < plane ? r0 + row + (long long)kk * plane : r0];
-            }
-#pragma unroll
-            for (int u = 0; u < FD_BATCH; ++u) {
-                const int idx = base + u * NTH + (int)threadIdx.x;
-                const int kk = idx / ZR, row = idx - kk * ZR;
-                if (idx < n && r0 + row < plane)
-                    y[r0 + row + (long long)kk * plane] = yv[u] + (TO)Out[row * ld + kk];
-            }
-        }
-        return;
-    }
-    for (int idx = threadIdx.x; idx < n; idx += NTH) {
-        int kk = idx / ZR, row = idx - kk * ZR;
-        if (r0 + row >= plane) continue;
-        y[r0 + row + (long long)kk * plane] = (TO)Out[row * ld + kk];
-    }
+template <typename T, int CT>
+constexpr int line_pitch() {
+    // FP32 operands read rows 4 apart: 4 more words put them in other banks
+    return 16 * CT + (std::is_same<T, double>::value ? 0 : 4);
 }
 
+// Workgroups are dealt round-robin to the 8 XCDs in launch order: workgroup i
+// to the tile, so that an XCD's tiles are one contiguous range.
+__device__ __forceinline__ int xcd_tile(int i, int total) {
+    const int per = total / 8, rem = total % 8, x = i % 8;
+    return x * per + min(x, rem) + i / 8;
+}
 
-template <typename T, typename TI, typename TO, bool STAGE>
-__global__ __launch_bounds__(FD_THREADS) void k_fd_z(ZArgs a, FDTables<T> t) {
+struct Tile {
+    int c, b, f, r;  // column tile, plane, field, right-hand side
+};
+__device__ __forceinline__ Tile tile_of(const LineArgs& a, int id) {
+    Tile w;
+    w.c = id % a.ctiles;
+    id /= a.ctiles;
+    w.b = id % a.nbatch;
+    id /= a.nbatch;
+    w.f = a.fields_lo + id % a.nf;
+    w.r = id / a.nf;
+    return w;
+}
+
+// Both parities of one product with the fragments of tab, output tile u:
+// acc[h][c] += table tile . operand, operand value i of lane (lr, lk) from
+// opnd(h, c, 16 s, i), i.e. contraction index 16 s + kmap(lk, i).  TA: the
+// table is the A operand.
+// Fragments are loaded ahead: a contraction tile of both parities (two tiles
+// in registers) or, LEAN, one parity's fragment (the directions beyond 128,
+// where the registers saved give a second workgroup per CU).
+template <typename T, bool SPLIT, bool TA, int CT, bool LEAN>
+struct HalfProduct {
     using M = Mfma<T>;
     using V = typename M::V;
-    extern __shared__ unsigned char smem_raw[];
-    T* S = reinterpret_cast<T*>(smem_raw);
-    const int nf = a.fields_hi - a.fields_lo;
-    const int f = a.fields_lo + (int)(blockIdx.y % nf);
-    const int r = (int)(blockIdx.y / nf);
-    const int n1 = a.dims[f][0], n2 = a.dims[f][1], n3 = a.dims[f][2];
-    const long long plane = (long long)n1 * n2;
-    const long long r0 = (long long)blockIdx.x * ZROWS;
-    if (r0 >= plane) return;
-    const int N3 = (n3 + 15) & ~15;
-    const int ld = N3 + 1;  // row-major [row][k]
-    const int nb3 = N3 >> 4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int lr = lane & 15, lk = lane >> 4;
-    const TI* x = reinterpret_cast<const TI*>(a.in[f]) + (long long)r * a.sin[f];
-    z_stage<T, TI, FD_THREADS, ZROWS>(x, r0, plane, n3, N3, S, ld);
-    const bool pres = (f == 3);
-    const T* U3 = pres ? t.Mi : (f == 2 ? t.UK : t.UT);
-    const T* U3t = pres ? t.Mi : (f == 2 ? t.UKt : t.UTt);
-    const int ldU = (f == 2) ? t.NNp : t.NMp;
-    if (STAGE) {
-        T* Us = S + ZROWS * ld;
-        T* Uts = Us + N3 * N3;
-        for (int idx = threadIdx.x; idx < N3 * N3; idx += FD_THREADS) {
-            Us[idx] = U3[idx];
-            if (!pres) Uts[idx] = U3t[idx];
+    const T* tab;
+    int u, nt, he, ho, lane;
+    V g0[2], g1[2];  // LEAN: g0[0] and g1[0] only
+    __device__ __forceinline__ V load(int s, int h) const {
+        return frag(tab, (h * nt + u) * nt + min(s, nt - 1), lane);
+    }
+    // the first fragments, to be in flight before the operand is ready
+    __device__ __forceinline__ void prime(const T* table) {
+        tab = table;
+        g0[0] = load(0, 0);
+        if constexpr (LEAN) {
+            g1[0] = 16 * u < ho ? load(0, 1) : load(1, 0);
+        } else {
+            g0[1] = load(0, 1);
+            g1[0] = load(1, 0);
+            g1[1] = load(1, 1);
         }
-        U3 = Us;
-        U3t = pres ? Us : Uts;  // M^^{-1} is symmetric: one staged copy serves both
+    }
+    // N steps of tile s of parity h with the fragment g
+    template <int N, typename F>
+    __device__ __forceinline__ void step(const V& g, int s, int h, V (&acc)[CT], F opnd) const {
+        V b[CT];
+#pragma unroll
+        for (int i = 0; i < (SPLIT ? 4 : N); ++i)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) b[c][i] = opnd(h, c, 16 * s, i);
+        if constexpr (SPLIT) {
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                if (TA) mm<T, true, 4>(acc[c], g, b[c]);
+                else mm<T, true, 4>(acc[c], b[c], g);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+                    acc[c] = TA ? M::mma(g[i], b[c][i], acc[c]) : M::mma(b[c][i], g[i], acc[c]);
+        }
+    }
+    // NH parities (1: there is no odd output tile u)
+    template <int NH, typename F>
+    __device__ __forceinline__ void loop(V (&acc)[2][CT], F opnd) {
+#pragma unroll 1
+        for (int s = 0; s + 1 < nt; ++s) {
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+                if constexpr (LEAN) {
+                    step<4>(g0[0], s, h, acc[h], opnd);
+                    g0[0] = g1[0];
+                    g1[0] = NH == 2 ? load(s + 1, h) : load(s + 2, 0);
+                } else {
+                    step<4>(g0[h], s, h, acc[h], opnd);
+                    g0[h] = g1[h];
+                    g1[h] = load(s + 2, h);
+                }
+            }
+        }
+        // the even half's steps serve the odd half too (no more than one fewer)
+        tail_steps(M::steps(he - 16 * (nt - 1)), [&](auto st) {
+            constexpr int N = decltype(st)::value;
+            step<N>(g0[0], nt - 1, 0, acc[0], opnd);
+            if (NH == 2) step<N>(LEAN ? g1[0] : g0[1], nt - 1, 1, acc[1], opnd);
+        });
+    }
+    template <typename F>
+    __device__ __forceinline__ void run(V (&acc)[2][CT], F opnd) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) acc[h][c] = V{0, 0, 0, 0};
+        if (16 * u < ho) loop<2>(acc, opnd);
+        else loop<1>(acc, opnd);
+    }
+};
+
+// Direction 2 or 3 of 16 CT columns: the columns are contiguous (the B
+// operand, [k][column] in LDS), the table is the A operand.  Mode 3 forward,
+// scaling by omega / (2 nu (l1 + l2 + l3)) and inverse run in one pass: the
+// scaled tiles of the first product replace its operand in LDS.
+template <typename T, typename TI, typename TO, bool SPLIT, int CT, int NW>
+__global__ __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(4))) void k_fd_line(LineArgs a, FDTables<T> t) {
+    using M = Mfma<T>;
+    using V = typename M::V;
+    constexpr int W = 16 * CT, P = line_pitch<T, CT>();
+    constexpr int U = NW == 4 ? 1 : (NW == 8 ? 2 : 3);
+    // pairs (k, n-1-k) a thread has in flight: the whole tile to 320 per direction
+    constexpr int NG = NW == 4 ? 4 * CT : (NW == 8 ? 10 : 4);
+    extern __shared__ unsigned char smem_raw[];
+    const int nt = t.nt;
+    T* X[2];
+    X[0] = reinterpret_cast<T*>(smem_raw);
+    X[1] = X[0] + 16 * nt * P;
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lr = lane & 15, lk = lane >> 4;
+    const bool d3 = a.dir == 2;
+    const int sc = threadIdx.x % W, sk = threadIdx.x / W, ks = blockDim.x / W;
+    const int turn = (wave + (int)blockIdx.x) % nw;
+    auto tile_u = [&](int q) { return q == 0 ? wave : q * nw + turn; };
+    const Tile w = tile_of(a, xcd_tile(blockIdx.x, a.ntiles));
+    const int f = w.f, r = w.r;
+    const int n1 = a.dims[f][0];
+    const unsigned plane = (unsigned)n1 * a.dims[f][1];
+    const unsigned ncol = d3 ? plane : (unsigned)n1;  // columns, and the direction's stride
+    const unsigned c0 = (unsigned)w.c * W;
+    if (c0 >= ncol || (!d3 && w.b >= a.dims[f][2])) return;
+    const long long ofs = (d3 ? 0 : (long long)w.b * plane) + c0;
+    const bool pres = f == 3, second = a.fused && !pres;
+    const bool fold = !a.inverse, unfold = a.inverse || a.fused || pres;
+    const Dir<T> d = dir_of(t, f, a.dir, a.inverse);
+    const int n = d.n, he = d.he, ho = d.ho;
+    HalfProduct<T, SPLIT, true, CT, NW == 8> hp;
+    hp.u = min(wave, nt - 1);
+    hp.nt = nt;
+    hp.he = he;
+    hp.ho = ho;
+    hp.lane = lane;
+    hp.prime(d.tab);
+    {
+        // the pairs (k, n-1-k) (or (k, he + k)), k = kb + sk + g ks
+        const TI* x = reinterpret_cast<const TI*>(a.in[f]) + (long long)r * a.sin[f] + ofs;
+        const bool in = c0 + sc < ncol;
+        const uint32_t o0 = (uint32_t)sizeof(TI) * (sk * ncol + sc);
+        const uint32_t o1 = (uint32_t)sizeof(TI) * ((ks - 1 - sk) * ncol + sc);
+#pragma unroll 1
+        for (int kb = 0; kb < 16 * nt; kb += NG * ks) {
+            TI v[NG][2];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const int k = kb + g * ks;  // of the lanes with sk = 0
+                const bool on = in && k + sk < he;
+                v[g][0] = bload(x + (long long)k * ncol, on ? o0 : OOB);
+                v[g][1] = fold ? bload(x + (long long)(n - k - ks) * ncol, on ? o1 : OOB)
+                               : bload(x + (long long)(he + k) * ncol, in && k + sk < ho ? o0 : OOB);
+            }
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const int k = kb + sk + g * ks;
+                if (k >= 16 * nt) break;
+                TI e = v[g][0], o = v[g][1];
+                if (fold) {
+                    o = v[g][0] - v[g][1];
+                    e = k < ho ? v[g][0] + v[g][1] : v[g][0];
+                }
+                X[0][k * P + sc] = (T)e;
+                X[1][k * P + sc] = k < ho ? (T)o : T(0);
+            }
+        }
     }
     __syncthreads();
-    T* Sw = S + wave * 16 * ld;  // this wave's 16 rows
-    const long long w0 = r0 + wave * 16;
-    // Y = X U3
-    V acc[MAXB];
+    V acc[U][2][CT];
+    auto opnd = [&](int h, int c, int k, int i) {
+        return X[h][(k + M::kmap(lk, i)) * P + 16 * c + lr];
+    };
+    auto product = [&](const T* tab) {
 #pragma unroll
-    for (int b = 0; b < MAXB; ++b) acc[b] = V{0, 0, 0, 0};
-    if (w0 < plane)
-        mfma_row<T, true>(
-            acc, nb3, N3, [&](int kk) { return Sw[lr * ld + kk + lk]; },
-            [&](int b, int kk) { return U3[(kk + lk) * ldU + b * 16 + lr]; });
-    if (pres) {
+        for (int q = 0; q < U; ++q) {
+            const int u = tile_u(q);
+            if (u >= nt) break;
+            if (q > 0) {
+                hp.u = u;
+                hp.prime(tab);
+            }
+            hp.run(acc[q], opnd);
+        }
+    };
+    product(d.tab);
+    if (second) {
+        const T* tab2 = dir_of(t, f, a.dir, true).tab;
+        hp.u = min(wave, nt - 1);
+        hp.prime(tab2);
+        const double* t1 = t.lam[f == 0 ? 0 : 1];
+        const double* t2 = t.lam[f == 1 ? 0 : 1];
+        const double* t3 = t.lam[f == 2 ? 0 : 1];
+        double l12[CT];
 #pragma unroll
-        for (int b = 0; b < MAXB; ++b)
-            if (b < nb3)
+        for (int c = 0; c < CT; ++c) {
+            const unsigned rr = min(c0 + 16 * c + lr, ncol - 1);
+            const unsigned i2 = rr / (unsigned)n1;
+            l12[c] = t1[rr - i2 * n1] + t2[i2];
+        }
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    Sw[M::row(lk, i) * ld + b * 16 + lr] =
-                        (T)(a.omega * a.two_nu * (double)acc[b][i]);
-    } else {
-        // scale by 1 / (2 nu (l1 + l2 + l3)) and transform back: Z = Y U3^T
-        const double* l1 = (f == 0) ? t.lamK : t.lamT;
-        const double* l2 = (f == 1) ? t.lamK : t.lamT;
-        const double* l3 = (f == 2) ? t.lamK : t.lamT;
+        for (int q = 0; q < U; ++q) {
+            const int u = tile_u(q);
+            if (u >= nt) break;
 #pragma unroll
-        for (int b = 0; b < MAXB; ++b)
-            if (b < nb3)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int row = M::row(lk, i);
-                    const long long rr = w0 + row;
-                    const int col = b * 16 + lr;
-                    double sc = 0.0;
-                    if (rr < plane && col < n3) {
-                        const int i1 = (int)(rr % n1), i2 = (int)(rr / n1);
-                        sc = a.omega / (a.two_nu * (l1[i1] + l2[i2] + l3[col]));
-                    }
-                    Sw[row * ld + col] = (T)(sc * (double)acc[b][i]);
+                    const int m = 16 * u + M::kmap(lk, i);
+                    const bool ok = m < (h ? ho : he);
+                    const double l3 = t3[min(h * he + m, n - 1)];
+#pragma unroll
+                    for (int c = 0; c < CT; ++c)
+                        acc[q][h][c][i] = ok ? (T)(a.omega * recip(a.two_nu * (l12[c] + l3)) *
+                                                   (double)acc[q][h][c][i])
+                                             : T(0);
                 }
-#pragma unroll
-        for (int b = 0; b < MAXB; ++b) acc[b] = V{0, 0, 0, 0};
-        if (w0 < plane)
-            mfma_row<T, true>(
-                acc, nb3, N3, [&](int kk) { return Sw[lr * ld + kk + lk]; },
-                [&](int b, int kk) { return U3t[(kk + lk) * ldU + b * 16 + lr]; });
-#pragma unroll
-        for (int b = 0; b < MAXB; ++b)
-            if (b < nb3)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) Sw[M::row(lk, i) * ld + b * 16 + lr] = acc[b][i];
-    }
-    __syncthreads();
-    z_store<T, TO, FD_THREADS>(a, S, S, ld, f, r, r0, plane, n3);
-}
-
-// ---- tile-per-wave variants ----------------------------------------------------------
-// Each wave owns one 16x16 output tile at a time (16 waves per workgroup), so
-// every dependency chain is one tile's k-loop; the two GEMM steps use
-// separate LDS buffers.  Used when both buffers (and, when small enough,
-// the two dense 1D matrices) fit in LDS.
-constexpr int FD_WIDE = 1024;   // 16 waves
-
-// D = A B on one 16x16 tile, K <= 128 (a multiple of 16).  One operand, G,
-// is stored with contiguous k: G(idx, k) = G[idx*ldg + k] (global memory or
-// an LDS copy); the other, H, is in LDS: H(k, idx) = H[k*h_k + idx*h_i].
-// GA: G is the A operand (rows of D), else the B operand (columns of D).
-// The contraction order over k is free as long as both operands use the same
-// one: in k-chunk c (16 wide), MFMA step s, lane (lr, lk) supplies
-// k = 16c + 4 lk + s, so its four G values of a chunk are contiguous and
-// arrive in one vector load, issued one chunk ahead of their products.
-template <typename T>
-struct Vec4T;
-template <>
-struct Vec4T<double> {
-    typedef double V __attribute__((ext_vector_type(4)));
-};
-template <>
-struct Vec4T<float> {
-    typedef float V __attribute__((ext_vector_type(4)));
-};
-
-// K (the contraction length) is a multiple of 4: the full 16-wide chunks
-// as above, then the remaining 4, 8 or 12 values with step s taking
-// k = K16 + 4 s + lk (any assignment of k to (step, lane group) that both
-// operands share gives the same sum), so that no MFMA step multiplies only
-// zero padding.  Up to two chunks (K <= 44) all G values are loaded before
-// the first product, the same products in the same order (at 32^3 this
-// saves the waits of the second chunk and the tail: P_0 21.2 -> 21.0 us,
-// 2-4 % per MINRES iteration).
-template <typename T, bool GA>
-__device__ __forceinline__ typename Mfma<T>::V tile_gemm(const T* G, int ldg, const T* H, int h_k,
-                                                         int h_i, int K, int lr, int lk) {
-    using M = Mfma<T>;
-    using V4 = typename Vec4T<T>::V;
-    const int K16 = K & ~15;
-    const T* gp = G + lr * ldg + 4 * lk;
-    const T* hp = H + lr * h_i + 4 * lk * h_k;
-    typename M::V acc = {0, 0, 0, 0};
-    if (K16 <= 32) {
-        V4 g0 = *reinterpret_cast<const V4*>(gp), g1 = g0;
-        if (K16 > 16) g1 = *reinterpret_cast<const V4*>(gp + 16);
-        const T* gt = G + lr * ldg + K16 + lk;
-        T tv[3];
-#pragma unroll
-        for (int s = 0; s < 3; ++s) tv[s] = (K16 + 4 * s < K) ? gt[4 * s] : T(0);
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            if (16 * c >= K16) break;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const T h = hp[(16 * c + s) * h_k];
-                const T gv = c ? g1[s] : g0[s];
-                acc = GA ? M::mma(gv, h, acc) : M::mma(h, gv, acc);
-            }
-        }
-        const T* ht = H + lr * h_i + (K16 + lk) * h_k;
-#pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            if (K16 + 4 * s >= K) break;
-            const T h = ht[4 * s * h_k];
-            acc = GA ? M::mma(tv[s], h, acc) : M::mma(h, tv[s], acc);
-        }
-        return acc;
-    }
-    V4 g[2];
-    g[0] = *reinterpret_cast<const V4*>(gp);
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        if (16 * c >= K16) break;
-        if (16 * (c + 1) < K16) g[(c + 1) & 1] = *reinterpret_cast<const V4*>(gp + 16 * (c + 1));
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const T h = hp[(16 * c + s) * h_k];
-            const T gv = g[c & 1][s];
-            acc = GA ? M::mma(gv, h, acc) : M::mma(h, gv, acc);
-        }
-    }
-    const T* gt = G + lr * ldg + K16 + lk;
-    const T* ht = H + lr * h_i + (K16 + lk) * h_k;
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        if (K16 + 4 * s >= K) break;
-        const T h = ht[4 * s * h_k];
-        const T gv = gt[4 * s];
-        acc = GA ? M::mma(gv, h, acc) : M::mma(h, gv, acc);
-    }
-    return acc;
-}
-
-// A 2x2 block of tile products: row tiles G0, G1 (G1 used when g1) and column
-// tiles H0, H1 (when h1), each operand fragment loaded once for two MFMAs.
-template <typename T, bool GA>
-__device__ __forceinline__ void tile_gemm_2x2(const T* G0, const T* G1, int ldg, const T* H0,
-                                              const T* H1, int h_k, int h_i, int K, int lr, int lk,
-                                              bool g1, bool h1,
-                                              typename Mfma<T>::V (&acc)[2][2]) {
-    using M = Mfma<T>;
-    using V4 = typename Vec4T<T>::V;
-    const T* gp0 = G0 + lr * ldg + 4 * lk;
-    const T* gp1 = G1 + lr * ldg + 4 * lk;
-    const T* hp0 = H0 + lr * h_i + 4 * lk * h_k;
-    const T* hp1 = H1 + lr * h_i + 4 * lk * h_k;
-    V4 ga[2], gb[2];
-    ga[0] = *reinterpret_cast<const V4*>(gp0);
-    gb[0] = g1 ? *reinterpret_cast<const V4*>(gp1) : ga[0];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = typename M::V{0, 0, 0, 0};
-    const int K16 = K & ~15;  // K: a multiple of 4, the tail as in tile_gemm
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        if (16 * c >= K16) break;
-        if (16 * (c + 1) < K16) {
-            ga[(c + 1) & 1] = *reinterpret_cast<const V4*>(gp0 + 16 * (c + 1));
-            gb[(c + 1) & 1] = g1 ? *reinterpret_cast<const V4*>(gp1 + 16 * (c + 1)) : ga[(c + 1) & 1];
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const T x0 = hp0[(16 * c + s) * h_k];
-            const T x1 = h1 ? hp1[(16 * c + s) * h_k] : x0;
-            const T a0 = ga[c & 1][s], a1 = gb[c & 1][s];
-            acc[0][0] = GA ? M::mma(a0, x0, acc[0][0]) : M::mma(x0, a0, acc[0][0]);
-            acc[0][1] = GA ? M::mma(a0, x1, acc[0][1]) : M::mma(x1, a0, acc[0][1]);
-            acc[1][0] = GA ? M::mma(a1, x0, acc[1][0]) : M::mma(x0, a1, acc[1][0]);
-            acc[1][1] = GA ? M::mma(a1, x1, acc[1][1]) : M::mma(x1, a1, acc[1][1]);
-        }
-    }
-    const T* gt0 = G0 + lr * ldg + K16 + lk;
-    const T* gt1 = G1 + lr * ldg + K16 + lk;
-    const T* ht0 = H0 + lr * h_i + (K16 + lk) * h_k;
-    const T* ht1 = H1 + lr * h_i + (K16 + lk) * h_k;
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        if (K16 + 4 * s >= K) break;
-        const T x0 = ht0[4 * s * h_k];
-        const T x1 = h1 ? ht1[4 * s * h_k] : x0;
-        const T a0 = gt0[4 * s];
-        const T a1 = g1 ? gt1[4 * s] : a0;
-        acc[0][0] = GA ? M::mma(a0, x0, acc[0][0]) : M::mma(x0, a0, acc[0][0]);
-        acc[0][1] = GA ? M::mma(a0, x1, acc[0][1]) : M::mma(x1, a0, acc[0][1]);
-        acc[1][0] = GA ? M::mma(a1, x0, acc[1][0]) : M::mma(x0, a1, acc[1][0]);
-        acc[1][1] = GA ? M::mma(a1, x1, acc[1][1]) : M::mma(x1, a1, acc[1][1]);
-    }
-}
-
-// Split-BF16 ("bf16x3") product for FP32 data: each operand is written as
-// hi + lo with hi = bf16(x), lo = bf16(x - hi) (round to nearest even), and
-// A B ~= A_hi B_hi + A_hi B_lo + A_lo B_hi, three 16x16x16 BF16 MFMAs per
-// 16-wide k step accumulated in FP32.  hi + lo keeps 16 significant bits of
-// each operand (relative error up to 2^-17), so a product is good to about
-// 1e-5 relative, not to FP32 rounding; the dropped lo*lo term is of the
-// same order.  A lane supplies the four values
-// k = 16c + 4 lk + j, j < 4, of both operands (the instruction only needs
-// the same k for both); result rows are 4 (l/16) + i as for FP32.  Operand
-// roles and layouts as in tile_gemm.
-typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
-
-template <bool GA>
-__device__ __forceinline__ f4 tile_gemm_bf16x3(const float* G, int ldg, const float* H, int h_k,
-                                               int h_i, int K, int lr, int lk) {
-    const float* gp = G + lr * ldg + 4 * lk;
-    const float* hp = H + lr * h_i + 4 * lk * h_k;
-    f4 g[2];
-    g[0] = *reinterpret_cast<const f4*>(gp);
-    f4 acc = {0, 0, 0, 0};
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        if (16 * c >= K) break;
-        if (16 * (c + 1) < K) g[(c + 1) & 1] = *reinterpret_cast<const f4*>(gp + 16 * (c + 1));
-        bf4 ghi, glo, hhi, hlo;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float gv = g[c & 1][j];
-            const float hv = hp[(16 * c + j) * h_k];
-            const __bf16 gh = (__bf16)gv, hh = (__bf16)hv;
-            ghi[j] = gh;
-            hhi[j] = hh;
-            glo[j] = (__bf16)(gv - (float)gh);
-            hlo[j] = (__bf16)(hv - (float)hh);
-        }
-        if (GA) {
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ghi, hhi, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ghi, hlo, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(glo, hhi, acc, 0, 0, 0);
-        } else {
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(hhi, ghi, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(hhi, glo, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(hlo, ghi, acc, 0, 0, 0);
-        }
-    }
-    return acc;
-}
-
-// dispatch of a 16x16 tile product: native MFMA of T, or split BF16 (T = float)
-template <typename T, bool SPLIT, bool GA>
-__device__ __forceinline__ typename Mfma<T>::V tile_mm(const T* G, int ldg, const T* H, int h_k,
-                                                       int h_i, int n, int lr, int lk) {
-    // n: the contraction's true length; the operands are zero from n to the
-    // next multiple of 16
-    if constexpr (SPLIT) {
-        return tile_gemm_bf16x3<GA>(G, ldg, H, h_k, h_i, (n + 15) & ~15, lr, lk);
-    } else {
-        return tile_gemm<T, GA>(G, ldg, H, h_k, h_i, (n + 3) & ~3, lr, lk);
-    }
-}
-
-// One i3-plane per workgroup, one buffer: the plane is transformed in place.
-// Each wave computes its (at most XY_MT) output tiles into registers, the
-// workgroup synchronises, and only then are the tiles written back, so the
-// two steps need a single plane of LDS (which leaves room to stage the two
-// dense 1D matrices, or lets FP64 planes up to 128 x 128 use 16 waves).
-constexpr int XY_MT = 4;        // tiles per wave: 8 x 8 tiles over 16 waves
-
-template <typename T, typename TI, typename TO, bool STAGE, bool SPLIT = false, bool BLK = false>
-__global__ __launch_bounds__(FD_WIDE) void k_fd_xy_w(XYArgs a, FDTables<T> t) {
-    using M = Mfma<T>;
-    using V = typename M::V;
-    extern __shared__ unsigned char smem_raw[];
-    T* S = reinterpret_cast<T*>(smem_raw);
-    const int nf = a.fields_hi - a.fields_lo;
-    const int f = a.fields_lo + (int)(blockIdx.y % nf);
-    const int r = (int)(blockIdx.y / nf);
-    const int k = blockIdx.x;
-    const int n1 = a.dims[f][0], n2 = a.dims[f][1], n3 = a.dims[f][2];
-    if (k >= n3) return;
-    const int N1 = (n1 + 15) & ~15, N2 = (n2 + 15) & ~15;
-    const int ld = N1 + 1;  // column-major plane
-    const int nb1 = N1 >> 4, nb2 = N2 >> 4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nw = FD_WIDE / 64;
-    const int lr = lane & 15, lk = lane >> 4;
-    const long long kofs = (long long)k * n1 * n2;
-    const TI* x = reinterpret_cast<const TI*>(a.in[f]) + (long long)r * a.sin[f] + kofs;
-    xy_stage<T, TI, FD_WIDE>(a, f, x, r, kofs, S, ld, n1, n2, N1, N2);
-    // L (rows contiguous) for step 1 and R^T (rows of R^T = columns of R) for step 2
-    const T* L = xy_left(t, f, a.inverse);
-    const T* Rt = xy_right_t(t, f, a.inverse);
-    const int ldL = (f == 0) ? t.NNp : t.NMp;
-    const int ldR = (f == 1) ? t.NNp : t.NMp;
-    if (STAGE) {
-        T* Ls = S + N2 * ld;
-        T* Rs = Ls + N1 * N1;
-        for (int idx = threadIdx.x; idx < N1 * N1; idx += FD_WIDE) Ls[idx] = L[idx];
-        for (int idx = threadIdx.x; idx < N2 * N2; idx += FD_WIDE) Rs[idx] = Rt[idx];
-        L = Ls;
-        Rt = Rs;
-    }
-    __syncthreads();
-    if constexpr (!SPLIT && BLK) {
-        {
-            // 2x2 blocks of tiles per wave: each operand fragment feeds two MFMAs
-            const int nbb1 = (nb1 + 1) >> 1, nbb2 = (nb2 + 1) >> 1;
-            const int nblk = nbb1 * nbb2;
-            V bacc[2][2];
-            const bool mine = wave < nblk;  // 16 waves cover up to 4 x 4 blocks
-            const int RB = mine ? wave % nbb1 : 0, CB = mine ? wave / nbb1 : 0;
-            const bool g1 = 2 * RB + 1 < nb1, h1 = 2 * CB + 1 < nb2;
-            if (mine)
-                tile_gemm_2x2<T, true>(L + 2 * RB * 16 * ldL, L + (2 * RB + 1) * 16 * ldL, ldL,
-                                       S + 2 * CB * 16 * ld, S + (2 * CB + 1) * 16 * ld, 1, ld,
-                                       (n1 + 3) & ~3, lr, lk, g1, h1, bacc);
-            __syncthreads();
-            if (mine)
-#pragma unroll
-                for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-                    for (int jj = 0; jj < 2; ++jj) {
-                        if ((ii && !g1) || (jj && !h1)) continue;
-                        const int rb = 2 * RB + ii, cb = 2 * CB + jj;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            S[(cb * 16 + lr) * ld + rb * 16 + M::row(lk, i)] = bacc[ii][jj][i];
-                    }
-            __syncthreads();
-            // step 2: Y = T R; block (RB2, CB2): G from R^T rows cb, H from T rows rb
-            const int nbr = (nb1 + 1) >> 1, nbc = (nb2 + 1) >> 1;
-            const bool mine2 = wave < nbr * nbc;
-            const int RB2 = mine2 ? wave % nbr : 0, CB2 = mine2 ? wave / nbr : 0;
-            const bool gc1 = 2 * CB2 + 1 < nb2, hr1 = 2 * RB2 + 1 < nb1;
-            if (mine2)
-                tile_gemm_2x2<T, false>(Rt + 2 * CB2 * 16 * ldR, Rt + (2 * CB2 + 1) * 16 * ldR, ldR,
-                                        S + 2 * RB2 * 16, S + (2 * RB2 + 1) * 16, ld, 1,
-                                        (n2 + 3) & ~3, lr, lk, gc1, hr1, bacc);
-            __syncthreads();
-            if (mine2)
-#pragma unroll
-                for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-                    for (int jj = 0; jj < 2; ++jj) {
-                        if ((ii && !gc1) || (jj && !hr1)) continue;
-                        const int cb = 2 * CB2 + ii, rb = 2 * RB2 + jj;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            S[(cb * 16 + lr) * ld + rb * 16 + M::row(lk, i)] = bacc[ii][jj][i];
-                    }
-            __syncthreads();
-            xy_store<T, TO, FD_WIDE>(a, S, ld, f, r, k, n1, n2);
-            return;
-        }
-    }
-    const int ntile = nb1 * nb2;
-    V acc[XY_MT];
-    // step 1: T = L X  (tile (rb, cb): rows of L, columns of X)
-#pragma unroll
-    for (int m = 0; m < XY_MT; ++m) {
-        const int tt = wave + m * nw;
-        if (tt < ntile) {
-            const int rb = tt % nb1, cb = tt / nb1;
-            acc[m] = tile_mm<T, SPLIT, true>(L + rb * 16 * ldL, ldL, S + cb * 16 * ld, 1, ld, n1,
-                                             lr, lk);
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < XY_MT; ++m) {
-        const int tt = wave + m * nw;
-        if (tt < ntile) {
-            const int rb = tt % nb1, cb = tt / nb1;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) S[(cb * 16 + lr) * ld + rb * 16 + M::row(lk, i)] = acc[m][i];
-        }
-    }
-    __syncthreads();
-    // step 2: Y = T R
-#pragma unroll
-    for (int m = 0; m < XY_MT; ++m) {
-        const int tt = wave + m * nw;
-        if (tt < ntile) {
-            const int rb = tt % nb1, cb = tt / nb1;
-            acc[m] = tile_mm<T, SPLIT, false>(Rt + cb * 16 * ldR, ldR, S + rb * 16, ld, 1, n2, lr,
-                                              lk);
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < XY_MT; ++m) {
-        const int tt = wave + m * nw;
-        if (tt < ntile) {
-            const int rb = tt % nb1, cb = tt / nb1;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) S[(cb * 16 + lr) * ld + rb * 16 + M::row(lk, i)] = acc[m][i];
-        }
-    }
-    __syncthreads();
-    xy_store<T, TO, FD_WIDE>(a, S, ld, f, r, k, n1, n2);
-}
-
-// One 16-row block of one i3-plane per 4-wave workgroup, for meshes whose
-// planes alone leave most compute units idle: the nb1 row blocks of a plane
-// run as nb1 workgroups.  Step 1's row block T_b = L_b X needs the whole
-// plane X, which every workgroup of the plane stages; T_b stays in LDS
-// (column-major, pitch 17) and Y_b = T_b R follows.  The dense 1D matrices
-// are read from L2.  Per output tile the contraction is tile_mm's, with the
-// operands of the wide kernel, so the result equals it bit for bit.
-// Grid order: workgroup g runs on XCD g mod 8 (round-robin dispatch), and the
-// row blocks of plane k take consecutive slots of XCD k mod 8, so that the
-// workgroups staging one plane share that XCD's L2.
-constexpr int FD_SPLIT = 256;   // 4 waves
-constexpr int TBP = 17;         // pitch of the row block T_b in LDS
-
-template <typename T, typename TI, typename TO, bool SPLIT = false>
-__global__ __launch_bounds__(FD_SPLIT) void k_fd_xy_s(XYArgs a, FDTables<T> t) {
-    using M = Mfma<T>;
-    extern __shared__ unsigned char smem_raw[];
-    T* S = reinterpret_cast<T*>(smem_raw);
-    const int nf = a.fields_hi - a.fields_lo;
-    const int f = a.fields_lo + (int)(blockIdx.y % nf);
-    const int r = (int)(blockIdx.y / nf);
-    const int xcd = (int)(blockIdx.x & 7), slot = (int)(blockIdx.x >> 3);
-    const int k = (slot / a.nrb) * 8 + xcd, rb = slot % a.nrb;
-    const int n1 = a.dims[f][0], n2 = a.dims[f][1], n3 = a.dims[f][2];
-    const int N1 = (n1 + 15) & ~15, N2 = (n2 + 15) & ~15;
-    if (k >= n3 || 16 * rb >= N1) return;
-    const int ld = N1 + 1;  // column-major plane
-    const int nb2 = N2 >> 4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int lr = lane & 15, lk = lane >> 4;
-    const long long kofs = (long long)k * n1 * n2;
-    const TI* x = reinterpret_cast<const TI*>(a.in[f]) + (long long)r * a.sin[f] + kofs;
-    xy_stage<T, TI, FD_SPLIT>(a, f, x, r, kofs, S, ld, n1, n2, N1, N2);
-    T* Tb = S + N2 * ld;  // Tb[col * TBP + i]: row 16 rb + i of T (and later of Y)
-    const T* L = xy_left(t, f, a.inverse);
-    const T* Rt = xy_right_t(t, f, a.inverse);
-    const int ldL = (f == 0) ? t.NNp : t.NMp;
-    const int ldR = (f == 1) ? t.NNp : t.NMp;
-    __syncthreads();
-    typename M::V acc[2];
-    // step 1: T_b = L_b X, tiles (rb, cb), cb = wave, wave + 4 (nb2 <= 8)
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const int cb = wave + 4 * m;
-        if (cb < nb2)
-            acc[m] = tile_mm<T, SPLIT, true>(L + rb * 16 * ldL, ldL, S + cb * 16 * ld, 1, ld, n1,
-                                             lr, lk);
-    }
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const int cb = wave + 4 * m;
-        if (cb < nb2)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) Tb[(cb * 16 + lr) * TBP + M::row(lk, i)] = acc[m][i];
-    }
-    __syncthreads();
-    // step 2: Y_b = T_b R, tiles (rb, cb)
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const int cb = wave + 4 * m;
-        if (cb < nb2)
-            acc[m] = tile_mm<T, SPLIT, false>(Rt + cb * 16 * ldR, ldR, Tb, TBP, 1, n2, lr, lk);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const int cb = wave + 4 * m;
-        if (cb < nb2)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) Tb[(cb * 16 + lr) * TBP + M::row(lk, i)] = acc[m][i];
-    }
-    __syncthreads();
-    // write-out of rows [16 rb, min(n1, 16 rb + 16)), as xy_store for one row block
-    const int rows = min(16, n1 - 16 * rb), n = 16 * n2;
-    TO* y = reinterpret_cast<TO*>(a.out[f]) + (long long)r * a.sout[f] + kofs + 16 * rb;
-    if constexpr (std::is_same<TO, double>::value) {
-        if (a.dpart) {
-            const double* w = a.dw[f] + (long long)r * a.sout[f] + kofs + 16 * rb;
-            double s = 0.0;
-            for (int base = 0; base < n; base += FD_BATCH * FD_SPLIT) {
-                double yv[FD_BATCH], wv[FD_BATCH];
-#pragma unroll
-                for (int u = 0; u < FD_BATCH; ++u) {
-                    const int idx = base + u * FD_SPLIT + (int)threadIdx.x;
-                    const int col = idx >> 4, i = idx & 15;
-                    const long long o = idx < n && i < rows ? i + (long long)col * n1 : 0;
-                    yv[u] = a.accumulate ? y[o] : 0.0;
-                    wv[u] = w[o];
-                }
-#pragma unroll
-                for (int u = 0; u < FD_BATCH; ++u) {
-                    const int idx = base + u * FD_SPLIT + (int)threadIdx.x;
-                    const int col = idx >> 4, i = idx & 15;
-                    if (idx < n && i < rows) {
-                        double v = (double)Tb[col * TBP + i];
-                        if (a.accumulate) v += yv[u];
-                        y[i + (long long)col * n1] = v;
-                        s += v * wv[u];
-                    }
-                }
-            }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-            __syncthreads();
-            double* red = reinterpret_cast<double*>(S);
-            if (lane == 0) red[wave] = s;
-            __syncthreads();
-            if (threadIdx.x == 0)
-                a.dpart[(long long)r * a.dp_stride + (long long)f * a.dp_planes + k +
-                        rb * a.dp_rb] = red[0] + red[1] + red[2] + red[3];
-            return;
-        }
-    }
-    if (a.accumulate) {
-        for (int base = 0; base < n; base += FD_BATCH * FD_SPLIT) {
-            TO yv[FD_BATCH];
-#pragma unroll
-            for (int u = 0; u < FD_BATCH; ++u) {
-                const int idx = base + u * FD_SPLIT + (int)threadIdx.x;
-                const int col = idx >> 4, i = idx & 15;
-                yv[u] = y[idx < n && i < rows ? i + (long long)col * n1 : 0];
-            }
-#pragma unroll
-            for (int u = 0; u < FD_BATCH; ++u) {
-                const int idx = base + u * FD_SPLIT + (int)threadIdx.x;
-                const int col = idx >> 4, i = idx & 15;
-                if (idx < n && i < rows) y[i + (long long)col * n1] = yv[u] + (TO)Tb[col * TBP + i];
-            }
-        }
-        return;
-    }
-    for (int idx = threadIdx.x; idx < n; idx += FD_SPLIT) {
-        const int col = idx >> 4, i = idx & 15;
-        if (i >= rows) continue;
-        y[i + (long long)col * n1] = (TO)Tb[col * TBP + i];
-    }
-}
-
-// z: ZR (i1,i2)-rows x n3 per workgroup of NTH threads (64 rows and 16
-// waves, or 16 rows and 4 waves for small meshes), tiles of Y = X U3 and
-// Z = Y U3^T dealt to the waves; the scaling by 1/(2 nu (l1 + l2 + l3)) is
-// applied to Y.
-template <typename T, typename TI, typename TO, bool STAGE, bool SPLIT = false, int ZR = ZROWS,
-          int NTH = FD_WIDE>
-__global__ __launch_bounds__(NTH) void k_fd_z_w(ZArgs a, FDTables<T> t) {
-    using M = Mfma<T>;
-    extern __shared__ unsigned char smem_raw[];
-    T* S = reinterpret_cast<T*>(smem_raw);
-    const int nf = a.fields_hi - a.fields_lo;
-    const int f = a.fields_lo + (int)(blockIdx.y % nf);
-    const int r = (int)(blockIdx.y / nf);
-    const int n1 = a.dims[f][0], n2 = a.dims[f][1], n3 = a.dims[f][2];
-    const long long plane = (long long)n1 * n2;
-    const long long r0 = (long long)blockIdx.x * ZR;
-    if (r0 >= plane) return;
-    const int N3 = (n3 + 15) & ~15;
-    const int ld = N3 + 1;  // row-major [row][k]
-    const int nb3 = N3 >> 4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nw = NTH / 64;
-    const int lr = lane & 15, lk = lane >> 4;
-    T* Y = S + ZR * ld;
-    const TI* x = reinterpret_cast<const TI*>(a.in[f]) + (long long)r * a.sin[f];
-    z_stage<T, TI, NTH, ZR>(x, r0, plane, n3, N3, S, ld);
-    const bool pres = (f == 3);
-    const T* U3 = pres ? t.Mi : (f == 2 ? t.UK : t.UT);
-    const T* U3t = pres ? t.Mi : (f == 2 ? t.UKt : t.UTt);
-    const int ldU = (f == 2) ? t.NNp : t.NMp;
-    if (STAGE) {
-        T* Us = Y + ZR * ld;
-        T* Uts = Us + N3 * N3;
-        for (int idx = threadIdx.x; idx < N3 * N3; idx += NTH) {
-            Us[idx] = U3[idx];
-            if (!pres) Uts[idx] = U3t[idx];
-        }
-        U3 = Us;
-        U3t = pres ? Us : Uts;  // M^^{-1} is symmetric: one staged copy serves both
-    }
-    __syncthreads();
-    const int ntile = (ZR / 16) * nb3;
-    const double* l1 = (f == 0) ? t.lamK : t.lamT;
-    const double* l2 = (f == 1) ? t.lamK : t.lamT;
-    const double* l3 = (f == 2) ? t.lamK : t.lamT;
-    for (int tt = wave; tt < ntile; tt += nw) {
-        const int rb = tt % (ZR / 16), cb = tt / (ZR / 16);
-        auto acc = tile_mm<T, SPLIT, false>(U3t + cb * 16 * ldU, ldU, S + rb * 16 * ld, 1, ld, n3, lr, lk);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = rb * 16 + M::row(lk, i);
-            const int col = cb * 16 + lr;
-            double sc;
-            if (pres) {
-                sc = a.omega * a.two_nu;
-            } else {
-                sc = 0.0;
-                const long long rr = r0 + row;
-                if (rr < plane && col < n3) {
-                    const int i1 = (int)(rr % n1), i2 = (int)(rr / n1);
-                    sc = a.omega / (a.two_nu * (l1[i1] + l2[i2] + l3[col]));
-                }
-            }
-            Y[row * ld + col] = (T)(sc * (double)acc[i]);
-        }
-    }
-    __syncthreads();
-    T* Out = Y;
-    if (!pres) {
-        for (int tt = wave; tt < ntile; tt += nw) {
-            const int rb = tt % (ZR / 16), cb = tt / (ZR / 16);
-            auto acc = tile_mm<T, SPLIT, false>(U3 + cb * 16 * ldU, ldU, Y + rb * 16 * ld, 1, ld, n3, lr, lk);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) S[(rb * 16 + M::row(lk, i)) * ld + cb * 16 + lr] = acc[i];
         }
         __syncthreads();
-        Out = S;
-    }
-    z_store<T, TO, NTH, ZR>(a, Out, S, ld, f, r, r0, plane, n3);
-}
-
-// LDS plan for a direction of padded size np: wide (two buffers) or in place,
-// and whether the dense 1D matrices are staged in LDS as well.
-struct FDPlan {
-    bool wide, stage_xy, stage_z, block;
-    bool split;  // row-block xy kernel and 16-row z kernel (FD_PLAN_SPLIT)
-    size_t shm_xy, shm_z;
-};
-
-// The plan of plan code `code` (bit 0: wide kernels, bit 1: stage the 1D
-// matrices in LDS when they fit, bit 2: 2x2 blocks of MFMA tiles per wave in
-// the wide xy kernel); code < 0 gives the default plan: wide when two planes
-// fit in LDS, staging when it leaves room for a second workgroup.
-template <typename T>
-FDPlan fd_plan(int np, int code) {
-    // wide kernels: the xy kernel transforms one plane in place (one plane of
-    // LDS), the z kernel keeps its input and intermediate rows (two buffers)
-    const size_t lim = 160 * 1024, e = sizeof(T);
-    FDPlan pl{};
-    if (code == FD_PLAN_SPLIT) {
-        pl.wide = true;
-        pl.split = true;
-        pl.shm_xy = (size_t)np * (np + 1 + TBP) * e;
-        pl.shm_z = (size_t)2 * 16 * (np + 1) * e;
-        return pl;
-    }
-    const size_t plane = (size_t)np * (np + 1) * e, mats = (size_t)2 * np * np * e;
-    const size_t zbuf = (size_t)ZROWS * (np + 1) * e;
-    const bool wide_fits = plane <= lim && 2 * zbuf <= lim;
-    if (code < 0) {
-        pl.wide = wide_fits;
-        if (pl.wide) {
-            pl.stage_xy = plane + mats <= 140 * 1024;
-            pl.stage_z = 2 * zbuf + mats <= 140 * 1024;
-        } else {
-            pl.stage_xy = plane + mats <= 96 * 1024;
-            pl.stage_z = zbuf + mats <= 96 * 1024;
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int u = tile_u(q);
+            if (u >= nt) break;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        X[h][(16 * u + M::kmap(lk, i)) * P + 16 * c + lr] = acc[q][h][c][i];
         }
-    } else {
-        pl.wide = (code & 1) != 0;
-        pl.stage_xy = (code & 2) && plane + mats <= lim;
-        pl.stage_z = (code & 2) && (pl.wide ? 2 : 1) * zbuf + mats <= lim;
-        pl.block = (code & 4) && pl.wide;
+        __syncthreads();
+        product(tab2);
     }
-    pl.shm_xy = plane + (pl.stage_xy ? mats : 0);
-    pl.shm_z = (pl.wide ? 2 : 1) * zbuf + (pl.stage_z ? mats : 0);
-    return pl;
+    TO* y = reinterpret_cast<TO*>(a.out[f]) + (long long)r * a.sout[f] + ofs;
+    const bool add = (a.accumulate >> f) & 1;
+    const bool dot = std::is_same<TO, double>::value && a.dpart != nullptr;
+    const double* dw = dot ? a.dw + (long long)r * a.sout[f] + ofs : nullptr;
+    const double ps = pres ? a.pscale : 1.0;
+    double sum = 0.0;
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        const int u = tile_u(q);
+        if (u >= nt) break;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const unsigned col = 16 * c + lr;
+            const bool in = c0 + col < ncol;
+            // rows 16 u + kmap(lk, i) (and their mirror images), from the
+            // row of lk = 0 (of the last lk)
+            constexpr int S = M::kmap(1, 0), E3 = 3 * S;
+            const uint32_t o0 = (uint32_t)sizeof(TO) * (lk * S * ncol + col);
+            const uint32_t o1 = (uint32_t)sizeof(TO) * ((E3 - lk * S) * ncol + col);
+            TO yv[4][2];
+            double wv[4][2];
+            uint32_t o[4][2];
+            long long ro[4][2];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int m0 = 16 * u + M::kmap(0, i), m = m0 + lk * S;
+                ro[i][0] = (long long)m0 * ncol;
+                ro[i][1] = (long long)(unfold ? n - 1 - m0 - E3 : he + m0) * ncol;
+                o[i][0] = in && m < he ? o0 : OOB;
+                o[i][1] = in && m < ho ? (unfold ? o1 : o0) : OOB;
+                if (add)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) yv[i][h] = bload(y + ro[i][h], o[i][h]);
+                if (dot)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) wv[i][h] = bload(dw + ro[i][h], o[i][h]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const T E = acc[q][0][c][i], O = acc[q][1][c][i];
+                T z[2] = {E, O};
+                if (unfold) {
+                    z[0] = o[i][1] != OOB ? E + O : E;
+                    z[1] = E - O;
+                }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    TO s = pres ? (TO)(ps * (double)z[h]) : (TO)z[h];
+                    if (add) s += yv[i][h];
+                    bstore(y + ro[i][h], o[i][h], s);
+                    if (dot) sum += o[i][h] != OOB ? (double)s * wv[i][h] : 0.0;
+                }
+            }
+        }
+    }
+    if (dot) {
+        __syncthreads();
+        const double s = wg_sum(sum, reinterpret_cast<double*>(smem_raw));
+        if (threadIdx.x == 0) a.dpart[(long long)r * a.dp_stride + w.c] = s;
+    }
 }
+
+// Direction 1 of 16 CT lines.  The lines are contiguous: rows of the products
+// are lines (the A operand, [line][even | odd] in LDS with an odd pitch),
+// columns the outputs (the table is the B operand), so that a store covers 16
+// consecutive entries of four lines.
+template <typename T, typename TI, typename TO, int CT, int NW>
+__global__ __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(4))) void k_fd_row(LineArgs a, FDTables<T> t) {
+    using M = Mfma<T>;
+    using V = typename M::V;
+    constexpr int W = 16 * CT;
+    constexpr int U = NW == 4 ? 1 : (NW == 8 ? 2 : 3);
+    // pairs (k, n-1-k) a thread has in flight: the whole tile to 320 per direction
+    constexpr int NG = NW == 4 ? 4 * CT : (NW == 8 ? 10 : 4);
+    extern __shared__ unsigned char smem_raw[];
+    T* S = reinterpret_cast<T*>(smem_raw);
+    const int nt = t.nt, K16 = 16 * nt, P = 2 * K16 + 1, nth = blockDim.x;
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lr = lane & 15, lk = lane >> 4;
+    const int turn = (wave + (int)blockIdx.x) % nw;
+    auto tile_u = [&](int q) { return q == 0 ? wave : q * nw + turn; };
+    const Tile w = tile_of(a, xcd_tile(blockIdx.x, a.ntiles));
+    const int f = w.f;
+    const long long left = (long long)a.dims[f][1] * a.dims[f][2] - (long long)w.c * W;
+    if (left <= 0) return;
+    const int nl = (int)min((long long)W, left);
+    const bool fold = !a.inverse, unfold = a.inverse || f == 3;
+    const Dir<T> d = dir_of(t, f, 0, a.inverse);
+    const int n = d.n, he = d.he, ho = d.ho;
+    HalfProduct<T, false, false, CT, NW == 8> hp;
+    hp.u = min(wave, nt - 1);
+    hp.nt = nt;
+    hp.he = he;
+    hp.ho = ho;
+    hp.lane = lane;
+    hp.prime(d.tab);
+    {
+        // entries k and n-1-k (or he + k) of line l; a thread's (l, k) advance
+        // by nth entries of the 16 CT x K16 tile
+        const TI* x = reinterpret_cast<const TI*>(a.in[f]) + (long long)w.r * a.sin[f] +
+                      (long long)w.c * W * n;
+        const int dl = nth / K16, dk = nth - dl * K16;
+        int l0 = threadIdx.x / K16, k0 = threadIdx.x - l0 * K16;
+#pragma unroll 1
+        for (int base = 0; base < W * K16; base += NG * nth) {
+            TI v[NG][2];
+            int l = l0, k = k0;
+            auto next = [&]() {
+                l += dl;
+                k += dk;
+                if (k >= K16) {
+                    k -= K16;
+                    ++l;
+                }
+            };
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const uint32_t lo = (uint32_t)sizeof(TI) * l * n;
+                const int k2 = fold ? n - 1 - k : he + k;
+                const bool in = l < nl;
+                v[g][0] = bload(x, in && k < he ? lo + (uint32_t)sizeof(TI) * k : OOB);
+                v[g][1] = bload(x, in && k < (fold ? he : ho) ? lo + (uint32_t)sizeof(TI) * k2 : OOB);
+                next();
+            }
+            l = l0;
+            k = k0;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if (l < W) {
+                    TI e = v[g][0], o = v[g][1];
+                    if (fold) {
+                        o = v[g][0] - v[g][1];
+                        e = k < ho ? v[g][0] + v[g][1] : v[g][0];
+                    }
+                    S[l * P + k] = (T)e;
+                    S[l * P + K16 + k] = k < ho ? (T)o : T(0);
+                }
+                next();
+            }
+            l0 = l;
+            k0 = k;
+        }
+    }
+    __syncthreads();
+    TO* y = reinterpret_cast<TO*>(a.out[f]) + (long long)w.r * a.sout[f] +
+            (long long)w.c * W * n;
+    const bool add = (a.accumulate >> f) & 1;
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        const int u = tile_u(q);
+        if (u >= nt) break;
+        if (q > 0) {
+            hp.u = u;
+            hp.prime(d.tab);
+        }
+        const int m = 16 * u + lr;
+        const bool one = m < he, two = m < ho;
+        const int m2 = unfold ? n - 1 - m : he + m;
+        // line 16 c + kmap(lk, i), from the line of lk = 0
+        constexpr int ST = M::kmap(1, 0);
+        const uint32_t o0 = (uint32_t)sizeof(TO) * (lk * ST * n + m);
+        const uint32_t o1 = (uint32_t)sizeof(TO) * (lk * ST * n + m2);
+        auto offset = [&](int c, int i, int h) -> uint32_t {
+            if (!(h ? two : one) || 16 * c + M::kmap(lk, i) >= nl) return OOB;
+            return h ? o1 : o0;
+        };
+        auto line0 = [&](int c, int i) { return y + (16 * c + M::kmap(0, i)) * n; };
+        V acc[2][CT];
+        hp.run(acc, [&](int h, int c, int k, int i) {
+            return S[(16 * c + lr) * P + h * K16 + k + M::kmap(lk, i)];
+        });
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            TO yv[4][2];
+            if (add)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) yv[i][h] = bload(line0(c, i), offset(c, i, h));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const T E = acc[0][c][i], O = acc[1][c][i];
+                T z[2] = {E, O};
+                if (unfold) {
+                    z[0] = two ? E + O : E;
+                    z[1] = E - O;
+                }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    TO s = (TO)z[h];
+                    if (add) s += yv[i][h];
+                    bstore(line0(c, i), offset(c, i, h), s);
+                }
+            }
+        }
+    }
+}
+
+// Partial sums of y . w for the Krylov dot of launch_P0 where the last launch
+// is a direction-1 pass: one per (field, i3-plane) at f nM + k, as the plane
+// kernel writes them.  Fixed-order block sums.
+struct DotArgs {
+    const double* y[3];
+    const double* w[3];
+    long long stride[3];  // per rhs, of y and w
+    long long plane[3];
+    int planes[3];
+    double* part;
+    long long dp_stride;
+    int nM;
+};
+__global__ __launch_bounds__(256) void k_fd_dot_vel(DotArgs a) {
+    __shared__ double red[4];
+    const int k = blockIdx.x, f = blockIdx.y, r = blockIdx.z;
+    if (k >= a.planes[f]) return;
+    const long long plane = a.plane[f], ofs = (long long)r * a.stride[f] + k * plane;
+    const double* y = a.y[f] + ofs;
+    const double* w = a.w[f] + ofs;
+    double s = 0.0;
+    for (long long i = threadIdx.x; i < plane; i += 256) s += y[i] * w[i];
+    s = wg_sum(s, red);
+    if (threadIdx.x == 0) a.part[(long long)r * a.dp_stride + f * a.nM + k] = s;
+}
+
+// ---- launches -----------------------------------------------------------------------------
+int half_tiles(int n) { return ((n + 1) / 2 + 15) / 16; }
+
+// Waves per line / row workgroup: one per tile up to 8, with up to two tiles
+// each to 512 per direction, then 16 with up to three; and its columns per tile
+// in 16s: two share each fragment load, one gives FD_PLAN_SMALL twice the
+// workgroups and the longest directions their LDS.
+int line_waves(int n) { return half_tiles(n) <= 4 ? 4 : (half_tiles(n) <= 16 ? 8 : 16); }
+int line_ct(int plan, int n) { return plan == FD_PLAN_SMALL || line_waves(n) == 16 ? 1 : 2; }
 
 template <typename T>
-bool fd_plan_fits(int np, int code) {
-    if (code < 0) return true;
-    if (code == FD_PLAN_SPLIT) return fd_plan<T>(np, code).shm_xy <= 160 * 1024;
-    if (code > 7) return false;
-    if ((code & 4) && !(code & 1)) return false;  // blocking exists in the wide kernel only
-    const size_t lim = 160 * 1024, e = sizeof(T);
-    const size_t plane = (size_t)np * (np + 1) * e, zbuf = (size_t)ZROWS * (np + 1) * e;
-    // a staging plan must actually stage something to differ from its pair
-    const FDPlan pl = fd_plan<T>(np, code);
-    const bool fits = (code & 1) ? plane <= lim && 2 * zbuf <= lim : plane <= lim && zbuf <= lim;
-    return fits && (!(code & 2) || pl.stage_xy || pl.stage_z);
+size_t line_lds(int n, int ct) {
+    const size_t p = 16 * ct + (std::is_same<T, double>::value ? 0 : 4);
+    return 2 * 16 * (size_t)half_tiles(n) * p * sizeof(T);
+}
+template <typename T>
+size_t row_lds(int n, int ct) {
+    return (size_t)16 * ct * (32 * half_tiles(n) + 1) * sizeof(T);
+}
+template <typename T>
+size_t plane_lds(int n1, int n2) {
+    // at least the partial sums of the dot
+    return std::max<size_t>((size_t)n2 * plane_pitch<T>(n1) * sizeof(T), 256);
 }
 
+template <typename T, typename TI, typename TO, bool SPLIT>
+hipError_t launch_plane(hipStream_t st, const PlaneArgs& a, const FDTables<T>& t, int nrhs) {
+    const int nt = t.nt;
+    const dim3 g(t.nM, a.nf * nrhs), b(nt <= 2 ? 256 * nt : 128 * nt);
+    size_t lds = plane_lds<T>(t.nM, t.nM);
+    if (t.nN < t.nM) {
+        lds = std::max(lds, plane_lds<T>(t.nN, t.nM));
+        lds = std::max(lds, plane_lds<T>(t.nM, t.nN));
+    }
+    if (lds > FD_LDS) return hipErrorInvalidConfiguration;
+    switch (nt) {
+        case 1: hipLaunchKernelGGL((k_fd_plane<T, TI, TO, SPLIT, 1>), g, b, lds, st, a, t); break;
+        case 2: hipLaunchKernelGGL((k_fd_plane<T, TI, TO, SPLIT, 2>), g, b, lds, st, a, t); break;
+        case 3: hipLaunchKernelGGL((k_fd_plane<T, TI, TO, SPLIT, 3>), g, b, lds, st, a, t); break;
+        case 4: hipLaunchKernelGGL((k_fd_plane<T, TI, TO, SPLIT, 4>), g, b, lds, st, a, t); break;
+        default: return hipErrorInvalidConfiguration;
+    }
+    return hipGetLastError();
+}
+
+// LINE: the line kernel (directions 2 and 3), else the row kernel (direction 1).
+template <typename T, typename TI, typename TO, bool SPLIT, bool LINE>
+hipError_t launch_lines(hipStream_t st, const LineArgs& arg, const FDTables<T>& t, int ct, int nrhs) {
+    const int nM = t.nM, nt = t.nt;
+    const size_t lds = std::max<size_t>(LINE ? line_lds<T>(nM, ct) : row_lds<T>(nM, ct), 256);
+    if (lds > FD_LDS || nt > 48) return hipErrorInvalidConfiguration;
+    const bool planes = LINE && arg.dir == 1;
+    const long long cols = planes ? nM : (long long)nM * nM;
+    LineArgs a = arg;
+    a.ctiles = (int)((cols + 16 * ct - 1) / (16 * ct));
+    a.nbatch = planes ? nM : 1;
+    const long long tiles = (long long)a.ctiles * a.nbatch * a.nf * nrhs;
+    if (tiles > INT_MAX) return hipErrorInvalidConfiguration;
+    a.ntiles = (int)tiles;
+    const dim3 g((unsigned)tiles);
+    const dim3 b(64 * std::min(nt, line_waves(nM)));
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, g, b, lds, st, a, t); };
+    const int nw = line_waves(nM);
+    if constexpr (SPLIT) {  // with the plane kernel only: up to 128 per direction
+        if (ct == 2) go(k_fd_line<T, TI, TO, true, 2, 4>);
+        else go(k_fd_line<T, TI, TO, true, 1, 4>);
+    } else if constexpr (LINE) {
+        if (nw == 16) go(k_fd_line<T, TI, TO, false, 1, 16>);
+        else if (nw == 8) go(k_fd_line<T, TI, TO, false, 2, 8>);
+        else if (ct == 2) go(k_fd_line<T, TI, TO, false, 2, 4>);
+        else go(k_fd_line<T, TI, TO, false, 1, 4>);
+    } else {
+        if (nw == 16) go(k_fd_row<T, TI, TO, 1, 16>);
+        else if (nw == 8) go(k_fd_row<T, TI, TO, 2, 8>);
+        else go(k_fd_row<T, TI, TO, 2, 4>);
+    }
+    return hipGetLastError();
+}
+
+// P_0^{-1} of the fields [vel ? 0 : 3, pres ? 4 : 3): modes 1 and 2 (one
+// plane launch, or two passes with FD_PLAN_PASSES / LINES), mode 3 with the scaling and
+// the inverse mode 3, and the velocity's inverse modes 2 and 1.  In FP64 the
+// four fields share the mode-3 launch; otherwise the pressure's writes its
+// FP64 output from a launch of its own.  Intermediates of precision T
+// ping-pong between the two scratch vectors.
 template <typename T, bool SPLIT = false>
 hipError_t run_P0(hp_ctx* c, const FDTables<T>& t, const Fields& in, const Fields& out, bool vel,
-                  bool pres, bool accumulate, int nrhs, const FdDot* dot, const FdComb* comb) {
-    // scratch for the two intermediate tensors (precision T), per rhs N values each
+                  bool pres, bool accumulate, int plan, int nrhs, const FdDot* dot,
+                  const FdComb* comb) {
     const long long N = c->N;
     T* tmp1 = reinterpret_cast<T*>(c->ws + ops_ws_stride(c) * (long long)c->opts.max_rhs);
     T* tmp2 = tmp1 + N * (long long)c->opts.max_rhs;
     const int lo = vel ? 0 : 3, hi = pres ? 4 : 3;
     if (lo >= hi) return hipSuccess;
-    const int nf = hi - lo;
-    const int nM = c->nM;
-    const int NMp = (nM + 15) & ~15;
-    XYArgs xa{};
+    const bool lines = !SPLIT && fd_plan_lines(plan);
+    const int ct = line_ct(plan, c->nM);
+    hipStream_t st = c->stream;
+    hipError_t e;
+    LineArgs la{};
+    PlaneArgs pa{};
     for (int f = 0; f < 4; ++f) {
-        for (int d = 0; d < 3; ++d) xa.dims[f][d] = (int)c->dims[f][d];
-        xa.in[f] = in.f[f];
-        xa.sin[f] = in.stride[f];
-        xa.out[f] = tmp1 + c->off[f];
-        xa.sout[f] = N;
+        for (int d = 0; d < 3; ++d) la.dims[f][d] = pa.dims[f][d] = (int)c->dims[f][d];
+        la.in[f] = pa.in[f] = in.f[f];
+        la.sin[f] = pa.sin[f] = in.stride[f];
+        la.out[f] = pa.out[f] = tmp1 + c->off[f];
+        la.sout[f] = pa.sout[f] = N;
     }
-    xa.fields_lo = lo;
-    xa.fields_hi = hi;
-    xa.inverse = 0;
-    xa.accumulate = 0;
-    if (comb) {
-        for (int f = lo; f < hi; ++f) {
-            xa.inb[f] = comb->b.f[f];
-            xa.inc[f] = comb->c.f[f];
-            xa.sinb[f] = comb->b.stride[f];
-            xa.sinc[f] = comb->c.stride[f];
-        }
-        xa.ca = comb->ca;
-        xa.cb = comb->cb;
-        xa.cc = comb->cc;
-    }
-    const FDPlan pl = fd_plan<T>(NMp, fd_plan_in_use(c, std::is_same<T, double>::value ? 0 : (SPLIT ? 2 : 1)));
-    const dim3 bxy(pl.wide ? FD_WIDE : FD_THREADS);
-    auto launch_xy = [&](const XYArgs& xa_, bool to_double, int nfields) {
-        dim3 g(nM, nfields * nrhs);
-        if (pl.split) {
-            XYArgs xs = xa_;
-            xs.nrb = NMp / 16;
-            const dim3 gs((unsigned)(8 * xs.nrb * ((nM + 7) / 8)), nfields * nrhs);
-            if (to_double) hipLaunchKernelGGL((k_fd_xy_s<T, T, double, SPLIT>), gs, dim3(FD_SPLIT), pl.shm_xy, c->stream, xs, t);
-            else hipLaunchKernelGGL((k_fd_xy_s<T, double, T, SPLIT>), gs, dim3(FD_SPLIT), pl.shm_xy, c->stream, xs, t);
-        } else if (pl.wide && pl.block && !SPLIT) {
-            if (to_double) {
-                if (pl.stage_xy) hipLaunchKernelGGL((k_fd_xy_w<T, T, double, true, SPLIT, true>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-                else hipLaunchKernelGGL((k_fd_xy_w<T, T, double, false, SPLIT, true>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-            } else {
-                if (pl.stage_xy) hipLaunchKernelGGL((k_fd_xy_w<T, double, T, true, SPLIT, true>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-                else hipLaunchKernelGGL((k_fd_xy_w<T, double, T, false, SPLIT, true>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-            }
-        } else if (pl.wide) {
-            if (to_double) {
-                if (pl.stage_xy) hipLaunchKernelGGL((k_fd_xy_w<T, T, double, true, SPLIT>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-                else hipLaunchKernelGGL((k_fd_xy_w<T, T, double, false, SPLIT>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-            } else {
-                if (pl.stage_xy) hipLaunchKernelGGL((k_fd_xy_w<T, double, T, true, SPLIT>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-                else hipLaunchKernelGGL((k_fd_xy_w<T, double, T, false, SPLIT>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-            }
-        } else {
-            if (to_double) {
-                if (pl.stage_xy) hipLaunchKernelGGL((k_fd_xy<T, T, double, true>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-                else hipLaunchKernelGGL((k_fd_xy<T, T, double, false>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-            } else {
-                if (pl.stage_xy) hipLaunchKernelGGL((k_fd_xy<T, double, T, true>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-                else hipLaunchKernelGGL((k_fd_xy<T, double, T, false>), g, bxy, pl.shm_xy, c->stream, xa_, t);
-            }
+    la.fields_lo = pa.fields_lo = lo;
+    la.nf = pa.nf = hi - lo;
+    la.two_nu = 2.0 * c->nu;
+    la.omega = c->opts.p0_scale;
+    la.pscale = 1.0;
+    auto between = [&](T* src, T* dst) {  // both buffers are intermediates
+        for (int f = 0; f < 4; ++f) {
+            la.in[f] = src + c->off[f];
+            la.sin[f] = N;
+            la.out[f] = dst + c->off[f];
+            la.sout[f] = N;
         }
     };
-    auto launch_z = [&](const ZArgs& za_, bool to_double, int nfields) {
-        const long long maxplane = (long long)nM * nM;
-        dim3 g((unsigned)((maxplane + ZROWS - 1) / ZROWS), nfields * nrhs);
-        if (pl.split) {
-            const dim3 gs((unsigned)((maxplane + 15) / 16), nfields * nrhs);
-            if (to_double) hipLaunchKernelGGL((k_fd_z_w<T, T, double, false, SPLIT, 16, FD_SPLIT>), gs, dim3(FD_SPLIT), pl.shm_z, c->stream, za_, t);
-            else hipLaunchKernelGGL((k_fd_z_w<T, T, T, false, SPLIT, 16, FD_SPLIT>), gs, dim3(FD_SPLIT), pl.shm_z, c->stream, za_, t);
-        } else if (pl.wide) {
-            dim3 b(FD_WIDE);
-            if (to_double) {
-                if (pl.stage_z) hipLaunchKernelGGL((k_fd_z_w<T, T, double, true, SPLIT>), g, b, pl.shm_z, c->stream, za_, t);
-                else hipLaunchKernelGGL((k_fd_z_w<T, T, double, false, SPLIT>), g, b, pl.shm_z, c->stream, za_, t);
-            } else {
-                if (pl.stage_z) hipLaunchKernelGGL((k_fd_z_w<T, T, T, true, SPLIT>), g, b, pl.shm_z, c->stream, za_, t);
-                else hipLaunchKernelGGL((k_fd_z_w<T, T, T, false, SPLIT>), g, b, pl.shm_z, c->stream, za_, t);
+    T *cur = tmp1, *nxt = tmp2;
+    if (lines) {
+        if (comb)
+            for (int f = lo; f < hi; ++f) {
+                if (!comb->b.f[f]) continue;
+                // one field per call (the pressure): the operator workspace
+                // holds n_Q per right-hand side
+                const long long n = c->dims[f][0] * c->dims[f][1] * c->dims[f][2];
+                e = vec_axpbypcz(st, n, nrhs, comb->ca, in.f[f], in.stride[f], comb->cb,
+                                 comb->b.f[f], comb->b.stride[f], comb->cc, comb->c.f[f],
+                                 comb->c.stride[f], c->ws, ops_ws_stride(c));
+                if (e != hipSuccess) return e;
+                la.in[f] = c->ws;
+                la.sin[f] = ops_ws_stride(c);
             }
-        } else {
-            dim3 b(FD_THREADS);
-            if (to_double) {
-                if (pl.stage_z) hipLaunchKernelGGL((k_fd_z<T, T, double, true>), g, b, pl.shm_z, c->stream, za_, t);
-                else hipLaunchKernelGGL((k_fd_z<T, T, double, false>), g, b, pl.shm_z, c->stream, za_, t);
-            } else {
-                if (pl.stage_z) hipLaunchKernelGGL((k_fd_z<T, T, T, true>), g, b, pl.shm_z, c->stream, za_, t);
-                else hipLaunchKernelGGL((k_fd_z<T, T, T, false>), g, b, pl.shm_z, c->stream, za_, t);
+        if ((e = launch_lines<T, double, T, false, false>(st, la, t, ct, nrhs)) != hipSuccess) return e;
+        between(tmp1, tmp2);
+        la.dir = 1;
+        if ((e = launch_lines<T, T, T, false, true>(st, la, t, ct, nrhs)) != hipSuccess) return e;
+        cur = tmp2;
+        nxt = tmp1;
+    } else {
+        if (comb) {
+            for (int f = lo; f < hi; ++f) {
+                pa.inb[f] = comb->b.f[f];
+                pa.inc[f] = comb->c.f[f];
+                pa.sinb[f] = comb->b.stride[f];
+                pa.sinc[f] = comb->c.stride[f];
             }
+            pa.ca = comb->ca;
+            pa.cb = comb->cb;
+            pa.cc = comb->cc;
         }
-    };
-    launch_xy(xa, false, nf);
-    ZArgs za{};
-    for (int f = 0; f < 4; ++f) {
-        for (int d = 0; d < 3; ++d) za.dims[f][d] = (int)c->dims[f][d];
-        za.in[f] = tmp1 + c->off[f];
-        za.sin[f] = N;
-        za.out[f] = tmp2 + c->off[f];
-        za.sout[f] = N;
+        if ((e = launch_plane<T, double, T, SPLIT>(st, pa, t, nrhs)) != hipSuccess) return e;
     }
-    za.two_nu = 2.0 * c->nu;
-    za.omega = c->opts.p0_scale;
+    between(cur, nxt);
+    la.dir = 2;
+    la.fused = 1;
+    la.pscale = la.omega * la.two_nu;
     // the pressure's mode-3 step writes the final output; the velocity's
-    // feeds the inverse xy step.  In FP64 both output types agree, so the
-    // four fields share one launch.
-    za.out[3] = out.f[3];
-    za.sout[3] = out.stride[3];
-    za.accumulate = accumulate ? (1 << 3) : 0;
+    // feeds the inverse modes 2 and 1
+    la.out[3] = out.f[3];
+    la.sout[3] = out.stride[3];
+    la.accumulate = accumulate ? (1 << 3) : 0;
     if (vel && pres && std::is_same<T, double>::value) {
-        ZArgs zb = za;
-        zb.fields_lo = 0;
-        zb.fields_hi = 4;
-        launch_z(zb, true, 4);
+        if ((e = launch_lines<T, T, double, SPLIT, true>(st, la, t, ct, nrhs)) != hipSuccess) return e;
     } else {
         if (vel) {
-            ZArgs zv = za;
-            zv.fields_lo = 0;
-            zv.fields_hi = 3;
-            launch_z(zv, false, 3);
+            la.fields_lo = 0;
+            la.nf = 3;
+            if ((e = launch_lines<T, T, T, SPLIT, true>(st, la, t, ct, nrhs)) != hipSuccess) return e;
         }
         if (pres) {
-            ZArgs zp = za;
-            zp.fields_lo = 3;
-            zp.fields_hi = 4;
+            LineArgs lp = la;
+            lp.fields_lo = 3;
+            lp.nf = 1;
             if (dot && !vel) {
-                zp.dw = dot->with + c->off[3];
-                zp.dpart = dot->part;
-                zp.dp_stride = fd_dot_count(c, false);
+                lp.dw = dot->with + c->off[3];
+                lp.dpart = dot->part;
+                lp.dp_stride = fd_dot_count(c, false);
             }
-            launch_z(zp, true, 1);
+            if ((e = launch_lines<T, T, double, SPLIT, true>(st, lp, t, ct, nrhs)) != hipSuccess) return e;
         }
     }
-    if (vel) {
-        XYArgs xi = xa;
+    if (!vel) return hipSuccess;
+    la.fields_lo = 0;
+    la.nf = 3;
+    la.inverse = 1;
+    la.fused = 0;
+    la.accumulate = accumulate ? 7 : 0;
+    if (lines) {
+        LineArgs lm = la;
         for (int f = 0; f < 3; ++f) {
-            xi.in[f] = tmp2 + c->off[f];
-            xi.sin[f] = N;
-            xi.out[f] = out.f[f];
-            xi.sout[f] = out.stride[f];
+            lm.in[f] = nxt + c->off[f];
+            lm.out[f] = cur + c->off[f];
         }
-        xi.fields_lo = 0;
-        xi.fields_hi = 3;
-        xi.inverse = 1;
-        xi.accumulate = accumulate ? 1 : 0;
+        lm.dir = 1;
+        lm.accumulate = 0;
+        if ((e = launch_lines<T, T, T, false, true>(st, lm, t, ct, nrhs)) != hipSuccess) return e;
+        for (int f = 0; f < 3; ++f) {
+            la.in[f] = cur + c->off[f];
+            la.out[f] = out.f[f];
+            la.sout[f] = out.stride[f];
+        }
+        la.dir = 0;
+        if ((e = launch_lines<T, T, double, false, false>(st, la, t, ct, nrhs)) != hipSuccess) return e;
         if (dot) {
-            // xy partials: per rhs 3 nM, times the row blocks of the split plan
-            // (see fd_dot_count)
-            for (int f = 0; f < 3; ++f) xi.dw[f] = dot->with + c->off[f];
-            xi.dpart = dot->part;
-            xi.dp_stride = fd_dot_count(c, true);
-            xi.dp_planes = nM;
-            xi.dp_rb = 3LL * nM;
+            DotArgs da{};
+            for (int f = 0; f < 3; ++f) {
+                da.y[f] = out.f[f];
+                da.w[f] = dot->with + c->off[f];
+                da.stride[f] = out.stride[f];
+                da.plane[f] = c->dims[f][0] * c->dims[f][1];
+                da.planes[f] = (int)c->dims[f][2];
+            }
+            da.part = dot->part;
+            da.dp_stride = fd_dot_count(c, true);
+            da.nM = c->nM;
+            hipLaunchKernelGGL(k_fd_dot_vel, dim3(c->nM, 3, nrhs), dim3(256), 0, st, da);
         }
-        launch_xy(xi, true, 3);
+        return hipGetLastError();
     }
-    return hipGetLastError();
+    PlaneArgs pi{};
+    for (int f = 0; f < 3; ++f) {
+        for (int d = 0; d < 3; ++d) pi.dims[f][d] = (int)c->dims[f][d];
+        pi.in[f] = nxt + c->off[f];
+        pi.sin[f] = N;
+        pi.out[f] = out.f[f];
+        pi.sout[f] = out.stride[f];
+        if (dot) pi.dw[f] = dot->with + c->off[f];
+    }
+    pi.nf = 3;
+    pi.inverse = 1;
+    pi.accumulate = accumulate ? 1 : 0;
+    if (dot) {
+        pi.dpart = dot->part;
+        pi.dp_stride = fd_dot_count(c, true);
+        pi.dp_planes = c->nM;
+    }
+    return launch_plane<T, T, double, SPLIT>(st, pi, t, nrhs);
 }
 
-// ---- mode products as batched GEMMs (directions of any length) ----------------------
-// The in-LDS kernels above hold a whole direction (<= 128) in MFMA tiles.  For
-// longer directions -- and as the selectable plan FD_GEMM at any size -- each
-// mode product of fast diagonalisation runs as a (batched) GEMM over HBM:
-//     C(i, j) = sum_k A(i, k) B(k, j),  B(k, j) = B[k ldb + j] (a dense 1D table)
-// with strided A and C; batch b adds (b % nb1) s1 + (b / nb1) s2 to A and C.
-// Mode 1 is taken transposed (i over the (i2, i3) lines, j over i1') so that
-// B is always a row-major 1D table and the tensor is the A operand:
-//   mode 1: A(i, k) = X[k + i n1]            (k contiguous), C(i, j) = Y[j + i n1]
-//   mode 2: A(i, k) = X[i + k n1], per i3    (i contiguous), C(i, j) = Y[i + j n1]
-//   mode 3: A(i, k) = X[i + k n1 n2]         (i contiguous), C(i, j) = Y[i + j n1 n2]
-// with B = U (forward) or U^T (inverse), M^^{-1} for the pressure.  The
-// eigenvalue scaling (epilogue 2) is fused into the forward mode-3 product.
-// Tile: 64 x 64 outputs per 256-thread workgroup, each wave 2 x 2 MFMA tiles
-// of 16 x 16 (sub-tiles entirely outside the output are skipped, so a ragged
-// direction costs at most 15 padded rows); the contraction runs in chunks of
-// 16 staged k-major in LDS (pitch 80: the 16 lanes of one k row and the next
-// k row fall in disjoint banks), double buffered, the next chunk loaded into
-// registers while the current one is multiplied.  The output tile goes
-// through LDS so that it is stored along C's contiguous direction.
-constexpr int GT = 64;
-constexpr int GK = 16;
-constexpr int GP = 80;
-constexpr int GTHREADS = 256;
-
-struct GemmArgs {
-    const void* A;
-    long long a_i, a_k, a_s1, a_s2;
-    const void* B;
-    int ldb;
-    void* C;
-    long long c_i, c_j, c_s1, c_s2;
-    int M, N, K, nb1, tiles_m;
-    int epi;          // 0: C = acc, 1: C = alpha acc, 2: C = alpha acc / (l1[i1] + l2[i2] + l3[j])
-    int accumulate;   // C += (epilogue value)
-    double alpha;
-    const double* l1;
-    const double* l2;
-    const double* l3;
-    int n1;           // epilogue 2: i = i1 + n1 i2
-};
-
-template <typename T, typename TI, typename TO, bool A_KC, bool C_IC>
-__global__ __launch_bounds__(GTHREADS) void k_mode_gemm(GemmArgs g) {
-    using M = Mfma<T>;
-    using V = typename M::V;
-    constexpr int TILE_T = 2 * 2 * GK * GP;       // As, Bs, double buffered
-    constexpr int CT_T = GT * (GT + 1);           // the output tile [i][j]
-    __shared__ T sm[TILE_T > CT_T ? TILE_T : CT_T];
-    T* As = sm;                                   // [buf][k][i]
-    T* Bs = sm + 2 * GK * GP;                     // [buf][k][j]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lr = lane & 15, lk = lane >> 4;
-    const int tm = blockIdx.x % g.tiles_m, tn = blockIdx.x / g.tiles_m;
-    const int i0 = tm * GT, j0 = tn * GT;
-    const long long bb = blockIdx.y;
-    const long long boffA = (bb % g.nb1) * g.a_s1 + (bb / g.nb1) * g.a_s2;
-    const long long boffC = (bb % g.nb1) * g.c_s1 + (bb / g.nb1) * g.c_s2;
-    const TI* A = reinterpret_cast<const TI*>(g.A) + boffA;
-    const T* B = reinterpret_cast<const T*>(g.B);
-    // staging: four A and four B values per thread per chunk
-    T ra[4], rb[4];
-    auto load = [&](int k0) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int e = tid + GTHREADS * s;
-            int i, k;
-            if (A_KC) { k = e % GK; i = e / GK; }
-            else { i = e % GT; k = e / GT; }
-            const int gi = i0 + i, gk = k0 + k;
-            ra[s] = (gi < g.M && gk < g.K) ? (T)A[gi * g.a_i + gk * g.a_k] : (T)0;
-            const int j = e % GT, kb = e / GT;
-            const int gj = j0 + j, gkb = k0 + kb;
-            rb[s] = (gj < g.N && gkb < g.K) ? B[(long long)gkb * g.ldb + gj] : (T)0;
-        }
-    };
-    auto store = [&](int buf) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int e = tid + GTHREADS * s;
-            int i, k;
-            if (A_KC) { k = e % GK; i = e / GK; }
-            else { i = e % GT; k = e / GT; }
-            As[buf * GK * GP + k * GP + i] = ra[s];
-            Bs[buf * GK * GP + (e / GT) * GP + (e % GT)] = rb[s];
-        }
-    };
-    const int wr = (wave & 1) * 32, wc = (wave >> 1) * 32;
-    bool on[2][2];
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-            on[ii][jj] = (i0 + wr + 16 * ii < g.M) && (j0 + wc + 16 * jj < g.N);
-    V acc[2][2];
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) acc[ii][jj] = V{0, 0, 0, 0};
-    load(0);
-    for (int k0 = 0, it = 0; k0 < g.K; k0 += GK, ++it) {
-        const int buf = it & 1;
-        store(buf);
-        __syncthreads();
-        if (k0 + GK < g.K) load(k0 + GK);
-        const T* as = As + buf * GK * GP;
-        const T* bs = Bs + buf * GK * GP;
-#pragma unroll
-        for (int st = 0; st < GK / 4; ++st) {
-            const int kk = 4 * st + lk;
-            T av[2], bv[2];
-#pragma unroll
-            for (int ii = 0; ii < 2; ++ii) av[ii] = as[kk * GP + wr + 16 * ii + lr];
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj) bv[jj] = bs[kk * GP + wc + 16 * jj + lr];
-#pragma unroll
-            for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-                for (int jj = 0; jj < 2; ++jj)
-                    if (on[ii][jj]) acc[ii][jj] = M::mma(av[ii], bv[jj], acc[ii][jj]);
-        }
-    }
-    __syncthreads();  // every wave is done with As/Bs: the output tile reuses them
-    T* Ct = sm;
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-            if (on[ii][jj])
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    Ct[(wr + 16 * ii + M::row(lk, e)) * (GT + 1) + wc + 16 * jj + lr] = acc[ii][jj][e];
-    __syncthreads();
-    TO* C = reinterpret_cast<TO*>(g.C) + boffC;
-    for (int s = 0; s < GT * GT / GTHREADS; ++s) {
-        const int e = tid + GTHREADS * s;
-        int i, j;
-        if (C_IC) { i = e % GT; j = e / GT; }
-        else { j = e % GT; i = e / GT; }
-        const int gi = i0 + i, gj = j0 + j;
-        if (gi >= g.M || gj >= g.N) continue;
-        double v = (double)Ct[i * (GT + 1) + j];
-        if (g.epi == 1) {
-            v *= g.alpha;
-        } else if (g.epi == 2) {
-            const int i1 = gi % g.n1, i2 = gi / g.n1;
-            v *= g.alpha / (g.l1[i1] + g.l2[i2] + g.l3[gj]);
-        }
-        TO* dst = C + (long long)gi * g.c_i + (long long)gj * g.c_j;
-        if (g.accumulate) *dst += (TO)v;
-        else *dst = (TO)v;
-    }
-}
-
-// Partial sums of y . w for the Krylov dot of launch_P0, in the layout of the
-// in-LDS kernels: velocity, one per (field, i3-plane) at f nM + k; pressure,
-// one per ZROWS-row block of the (i1, i2) plane.  Fixed-order block sums.
-__global__ __launch_bounds__(256) void k_fd_dot_vel(const double* y, const double* w,
-                                                    long long stride, long long plane,
-                                                    double* part, long long dp_stride,
-                                                    int slot0) {
-    __shared__ double red[4];
-    const int k = blockIdx.x, r = blockIdx.y;
-    const double* yr = y + (long long)r * stride + (long long)k * plane;
-    const double* wr = w + (long long)r * stride + (long long)k * plane;
-    double s = 0.0;
-    for (long long i = threadIdx.x; i < plane; i += 256) s += yr[i] * wr[i];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        part[(long long)r * dp_stride + slot0 + k] = red[0] + red[1] + red[2] + red[3];
-}
-
-__global__ __launch_bounds__(256) void k_fd_dot_pres(const double* y, const double* w,
-                                                     long long stride, long long plane, int n3,
-                                                     double* part, long long dp_stride) {
-    __shared__ double red[4];
-    const int r = blockIdx.y;
-    const long long r0 = (long long)blockIdx.x * ZROWS;
-    const double* yr = y + (long long)r * stride;
-    const double* wr = w + (long long)r * stride;
-    double s = 0.0;
-    for (long long idx = threadIdx.x; idx < (long long)ZROWS * n3; idx += 256) {
-        const long long kk = idx / ZROWS, row = idx - kk * ZROWS;
-        if (r0 + row >= plane) continue;
-        const long long o = r0 + row + kk * plane;
-        s += yr[o] * wr[o];
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        part[(long long)r * dp_stride + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
-}
-
-template <typename T, typename TI, typename TO, bool A_KC, bool C_IC>
-hipError_t gemm_launch(hipStream_t st, GemmArgs g, int nbatch) {
-    g.tiles_m = (g.M + GT - 1) / GT;
-    const int tiles_n = (g.N + GT - 1) / GT;
-    if (g.M <= 0 || g.N <= 0 || nbatch <= 0) return hipSuccess;
-    if (nbatch > 65535) return hipErrorInvalidConfiguration;  // grid y limit
-    hipLaunchKernelGGL((k_mode_gemm<T, TI, TO, A_KC, C_IC>), dim3(g.tiles_m * tiles_n, nbatch),
-                       dim3(GTHREADS), 0, st, g);
-    return hipGetLastError();
-}
-
-// P_0^{-1} by mode-product GEMMs (velocity: six products per component, the
-// eigenvalue scaling fused into the forward mode-3 product; pressure: three
-// products with M^^{-1}, the factor 2 nu w in the last).  Intermediates of
-// precision T ping-pong between the two fast-diagonalisation scratch
-// buffers; the combination input (comb) is formed first in the operator
-// workspace, the dot partials are summed from the final output.
-template <typename T>
-hipError_t run_P0_gemm(hp_ctx* c, const FDTables<T>& t, const Fields& in, const Fields& out,
-                       bool vel, bool pres, bool accumulate, int nrhs, const FdDot* dot,
-                       const FdComb* comb) {
-    const long long N = c->N, R = c->opts.max_rhs;
-    T* tmp1 = reinterpret_cast<T*>(c->ws + ops_ws_stride(c) * R);
-    T* tmp2 = tmp1 + N * R;
-    const double omega = c->opts.p0_scale, two_nu = 2.0 * c->nu;
-    hipError_t e = hipSuccess;
-    for (int f = vel ? 0 : 3; f < (pres ? 4 : 3) && e == hipSuccess; ++f) {
-        const int n1 = (int)c->dims[f][0], n2 = (int)c->dims[f][1], n3 = (int)c->dims[f][2];
-        const long long n12 = (long long)n1 * n2;
-        const double* x = in.f[f];
-        long long sx = in.stride[f];
-        if (comb && comb->b.f[f]) {
-            // x = ca in + cb b + cc c into the operator workspace (n_Q per rhs >= any field)
-            double* xc = c->ws;
-            e = vec_axpbypcz(c->stream, n12 * n3, nrhs, comb->ca, x, sx, comb->cb, comb->b.f[f],
-                             comb->b.stride[f], comb->cc, comb->c.f[f], comb->c.stride[f], xc,
-                             ops_ws_stride(c));
-            if (e != hipSuccess) break;
-            x = xc;
-            sx = ops_ws_stride(c);
-        }
-        T* Y1 = tmp1 + c->off[f];
-        T* Y2 = tmp2 + c->off[f];
-        const bool isp = (f == 3);
-        // 1D tables per direction: forward B = U, inverse B = U^T (M^^{-1} for p)
-        const T* Uf[3];
-        const T* Ui[3];
-        int ld[3];
-        for (int d = 0; d < 3; ++d) {
-            const bool kdir = (d == f);
-            Uf[d] = isp ? t.Mi : (kdir ? t.UK : t.UT);
-            Ui[d] = isp ? t.Mi : (kdir ? t.UKt : t.UTt);
-            ld[d] = (!isp && kdir) ? t.NNp : t.NMp;
-        }
-        auto mode1 = [&](const void* src, long long ss, const T* U, int ldu, void* dst,
-                         long long sd, bool to_out, int epi, double alpha, bool acc) {
-            GemmArgs g{};
-            g.A = src; g.a_i = n1; g.a_k = 1; g.a_s1 = ss; g.a_s2 = 0;
-            g.B = U; g.ldb = ldu;
-            g.C = dst; g.c_i = n1; g.c_j = 1; g.c_s1 = sd; g.c_s2 = 0;
-            g.M = (int)(n2 * (long long)n3); g.N = n1; g.K = n1; g.nb1 = nrhs;
-            g.epi = epi; g.alpha = alpha; g.accumulate = acc;
-            if (to_out) return gemm_launch<T, T, double, true, false>(c->stream, g, nrhs);
-            return gemm_launch<T, double, T, true, false>(c->stream, g, nrhs);
-        };
-        auto mode2 = [&](const T* src, const T* U, int ldu, T* dst) {
-            GemmArgs g{};
-            g.A = src; g.a_i = 1; g.a_k = n1; g.a_s1 = n12; g.a_s2 = N;
-            g.B = U; g.ldb = ldu;
-            g.C = dst; g.c_i = 1; g.c_j = n1; g.c_s1 = n12; g.c_s2 = N;
-            g.M = n1; g.N = n2; g.K = n2; g.nb1 = n3;
-            return gemm_launch<T, T, T, false, true>(c->stream, g, n3 * nrhs);
-        };
-        auto mode3 = [&](const T* src, const T* U, int ldu, void* dst, long long sd, bool to_out,
-                         int epi, double alpha, bool acc) {
-            GemmArgs g{};
-            g.A = src; g.a_i = 1; g.a_k = n12; g.a_s1 = N; g.a_s2 = 0;
-            g.B = U; g.ldb = ldu;
-            g.C = dst; g.c_i = 1; g.c_j = n12; g.c_s1 = sd; g.c_s2 = 0;
-            g.M = (int)n12; g.N = n3; g.K = n3; g.nb1 = nrhs;
-            g.epi = epi; g.alpha = alpha; g.accumulate = acc;
-            g.n1 = n1;
-            g.l1 = (f == 0) ? t.lamK : t.lamT;
-            g.l2 = (f == 1) ? t.lamK : t.lamT;
-            g.l3 = (f == 2) ? t.lamK : t.lamT;
-            if (to_out) return gemm_launch<T, T, double, false, true>(c->stream, g, nrhs);
-            return gemm_launch<T, T, T, false, true>(c->stream, g, nrhs);
-        };
-        if (isp) {
-            if ((e = mode1(x, sx, Uf[0], ld[0], Y1, N, false, 0, 1.0, false)) != hipSuccess) break;
-            if ((e = mode2(Y1, Uf[1], ld[1], Y2)) != hipSuccess) break;
-            e = mode3(Y2, Uf[2], ld[2], out.f[3], out.stride[3], true, 1, omega * two_nu,
-                      accumulate);
-        } else {
-            if ((e = mode1(x, sx, Uf[0], ld[0], Y1, N, false, 0, 1.0, false)) != hipSuccess) break;
-            if ((e = mode2(Y1, Uf[1], ld[1], Y2)) != hipSuccess) break;
-            if ((e = mode3(Y2, Uf[2], ld[2], Y1, N, false, 2, omega / two_nu, false)) != hipSuccess)
-                break;
-            if ((e = mode3(Y1, Ui[2], ld[2], Y2, N, false, 0, 1.0, false)) != hipSuccess) break;
-            if ((e = mode2(Y2, Ui[1], ld[1], Y1)) != hipSuccess) break;
-            e = mode1(Y1, N, Ui[0], ld[0], out.f[f], out.stride[f], true, 0, 1.0, accumulate);
-        }
-    }
-    if (e != hipSuccess || !dot) return e;
-    const int nM = c->nM;
-    if (vel && !pres) {
-        for (int f = 0; f < 3; ++f) {
-            const long long plane = c->dims[f][0] * c->dims[f][1];
-            hipLaunchKernelGGL(k_fd_dot_vel, dim3((unsigned)c->dims[f][2], nrhs), dim3(256), 0,
-                               c->stream, out.f[f], dot->with + c->off[f], out.stride[f], plane,
-                               dot->part, 3LL * nM, f * nM);
-        }
-    } else if (pres && !vel) {
-        const long long plane = (long long)nM * nM;
-        hipLaunchKernelGGL(k_fd_dot_pres, dim3((unsigned)((plane + ZROWS - 1) / ZROWS), nrhs),
-                           dim3(256), 0, c->stream, out.f[3], dot->with + c->off[3], out.stride[3],
-                           plane, nM, dot->part, fd_dot_count(c, false));
-    }
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t set_fd_attrs() {
-    const int bytes = 160 * 1024;
-    const void* ks[] = {
-        reinterpret_cast<const void*>(&k_fd_xy<T, double, T, true>),
-        reinterpret_cast<const void*>(&k_fd_xy<T, double, T, false>),
-        reinterpret_cast<const void*>(&k_fd_xy<T, T, double, true>),
-        reinterpret_cast<const void*>(&k_fd_xy<T, T, double, false>),
-        reinterpret_cast<const void*>(&k_fd_z<T, T, T, true>),
-        reinterpret_cast<const void*>(&k_fd_z<T, T, T, false>),
-        reinterpret_cast<const void*>(&k_fd_z<T, T, double, true>),
-        reinterpret_cast<const void*>(&k_fd_z<T, T, double, false>),
-        reinterpret_cast<const void*>(&k_fd_xy_w<T, double, T, true>),
-        reinterpret_cast<const void*>(&k_fd_xy_w<T, double, T, false>),
-        reinterpret_cast<const void*>(&k_fd_xy_w<T, T, double, true>),
-        reinterpret_cast<const void*>(&k_fd_xy_w<T, T, double, false>),
-        reinterpret_cast<const void*>(&k_fd_xy_w<T, double, T, true, false, true>),
-        reinterpret_cast<const void*>(&k_fd_xy_w<T, double, T, false, false, true>),
-        reinterpret_cast<const void*>(&k_fd_xy_w<T, T, double, true, false, true>),
-        reinterpret_cast<const void*>(&k_fd_xy_w<T, T, double, false, false, true>),
-        reinterpret_cast<const void*>(&k_fd_z_w<T, T, T, true>),
-        reinterpret_cast<const void*>(&k_fd_z_w<T, T, T, false>),
-        reinterpret_cast<const void*>(&k_fd_z_w<T, T, double, true>),
-        reinterpret_cast<const void*>(&k_fd_z_w<T, T, double, false>),
-        reinterpret_cast<const void*>(&k_fd_xy_s<T, double, T>),
-        reinterpret_cast<const void*>(&k_fd_xy_s<T, T, double>),
-        reinterpret_cast<const void*>(&k_fd_z_w<T, T, T, false, false, 16, FD_SPLIT>),
-        reinterpret_cast<const void*>(&k_fd_z_w<T, T, double, false, false, 16, FD_SPLIT>)};
+// dynamic LDS up to the CU's 160 KiB for every instantiation
+template <size_t N>
+hipError_t set_lds(const void* const (&ks)[N]) {
     for (const void* k : ks) {
-        hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        const hipError_t e =
+            hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FD_LDS);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+template <typename F>
+const void* fptr(F* f) {
+    return reinterpret_cast<const void*>(f);
+}
+template <typename T, typename TI, typename TO, bool SPLIT>
+hipError_t set_plane_attrs() {
+    return set_lds({fptr(&k_fd_plane<T, TI, TO, SPLIT, 1>), fptr(&k_fd_plane<T, TI, TO, SPLIT, 2>),
+                    fptr(&k_fd_plane<T, TI, TO, SPLIT, 3>), fptr(&k_fd_plane<T, TI, TO, SPLIT, 4>)});
+}
+template <typename T, typename TI, typename TO>
+hipError_t set_row_attrs() {
+    return set_lds({fptr(&k_fd_row<T, TI, TO, 2, 4>), fptr(&k_fd_row<T, TI, TO, 2, 8>),
+                    fptr(&k_fd_row<T, TI, TO, 1, 16>)});
+}
+template <typename T, typename TO>
+hipError_t set_line_attrs() {
+    return set_lds({fptr(&k_fd_line<T, T, TO, false, 1, 4>), fptr(&k_fd_line<T, T, TO, false, 2, 4>),
+                    fptr(&k_fd_line<T, T, TO, false, 2, 8>), fptr(&k_fd_line<T, T, TO, false, 1, 16>)});
 }
 
 }  // namespace
 
 hipError_t fd_init_attributes() {
-    hipError_t e = set_fd_attrs<double>();
-    if (e != hipSuccess) return e;
-    e = set_fd_attrs<float>();
-    if (e != hipSuccess) return e;
-    const void* ks[] = {
-        reinterpret_cast<const void*>(&k_fd_xy_w<float, double, float, true, true>),
-        reinterpret_cast<const void*>(&k_fd_xy_w<float, double, float, false, true>),
-        reinterpret_cast<const void*>(&k_fd_xy_w<float, float, double, true, true>),
-        reinterpret_cast<const void*>(&k_fd_xy_w<float, float, double, false, true>),
-        reinterpret_cast<const void*>(&k_fd_z_w<float, float, float, true, true>),
-        reinterpret_cast<const void*>(&k_fd_z_w<float, float, float, false, true>),
-        reinterpret_cast<const void*>(&k_fd_z_w<float, float, double, true, true>),
-        reinterpret_cast<const void*>(&k_fd_z_w<float, float, double, false, true>),
-        reinterpret_cast<const void*>(&k_fd_xy_s<float, double, float, true>),
-        reinterpret_cast<const void*>(&k_fd_xy_s<float, float, double, true>),
-        reinterpret_cast<const void*>(&k_fd_z_w<float, float, float, false, true, 16, FD_SPLIT>),
-        reinterpret_cast<const void*>(&k_fd_z_w<float, float, double, false, true, 16, FD_SPLIT>)};
-    for (const void* k : ks) {
-        e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    const hipError_t es[] = {
+        set_plane_attrs<double, double, double, false>(), set_plane_attrs<float, double, float, false>(),
+        set_plane_attrs<float, float, double, false>(),   set_plane_attrs<float, double, float, true>(),
+        set_plane_attrs<float, float, double, true>(),    set_row_attrs<double, double, double>(),
+        set_row_attrs<float, double, float>(),            set_row_attrs<float, float, double>(),
+        set_line_attrs<double, double>(),                 set_line_attrs<float, float>(),
+        set_line_attrs<float, double>(),
+        set_lds({fptr(&k_fd_line<float, float, float, true, 1, 4>),
+                 fptr(&k_fd_line<float, float, float, true, 2, 4>),
+                 fptr(&k_fd_line<float, float, double, true, 1, 4>),
+                 fptr(&k_fd_line<float, float, double, true, 2, 4>)})};
+    for (hipError_t e : es)
         if (e != hipSuccess) return e;
-    }
     return hipSuccess;
 }
 
-// directions longer than the in-LDS kernels hold (8 MFMA tiles of 16)
-static bool fd_needs_gemm(const hp_ctx* c) { return ((c->nM + 15) & ~15) > 128; }
+int fd_half_tiles(int n) { return half_tiles(n); }
 
+// Fragments of the half-size matrices of one parity: tile (u, t), lane l,
+// value i holds A(16u + l%16, 16t + kmap(l/16, i)), zero outside.
+template <typename T, typename F>
+static void pack_half(std::vector<T>& out, int h, int nt, F A) {
+    for (int u = 0; u < nt; ++u)
+        for (int t = 0; t < nt; ++t)
+            for (int l = 0; l < 64; ++l)
+                for (int i = 0; i < 4; ++i) {
+                    const int lk = l / 16;
+                    const int k = 16 * t + (std::is_same<T, double>::value ? lk + 4 * i : 4 * lk + i);
+                    const int m = 16 * u + l % 16;
+                    out.push_back(m < h && k < h ? (T)A(m, k) : (T)0);
+                }
+}
+
+template <typename T>
+void fd_pack(const std::vector<double>& A, int n, int nt, FdPack kind, std::vector<T>& out) {
+    const int he = (n + 1) / 2, ho = n / 2;
+    auto at = [&](int i, int j) { return A[(size_t)i * n + j]; };
+    for (int par = 0; par < 2; ++par) {
+        const int h = par ? ho : he, m0 = par ? he : 0;
+        if (kind == FdPack::forward) {          // rows: modes, columns: points
+            pack_half(out, h, nt, [&](int m, int k) { return at(k, m0 + m); });
+        } else if (kind == FdPack::inverse) {   // rows: points, columns: modes
+            pack_half(out, h, nt, [&](int m, int k) { return at(m, m0 + k); });
+        } else {
+            // symmetric matrix on the folded vectors: the middle column once
+            pack_half(out, h, nt, [&](int m, int k) {
+                return k >= ho ? at(m, k) : 0.5 * (at(m, k) + (par ? -1.0 : 1.0) * at(m, n - 1 - k));
+            });
+        }
+    }
+}
+template void fd_pack<double>(const std::vector<double>&, int, int, FdPack, std::vector<double>&);
+template void fd_pack<float>(const std::vector<double>&, int, int, FdPack, std::vector<float>&);
+
+// Whether plan `plan` exists for this mesh and precision (see hp_internal.h).
 bool fd_plan_valid(const hp_ctx* c, int precision, int plan) {
-    const int NMp = (c->nM + 15) & ~15;
-    // the mode-product GEMMs run in FP64 or FP32 (split BF16 keeps to the in-LDS kernels)
-    if (plan == FD_PLAN_GEMM) return precision != HP_PREC_BF16X3;
-    if (fd_needs_gemm(c)) return false;
-    if (precision == HP_PREC_BF16X3 && plan >= 0 && (plan & 4)) return false;  // not blocked
-    return precision == HP_PREC_FP64 ? fd_plan_fits<double>(NMp, plan) : fd_plan_fits<float>(NMp, plan);
+    if (fd_plan_lines(plan) && precision == HP_PREC_BF16X3) return false;
+    if (plan == FD_PLAN_LINES) return true;
+    return (plan == FD_PLAN_PASSES || plan == FD_PLAN_PLANE || plan == FD_PLAN_SMALL) && c->nM <= FD_PLANE_MAX;
 }
 
 int fd_plan_in_use(const hp_ctx* c, int precision) {
     if (c->fd_force >= 0) return c->fd_force;
     if (c->opts.fd_plan >= 0 && fd_plan_valid(c, precision, c->opts.fd_plan)) return c->opts.fd_plan;
-    if (fd_needs_gemm(c)) return FD_PLAN_GEMM;
-    return c->fd_tuned[precision];
+    if (c->nM > FD_PLANE_MAX) return FD_PLAN_LINES;
+    return c->fd_tuned[precision] >= 0 ? c->fd_tuned[precision] : FD_PLAN_PLANE;
 }
 
 long long fd_dot_count(const hp_ctx* c, bool vel) {
     const long long nM = c->nM;
-    if (fd_plan_in_use(c, HP_PREC_FP64) == FD_PLAN_SPLIT)
-        return vel ? 3 * nM * (((nM + 15) & ~15) / 16) : (nM * nM + 15) / 16;
-    return vel ? 3 * nM : (nM * nM + ZROWS - 1) / ZROWS;
+    if (vel) return 3 * nM;
+    // workgroups of the pressure's mode-3 launch
+    const int ct = line_ct(fd_plan_in_use(c, HP_PREC_FP64), c->nM);
+    return (nM * nM + 16 * ct - 1) / (16 * ct);
 }
 
 long long fd_dot_capacity(const hp_ctx* c, bool vel) {
     const long long nM = c->nM;
-    return vel ? 3 * nM * (((nM + 15) & ~15) / 16) : (nM * nM + 15) / 16;
+    return vel ? 3 * nM : (nM * nM + 15) / 16;
 }
 
 hipError_t launch_P0(hp_ctx* c, const Fields& in, const Fields& out, bool vel, bool pres,
                      bool accumulate, int precision, int nrhs, const FdDot* dot,
                      const FdComb* comb) {
     if (dot && (precision != HP_PREC_FP64 || (vel && pres))) return hipErrorInvalidValue;
-    if (fd_plan_in_use(c, precision) == FD_PLAN_GEMM || fd_needs_gemm(c)) {
-        // long directions with split BF16 fall back to FP32 products
-        if (precision == HP_PREC_FP64)
-            return run_P0_gemm<double>(c, c->fd64, in, out, vel, pres, accumulate, nrhs, dot, comb);
-        return run_P0_gemm<float>(c, c->fd32, in, out, vel, pres, accumulate, nrhs, dot, comb);
-    }
+    const int plan = fd_plan_in_use(c, precision);
     if (precision == HP_PREC_FP64)
-        return run_P0<double>(c, c->fd64, in, out, vel, pres, accumulate, nrhs, dot, comb);
-    if (precision == HP_PREC_BF16X3)
-        return run_P0<float, true>(c, c->fd32, in, out, vel, pres, accumulate, nrhs, nullptr, comb);
-    return run_P0<float>(c, c->fd32, in, out, vel, pres, accumulate, nrhs, nullptr, comb);
+        return run_P0<double>(c, c->fd64, in, out, vel, pres, accumulate, plan, nrhs, dot, comb);
+    // split BF16 takes FP32 products in the direction passes
+    if (precision == HP_PREC_BF16X3 && !fd_plan_lines(plan))
+        return run_P0<float, true>(c, c->fd32, in, out, vel, pres, accumulate, plan, nrhs, nullptr, comb);
+    return run_P0<float>(c, c->fd32, in, out, vel, pres, accumulate, plan, nrhs, nullptr, comb);
 }
 
 }  // namespace hp

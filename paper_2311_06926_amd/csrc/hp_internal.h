@@ -22,18 +22,23 @@ struct BandTables {
     int w[NBAND];
 };
 
-// Dense (padded) matrices for fast diagonalisation on MFMA tiles.
+// Half-size 1D matrices for fast diagonalisation as MFMA fragments (fd.hip):
+// per table the even half's nt x nt tiles of 256 values, then the odd half's.
 template <typename T>
 struct FDTables {
-    const T* UK;   // interior degree-p eigenvectors, NNp x NNp row-major (U)
-    const T* UKt;  // U^T
-    const T* UT;   // degree p-1 eigenvectors of (T^, M^)
-    const T* UTt;
-    const T* Mi;   // M^^{-1}, NMp x NMp
-    const double* lamK;  // nN eigenvalues
-    const double* lamT;  // nM eigenvalues
-    int nN, nM, NNp, NMp;
+    const T* F[2];         // forward transforms U^T: [0] interior degree p, [1] degree p-1
+    const T* V[2];         // inverse transforms U
+    const T* Mi;           // M^^{-1}
+    const double* lam[2];  // eigenvalues, [even modes | odd modes]
+    int nN, nM;
+    int nt;                // 16-wide tiles per half direction (of nM, for every table)
 };
+// How a dense n x n matrix becomes fragments: the columns of U transposed or
+// as they are, or a symmetric matrix that commutes with the reversal.
+enum class FdPack { forward, inverse, symmetric };
+template <typename T>
+void fd_pack(const std::vector<double>& A, int n, int nt, FdPack kind, std::vector<T>& out);
+int fd_half_tiles(int n);  // 16-wide tiles per half direction
 
 // A set of pointers to the four blocks of one (batched) vector.
 struct Fields {
@@ -168,10 +173,8 @@ hipError_t fd_init_attributes();
 // dot (FP64, the velocity blocks or the pressure block alone; may be null):
 // the last launch also writes partial sums of (final output) . dot->with to
 // dot->part[r * fd_dot_count(c, vel) + i] -- velocity: one per (field,
-// i3-plane), i = f nM + k, and with FD_PLAN_SPLIT one per (field, plane, row
-// block b), i = f nM + k + 3 nM b (slots no workgroup reaches -- planes or
-// row blocks a field lacks -- are never written: kept zero by the caller);
-// pressure: one per workgroup of its mode-3 launch.
+// i3-plane), i = f nM + k (slots of planes a field lacks are never written:
+// kept zero by the caller); pressure: one per workgroup of its mode-3 launch.
 // comb (FP64, may be null): the input is ca in + cb comb->b + cc comb->c,
 // formed where the first launch reads it (as k_axpbypcz would).
 struct FdDot {
@@ -188,17 +191,21 @@ hipError_t launch_P0(hp_ctx* c, const Fields& in, const Fields& out, bool vel, b
 long long fd_dot_count(const hp_ctx* c, bool vel);
 // the largest fd_dot_count over the plans (the partial buffers' size)
 long long fd_dot_capacity(const hp_ctx* c, bool vel);
-// fast-diagonalisation plans: bit 0 = one MFMA tile per wave (wide kernels),
-// bit 1 = stage the 1D matrices in LDS, bit 2 = 2x2 tile blocks per wave;
-// FD_PLAN_GEMM = the mode products as batched GEMMs over HBM (any direction
-// length; the only plan for directions longer than 128); FD_PLAN_SPLIT = one
-// 16-row block of a plane per 4-wave workgroup and 16 z rows per workgroup
-// (several times the workgroups of plans 0-7, for small meshes).  Whether plan
-// `plan` fits the LDS for `precision`, and the plan launch_P0 uses (forced,
-// option, tuned, default).
-constexpr int FD_PLAN_GEMM = 8;
-constexpr int FD_PLAN_SPLIT = 9;
+// Fast-diagonalisation plans: FD_PLAN_PLANE = modes 1 and 2 of a plane in one
+// workgroup's LDS (directions up to 128), mode 3 on 32 columns per workgroup;
+// FD_PLAN_SMALL = the same with 16 columns (twice the workgroups, for small
+// meshes); FD_PLAN_PASSES and FD_PLAN_LINES = one direction per pass, up to
+// 128 and at any length (the only plan beyond; the tuner takes the former).
+// The plane plans agree with each other bit for bit, and so do the two
+// others; between them the folds are rounded in another order.  Whether plan
+// `plan` exists for this mesh and `precision`, and the plan launch_P0 uses
+// (forced, option, tuned, default).
+constexpr int FD_PLAN_PASSES = 0;
+constexpr int FD_PLAN_PLANE = 1;
+constexpr int FD_PLAN_LINES = 8;
+constexpr int FD_PLAN_SMALL = 9;
 constexpr int FD_PLAN_LAST = 9;
+constexpr bool fd_plan_lines(int plan) { return plan == FD_PLAN_PASSES || plan == FD_PLAN_LINES; }
 bool fd_plan_valid(const hp_ctx* c, int precision, int plan);
 int fd_plan_in_use(const hp_ctx* c, int precision);
 

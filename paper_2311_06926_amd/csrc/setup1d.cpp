@@ -230,6 +230,73 @@ void generalized_eig(const std::vector<double>& K, const std::vector<double>& M,
             for (int k = i + 1; k < n; ++k) v -= L[k * n + i] * U[k * n + col];
             U[i * n + col] = v / L[i * n + i];
         }
+    // Rayleigh quotients and M-normalisation in extended precision: the error
+    // of a quotient is quadratic in the eigenvector's, so the small eigenvalues
+    // (which carry A^{-1}) lose nothing to the size of the large ones
+    for (int col = 0; col < n; ++col) {
+        long double uku = 0.0L, umu = 0.0L;
+        for (int i = 0; i < n; ++i) {
+            long double ku = 0.0L, mu = 0.0L;
+            for (int j = 0; j < n; ++j) {
+                ku += (long double)K[i * n + j] * U[j * n + col];
+                mu += (long double)M[i * n + j] * U[j * n + col];
+            }
+            uku += ku * U[i * n + col];
+            umu += mu * U[i * n + col];
+        }
+        lam[col] = (double)(uku / umu);
+        const double s = (double)(1.0L / std::sqrt(umu));
+        for (int i = 0; i < n; ++i) U[i * n + col] *= s;
+    }
+}
+
+// The same for matrices that commute with the reversal i -> n-1-i (uniform
+// mesh): the eigenvectors are even or odd, computed in the two subspaces (the
+// symmetric vectors (e_i + e_{n-1-i}) / sqrt 2 and, for odd n, the middle one;
+// the antisymmetric (e_i - e_{n-1-i}) / sqrt 2), so that they are so exactly.
+// Columns and eigenvalues: the ceil(n/2) even ones, then the floor(n/2) odd
+// ones, each group ascending.
+static void parity_eig(const std::vector<double>& K, const std::vector<double>& M, int n,
+                       std::vector<double>& lam, std::vector<double>& U) {
+    const int ho = n / 2;
+    lam.assign(n, 0.0);
+    U.assign((size_t)n * n, 0.0);
+    for (int par = 0; par < 2; ++par) {
+        const int h = par ? ho : n - ho, m0 = par ? n - ho : 0;
+        const double sg = par ? -1.0 : 1.0;
+        if (h == 0) continue;
+        auto reduced = [&](const std::vector<double>& A) {
+            std::vector<double> R((size_t)h * h);
+            auto at = [&](int i, int j) { return A[(size_t)i * n + j]; };
+            for (int i = 0; i < h; ++i)
+                for (int j = 0; j < h; ++j) {
+                    const int ri = n - 1 - i, rj = n - 1 - j;
+                    double v = 0.5 * (at(i, j) + at(ri, rj) + sg * (at(i, rj) + at(ri, j)));
+                    if (i >= ho && j >= ho) v = at(i, j);
+                    else if (i >= ho || j >= ho) v *= std::sqrt(0.5);
+                    R[(size_t)i * h + j] = v;
+                }
+            for (int i = 0; i < h; ++i)
+                for (int j = i + 1; j < h; ++j)
+                    R[(size_t)i * h + j] = R[(size_t)j * h + i] =
+                        0.5 * (R[(size_t)i * h + j] + R[(size_t)j * h + i]);
+            return R;
+        };
+        std::vector<double> l, u;
+        generalized_eig(reduced(K), reduced(M), h, l, u);
+        for (int m = 0; m < h; ++m) {
+            lam[m0 + m] = l[m];
+            for (int i = 0; i < h; ++i) {
+                const double v = u[(size_t)i * h + m];
+                if (i >= ho) {
+                    U[(size_t)i * n + m0 + m] = v;
+                } else {
+                    U[(size_t)i * n + m0 + m] = v * std::sqrt(0.5);
+                    U[(size_t)(n - 1 - i) * n + m0 + m] = sg * v * std::sqrt(0.5);
+                }
+            }
+        }
+    }
 }
 
 void inverse_spd(const std::vector<double>& M, int n, std::vector<double>& Minv) {
@@ -344,8 +411,8 @@ Tables1D build_tables(int E, int p, double c_pen) {
     T.int_M = intM;
     T.lid3.resize(nm);
     for (int i = 0; i < nm; ++i) T.lid3[i] = T.alpha * M1[i] - 0.5 * dM1[i];
-    generalized_eig(T.K_int, T.M_int, nN, T.lamK, T.UK);
-    generalized_eig(T.Tc, T.Mc, nm, T.lamT, T.UT);
+    parity_eig(T.K_int, T.M_int, nN, T.lamK, T.UK);
+    parity_eig(T.Tc, T.Mc, nm, T.lamT, T.UT);
     inverse_spd(T.Mc, nm, T.Mcinv);
     T.tp = tp;
     T.tm = tm;

@@ -12,7 +12,8 @@ struct Tables1D {
     std::vector<double> M_int, K_int;
     // degree p-1 (unit-integral M-spline) mass and the Nitsche-augmented T^ (nM x nM)
     std::vector<double> Mc, Tc, Mcinv;
-    // generalised eigenpairs: K_int U = M_int U diag(lamK), Tc U = Mc U diag(lamT)
+    // generalised eigenpairs: K_int U = M_int U diag(lamK), Tc U = Mc U diag(lamT);
+    // the even eigenvectors first, then the odd ones
     std::vector<double> lamK, UK, lamT, UT;
     // lid right-hand side pieces: int N_i (interior), int M_i, alpha M_i(1) - M_i'(1)/2
     std::vector<double> int_N, int_M, lid3;
