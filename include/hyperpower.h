@@ -234,14 +234,14 @@ hp_status hp_apply_K(hp_ctx* ctx, const double* x, double* y, int nrhs);
 
 /* y = K x by the quadrature-based, matrix-free route of Sec. 5.3: the
  * velocity gradients and the pressure are evaluated at the p+1 Gauss-Legendre
- * points per element and direction by global sum factorisation, the flux of
+ * points per element and direction by sum factorisation, the flux of
  * the weak form (Sec. 3.1; symmetric Nitsche face terms of Sec. 3.3 at the
  * face Gauss points) is formed at every point and integrated back.  Exact
  * quadrature: the same matrix as hp_apply_K, up to rounding.  x and y are
  * device arrays of nrhs vectors (stride N, layout of hp_apply_K), y must not
- * alias x.  The first call allocates the point tables and a scratch of
- * 7 (E(p+1)+2) n_M^2 + 10 (E(p+1)+2)^2 n_M + 10 (E(p+1)+2)^3 doubles
- * (one right-hand side at a time); HP_ENOMEM if that fails. */
+ * alias x.  The first call allocates the point tables and a scratch for the
+ * partial sums of up to 8 right-hand sides, each a few times N doubles;
+ * HP_ENOMEM if that fails. */
 hp_status hp_apply_K_quad(hp_ctx* ctx, const double* x, double* y, int nrhs);
 
 /* y = A u (velocity only, stride n_V; Sec. 3.3). */

@@ -68,26 +68,18 @@ struct OpTuned {
     OpShape shape;
 };
 
-// Banded table of the quadrature-based operator: row r holds
-// A[r][start[r] .. start[r] + w) of a rows x cols matrix.
-struct QBand {
-    const int* start;
-    const double* val;
-    int rows, cols, w;
-};
-
-// Device state of the quadrature-based forward operator (quad.hip): basis
-// tables at the points of one direction ([0] degree p-1, [1] interior degree
-// p; V values, D derivatives, VT/DT their transposes), the point weights and
-// the scratch of one right-hand side.
+// Device state of the quadrature-based forward operator (quad.hip): the point
+// tables of one direction with the point weights, the tiling and the scratch
+// of the tiles' partial sums.
 struct QuadOp {
     bool ready = false;
     int nq = 0;
+    int ex = 0, ey = 0, L = 0;         // elements per tile, element layers per chunk
+    int nt1 = 0, nt2 = 0, nch = 0;     // tiles and chunks
+    long long block_doubles = 0;       // partial sums of one tile and chunk
     double* tables = nullptr;
-    int* index = nullptr;
     double* scratch = nullptr;
     size_t scratch_doubles = 0;
-    QBand V[2]{}, D[2]{}, VT[2]{}, DT[2]{};
     const double* wq = nullptr;
 };
 
@@ -152,7 +144,7 @@ hipError_t ops_init_attributes();
 // Builds the point tables and allocates the scratch (once per context).
 hipError_t quad_setup(hp_ctx* c, QuadOp* q);
 void quad_free(QuadOp* q);
-// out = K in by global sum factorisation at the Gauss points (the same
+// out = K in by sum factorisation at the Gauss points (the same
 // matrix as OP_K of launch_operator, up to rounding); out must not alias in.
 hipError_t launch_quad_K(hp_ctx* c, const QuadOp* q, const Fields& in, const Fields& out,
                          int nrhs);
