@@ -391,9 +391,60 @@ hipError_t with_q_settings(hp_ctx* c, hipStream_t s, F fn) {
     return e;
 }
 
+// P_0, and P_1 of eq. Pcq1, with the two blocks in common launches.  At k = 1
+// they run in step: each of the q - 1 updates needs P_{V,0}^{-1} of the V
+// block's residual and of the Q block's 2 nu D' s, then the pressure chains of
+// A y and of B', and at the end P_0 of all four fields.  Against one stream
+// per block this is about half the launches and no fork and join (four event
+// calls, about 20 us of host time): a MINRES solve at 32^3, degree 3, 3.76 ->
+// 3.20 ms, the quadrature one at 16^3, degree 4, 4.08 -> 3.73.  Where the
+// kernels fill the chip the two are equal (61^3: 107 us either way).
+hipError_t apply_Pk_joint(hp_ctx* c, int q, int k, const double* x, double* y, int nrhs,
+                          const PkDot* pd) {
+    Extra* ex = extra_of(c);
+    const int prec = c->opts.precision;
+    const FdDot vdot = pd ? FdDot{pd->with, pd->vpart} : FdDot{};
+    const FdDot qdot = pd ? FdDot{pd->with, pd->qpart} : FdDot{};
+    const FdDot *vd = pd ? &vdot : nullptr, *qd = pd ? &qdot : nullptr;
+    const Fields fx = full_fields(c, x), fy = full_fields(c, y);
+    if (k == 0) {
+        const P0Set all{fx, fy, c->ws, false, false};
+        return launch_P0_sets(c, &all, 1, true, true, prec, nrhs, vd, qd);
+    }
+    const long long nV = c->nV, R = c->opts.max_rhs;
+    const Fields xv = vel_of_full(c, x), yv = vel_of_full(c, y), xq = pres_of_full(c, x);
+    const Fields res = vel_fields(c, ex->hv, nV);                 // V block: x - A y
+    const Fields b1 = vel_fields(c, ex->hv + nV * R, nV);         // Q block: 2 nu D' s
+    const Fields b2 = vel_fields(c, ex->hv + 2 * nV * R, nV);     // P_{V,0}^{-1} b1
+    const Fields sa = hq_slot(c, 1, 0), sb = hq_slot(c, 1, 1), t = hq_slot(c, 1, 2);
+    const Fields* s = &xq;  // s_1 = x
+    hipError_t e;
+    for (int i = 1; i < q; ++i) {
+        if ((e = launch_operator(c, OP_DT, *s, b1, q0_factor(c), 0.0, nullptr, nrhs)) != hipSuccess)
+            return e;
+        const P0Set vel[2] = {{i == 1 ? xv : res, yv, c->ws, i > 1, false},
+                              {b1, b2, ex->ws2, false, false}};
+        if ((e = launch_P0_sets(c, vel, 2, true, false, prec, nrhs)) != hipSuccess) return e;
+        if ((e = launch_residual_and_Bt(c, yv, res, xv, b2, t, nrhs)) != hipSuccess) return e;
+        if (i == q - 1) break;
+        const Fields* sn = (s == &sa) ? &sb : &sa;
+        if ((e = pres_axpbypcz(c, 1.0, xq, 1.0, *s, -1.0, t, *sn, nrhs)) != hipSuccess) return e;
+        s = sn;
+    }
+    // y_V += P_{V,0}^{-1} (x - A y), y_Q = P_{Q,0}^{-1} (x + s - t)
+    Fields in = res;
+    in.f[3] = xq.f[3];
+    in.stride[3] = xq.stride[3];
+    const FdComb comb{*s, t, 1.0, 1.0, -1.0};
+    const P0Set all{in, fy, c->ws, true, false};
+    return launch_P0_sets(c, &all, 1, true, true, prec, nrhs, vd, qd, &comb);
+}
+
 hipError_t apply_Pk(hp_ctx* c, int q, int k, const double* x, double* y, int nrhs,
                     const PkDot* pd = nullptr) {
     Extra* ex = extra_of(c);
+    if (ex->side && (k == 0 || (k == 1 && c->opts.schur_variant == HP_SCHUR_PCQ1)))
+        return apply_Pk_joint(c, q, k, x, y, nrhs, pd);
     if (!ex->side) {
         hipError_t e = pk_v_block(c, q, k, x, y, nrhs, pd);
         return e != hipSuccess ? e : pk_q_block(c, q, k, x, y, nrhs, pd);

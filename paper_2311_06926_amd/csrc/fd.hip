@@ -204,27 +204,37 @@ __device__ __forceinline__ double wg_sum(double s, double* red) {
     return t;
 }
 
+// One field of one set of right-hand sides; a launch takes one or two sets of
+// nr each (P_k: the V block's residual beside the Q block's B P_{Q,0}^{-1} s).
+// All that a workgroup reads of it is one cache line of the kernel arguments
+// (spread over arrays per member, P_0 at 32^3 took 20.1 us instead of 19.7).
+struct alignas(64) FieldIO {
+    const void* in;
+    void* out;
+    long long sin, sout;  // per-rhs strides
+    const double* dw;     // the dot's other vector (dpart set), rhs stride sout
+    int dims[3];
+    int add;              // the result is added to the output
+};
+
 // ---- modes 1 and 2 of one i3-plane -----------------------------------------------------
 struct PlaneArgs {
-    const void* in[4];
-    void* out[4];
-    long long sin[4], sout[4];  // per-rhs strides
-    int dims[4][3];
+    int nr;
     int fields_lo, nf;
     int inverse;                // velocity: 0 forward (fold, F), 1 inverse (V, unfold)
-    int accumulate;             // inverse: y += result
+    int comb;                   // the pressure's input is a combination (below)
+    FieldIO io[2][4];
     // FP64 output only: partial sums of (stored output) . dw per (field,
     // plane) to dpart[r * dp_stride + f * dp_planes + k] (dpart null: none)
-    const double* dw[4];        // same layout and rhs stride as out
     double* dpart;
     long long dp_stride;
     int dp_planes;
-    // FP64 input only: for a field with inb[f] set, the input is
-    // ca in + cb inb + cc inc (the same layout as in, rhs strides sinb, sinc),
-    // formed in the operation order of the vector kernel k_axpbypcz
-    const double* inb[4];
-    const double* inc[4];
-    long long sinb[4], sinc[4];
+    // FP64 input only, comb: the pressure's input is ca in + cb inb + cc inc
+    // (the same layout as in, rhs strides sinb, sinc), formed in the operation
+    // order of the vector kernel k_axpbypcz
+    const double* inb;
+    const double* inc;
+    long long sinb, sinc;
     double ca, cb, cc;
 };
 
@@ -265,11 +275,12 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_plane(PlaneArgs a,
     constexpr int RING = 4, NF = NB * NT * NT;
     extern __shared__ unsigned char smem_raw[];
     T* S = reinterpret_cast<T*>(smem_raw);
-    const int f = a.fields_lo + (int)(blockIdx.y % a.nf);
-    const int r = (int)(blockIdx.y / a.nf);
+    const int f = a.fields_lo + (int)blockIdx.y;
+    const int set = (int)blockIdx.z >= a.nr, r = (int)blockIdx.z - set * a.nr;
+    const FieldIO& io = a.io[set][f];
     const int k = blockIdx.x;
-    const int n1 = a.dims[f][0], n2 = a.dims[f][1];
-    if (k >= a.dims[f][2]) return;
+    const int n1 = io.dims[0], n2 = io.dims[1];
+    if (k >= io.dims[2]) return;
     const bool pres = f == 3;
     const bool fold = !a.inverse, unfold = a.inverse || pres;
     const Dir<T> d1 = dir_of(t, f, 0, a.inverse), d2 = dir_of(t, f, 1, a.inverse);
@@ -293,7 +304,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_plane(PlaneArgs a,
             if (w < NF) fr[w] = frag(tr, w, lane);
     }
     const long long kofs = (long long)k * n1 * n2;
-    const TI* x = reinterpret_cast<const TI*>(a.in[f]) + (long long)r * a.sin[f] + kofs;
+    const TI* x = reinterpret_cast<const TI*>(io.in) + (long long)r * io.sin + kofs;
     // a thread's groups (i, j): i, j of the first, advanced by NTH groups
     const int ng = he1 * he2, dj = NTH / he1, di = NTH - dj * he1;
     const int j00 = (int)threadIdx.x / he1, i00 = (int)threadIdx.x - j00 * he1;
@@ -318,10 +329,10 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_plane(PlaneArgs a,
         const double* xc = nullptr;
         bool comb = false;
         if constexpr (std::is_same<TI, double>::value) {
-            if (a.inb[f]) {
+            if (f == 3 && a.comb) {
                 comb = true;
-                if (a.cb != 0.0) xb = a.inb[f] + (long long)r * a.sinb[f] + kofs;
-                if (a.cc != 0.0) xc = a.inc[f] + (long long)r * a.sinc[f] + kofs;
+                if (a.cb != 0.0) xb = a.inb + (long long)r * a.sinb + kofs;
+                if (a.cc != 0.0) xc = a.inc + (long long)r * a.sinc + kofs;
             }
         }
         int i0 = i00, j0 = j00;
@@ -433,7 +444,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_plane(PlaneArgs a,
         for (int c = 0; c + 1 < NT; ++c) tile(c, std::integral_constant<int, 4>{});
         tail_steps(M::steps(ha - 16 * (NT - 1)), [&](auto st) { tile(NT - 1, st); });
     }
-    TO* y = reinterpret_cast<TO*>(a.out[f]) + (long long)r * a.sout[f] + kofs;
+    TO* y = reinterpret_cast<TO*>(io.out) + (long long)r * io.sout + kofs;
     if (unfold) __syncthreads();  // every wave is done with the input plane
     if (mine) {
         const int col = 16 * u1 + lr;
@@ -469,8 +480,9 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_plane(PlaneArgs a,
     if (!unfold) return;
     __syncthreads();
     // y = unfold(S), or y += unfold(S): the four mirror images of (i, j)
+    const bool add = io.add;
     const bool dot = std::is_same<TO, double>::value && a.dpart != nullptr;
-    const double* w = dot ? a.dw[f] + (long long)r * a.sout[f] + kofs : nullptr;
+    const double* w = dot ? io.dw + (long long)r * io.sout + kofs : nullptr;
     double sum = 0.0;
     int i0 = i00, j0 = j00;
     for (int base = threadIdx.x; base < ng; base += 2 * NTH) {
@@ -484,7 +496,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_plane(PlaneArgs a,
             gj[g] = on ? j0 : 0;
             next(i0, j0);
             mirror(gi[g], gj[g], o[g]);
-            if (a.accumulate)
+            if (add)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) yv[g][q] = y[o[g][q]];
             if (dot)
@@ -506,7 +518,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_plane(PlaneArgs a,
             for (int q = 0; q < 4; ++q)
                 if (on[q]) {
                     TO s = (TO)v[q];
-                    if (a.accumulate) s += yv[g][q];
+                    if (add) s += yv[g][q];
                     y[o[g][q]] = s;
                     if (dot) sum += (double)s * wv[g][q];
                 }
@@ -532,22 +544,18 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_plane(PlaneArgs a,
 // another's products; looking ahead to the next tile in registers instead
 // (one resident workgroup walking several tiles) spilled and was slower.
 struct LineArgs {
-    const void* in[4];
-    void* out[4];
-    long long sin[4], sout[4];
-    int dims[4][3];
+    int nr;
     int fields_lo, nf;
     int dir;          // 0: row kernel, 1: direction 2, 2: direction 3
     int inverse;      // one product: 0 forward (fold, F), 1 inverse (V, unfold)
     int fused;        // direction 3: the velocity's forward product, scaling and inverse product
-    int accumulate;   // bit f: field f is added to its output
     int ctiles, nbatch, ntiles;  // tiles per (field, rhs, plane), planes, tiles in all
     double two_nu;
     double omega;     // damping factor of P_0^{-1} (1: the plain base preconditioner)
     double pscale;    // the pressure's product is multiplied by this
-    // FP64 output, launches of one field only: partial sums of (stored
-    // output) . dw per tile to dpart[r * dp_stride + tile]
-    const double* dw;  // same layout and rhs stride as the output
+    FieldIO io[2][4];
+    // FP64 output: partial sums of (stored pressure) . dw per tile to
+    // dpart[r * dp_stride + tile]
     double* dpart;
     long long dp_stride;
 };
@@ -566,7 +574,7 @@ __device__ __forceinline__ int xcd_tile(int i, int total) {
 }
 
 struct Tile {
-    int c, b, f, r;  // column tile, plane, field, right-hand side
+    int c, b, f, set, r;  // column tile, plane, field, set, right-hand side
 };
 __device__ __forceinline__ Tile tile_of(const LineArgs& a, int id) {
     Tile w;
@@ -575,7 +583,9 @@ __device__ __forceinline__ Tile tile_of(const LineArgs& a, int id) {
     w.b = id % a.nbatch;
     id /= a.nbatch;
     w.f = a.fields_lo + id % a.nf;
-    w.r = id / a.nf;
+    id /= a.nf;
+    w.set = id >= a.nr;
+    w.r = id - w.set * a.nr;
     return w;
 }
 
@@ -693,11 +703,12 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_line(LineArgs a, FDTables<T> t
     auto tile_u = [&](int q) { return q == 0 ? wave : q * nw + turn; };
     const Tile w = tile_of(a, xcd_tile(blockIdx.x, a.ntiles));
     const int f = w.f, r = w.r;
-    const int n1 = a.dims[f][0];
-    const unsigned plane = (unsigned)n1 * a.dims[f][1];
+    const FieldIO& io = a.io[w.set][f];
+    const int n1 = io.dims[0];
+    const unsigned plane = (unsigned)n1 * io.dims[1];
     const unsigned ncol = d3 ? plane : (unsigned)n1;  // columns, and the direction's stride
     const unsigned c0 = (unsigned)w.c * W;
-    if (c0 >= ncol || (!d3 && w.b >= a.dims[f][2])) return;
+    if (c0 >= ncol || (!d3 && w.b >= io.dims[2])) return;
     const long long ofs = (d3 ? 0 : (long long)w.b * plane) + c0;
     const bool pres = f == 3, second = a.fused && !pres;
     const bool fold = !a.inverse, unfold = a.inverse || a.fused || pres;
@@ -712,7 +723,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_line(LineArgs a, FDTables<T> t
     hp.prime(d.tab);
     {
         // the pairs (k, n-1-k) (or (k, he + k)), k = kb + sk + g ks
-        const TI* x = reinterpret_cast<const TI*>(a.in[f]) + (long long)r * a.sin[f] + ofs;
+        const TI* x = reinterpret_cast<const TI*>(io.in) + (long long)r * io.sin + ofs;
         const bool in = c0 + sc < ncol;
         const uint32_t o0 = (uint32_t)sizeof(TI) * (sk * ncol + sc);
         const uint32_t o1 = (uint32_t)sizeof(TI) * ((ks - 1 - sk) * ncol + sc);
@@ -807,10 +818,10 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_line(LineArgs a, FDTables<T> t
         __syncthreads();
         product(tab2);
     }
-    TO* y = reinterpret_cast<TO*>(a.out[f]) + (long long)r * a.sout[f] + ofs;
-    const bool add = (a.accumulate >> f) & 1;
-    const bool dot = std::is_same<TO, double>::value && a.dpart != nullptr;
-    const double* dw = dot ? a.dw + (long long)r * a.sout[f] + ofs : nullptr;
+    TO* y = reinterpret_cast<TO*>(io.out) + (long long)r * io.sout + ofs;
+    const bool add = io.add;
+    const bool dot = std::is_same<TO, double>::value && pres && a.dpart != nullptr;
+    const double* dw = dot ? io.dw + (long long)r * io.sout + ofs : nullptr;
     const double ps = pres ? a.pscale : 1.0;
     double sum = 0.0;
 #pragma unroll
@@ -892,7 +903,8 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_row(LineArgs a, FDTables<T> t)
     auto tile_u = [&](int q) { return q == 0 ? wave : q * nw + turn; };
     const Tile w = tile_of(a, xcd_tile(blockIdx.x, a.ntiles));
     const int f = w.f;
-    const long long left = (long long)a.dims[f][1] * a.dims[f][2] - (long long)w.c * W;
+    const FieldIO& io = a.io[w.set][f];
+    const long long left = (long long)io.dims[1] * io.dims[2] - (long long)w.c * W;
     if (left <= 0) return;
     const int nl = (int)min((long long)W, left);
     const bool fold = !a.inverse, unfold = a.inverse || f == 3;
@@ -908,7 +920,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_row(LineArgs a, FDTables<T> t)
     {
         // entries k and n-1-k (or he + k) of line l; a thread's (l, k) advance
         // by nth entries of the 16 CT x K16 tile
-        const TI* x = reinterpret_cast<const TI*>(a.in[f]) + (long long)w.r * a.sin[f] +
+        const TI* x = reinterpret_cast<const TI*>(io.in) + (long long)w.r * io.sin +
                       (long long)w.c * W * n;
         const int dl = nth / K16, dk = nth - dl * K16;
         int l0 = threadIdx.x / K16, k0 = threadIdx.x - l0 * K16;
@@ -953,9 +965,9 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_row(LineArgs a, FDTables<T> t)
         }
     }
     __syncthreads();
-    TO* y = reinterpret_cast<TO*>(a.out[f]) + (long long)w.r * a.sout[f] +
+    TO* y = reinterpret_cast<TO*>(io.out) + (long long)w.r * io.sout +
             (long long)w.c * W * n;
-    const bool add = (a.accumulate >> f) & 1;
+    const bool add = io.add;
 #pragma unroll
     for (int q = 0; q < U; ++q) {
         const int u = tile_u(q);
@@ -1059,9 +1071,9 @@ size_t plane_lds(int n1, int n2) {
 }
 
 template <typename T, typename TI, typename TO, bool SPLIT>
-hipError_t launch_plane(hipStream_t st, const PlaneArgs& a, const FDTables<T>& t, int nrhs) {
+hipError_t launch_plane(hipStream_t st, const PlaneArgs& a, const FDTables<T>& t, int nsets) {
     const int nt = t.nt;
-    const dim3 g(t.nM, a.nf * nrhs), b(nt <= 2 ? 256 * nt : 128 * nt);
+    const dim3 g(t.nM, a.nf, a.nr * nsets), b(nt <= 2 ? 256 * nt : 128 * nt);
     size_t lds = plane_lds<T>(t.nM, t.nM);
     if (t.nN < t.nM) {
         lds = std::max(lds, plane_lds<T>(t.nN, t.nM));
@@ -1080,7 +1092,7 @@ hipError_t launch_plane(hipStream_t st, const PlaneArgs& a, const FDTables<T>& t
 
 // LINE: the line kernel (directions 2 and 3), else the row kernel (direction 1).
 template <typename T, typename TI, typename TO, bool SPLIT, bool LINE>
-hipError_t launch_lines(hipStream_t st, const LineArgs& arg, const FDTables<T>& t, int ct, int nrhs) {
+hipError_t launch_lines(hipStream_t st, const LineArgs& arg, const FDTables<T>& t, int ct, int nsets) {
     const int nM = t.nM, nt = t.nt;
     const size_t lds = std::max<size_t>(LINE ? line_lds<T>(nM, ct) : row_lds<T>(nM, ct), 256);
     if (lds > FD_LDS || nt > 48) return hipErrorInvalidConfiguration;
@@ -1089,7 +1101,7 @@ hipError_t launch_lines(hipStream_t st, const LineArgs& arg, const FDTables<T>& 
     LineArgs a = arg;
     a.ctiles = (int)((cols + 16 * ct - 1) / (16 * ct));
     a.nbatch = planes ? nM : 1;
-    const long long tiles = (long long)a.ctiles * a.nbatch * a.nf * nrhs;
+    const long long tiles = (long long)a.ctiles * a.nbatch * a.nf * a.nr * nsets;
     if (tiles > INT_MAX) return hipErrorInvalidConfiguration;
     a.ntiles = (int)tiles;
     const dim3 g((unsigned)tiles);
@@ -1112,19 +1124,18 @@ hipError_t launch_lines(hipStream_t st, const LineArgs& arg, const FDTables<T>& 
     return hipGetLastError();
 }
 
-// P_0^{-1} of the fields [vel ? 0 : 3, pres ? 4 : 3): modes 1 and 2 (one
-// plane launch, or two passes with FD_PLAN_PASSES / LINES), mode 3 with the scaling and
-// the inverse mode 3, and the velocity's inverse modes 2 and 1.  In FP64 the
-// four fields share the mode-3 launch; otherwise the pressure's writes its
-// FP64 output from a launch of its own.  Intermediates of precision T
-// ping-pong between the two scratch vectors.
+// P_0^{-1} of the fields [vel ? 0 : 3, pres ? 4 : 3) of one or two sets: modes
+// 1 and 2 (one plane launch, or two passes with FD_PLAN_PASSES / LINES), mode
+// 3 with the scaling and the inverse mode 3, and the velocity's inverse modes
+// 2 and 1.  In FP64 the four fields share the mode-3 launch; otherwise the
+// pressure's writes its FP64 output from a launch of its own.  Intermediates
+// of precision T ping-pong between the two scratch vectors of each set's
+// workspace.
 template <typename T, bool SPLIT = false>
-hipError_t run_P0(hp_ctx* c, const FDTables<T>& t, const Fields& in, const Fields& out, bool vel,
-                  bool pres, bool accumulate, int plan, int nrhs, const FdDot* dot,
+hipError_t run_P0(hp_ctx* c, const FDTables<T>& t, const P0Set* sets, int nsets, bool vel,
+                  bool pres, int plan, int nrhs, const FdDot* vdot, const FdDot* qdot,
                   const FdComb* comb) {
     const long long N = c->N;
-    T* tmp1 = reinterpret_cast<T*>(c->ws + ops_ws_stride(c) * (long long)c->opts.max_rhs);
-    T* tmp2 = tmp1 + N * (long long)c->opts.max_rhs;
     const int lo = vel ? 0 : 3, hi = pres ? 4 : 3;
     if (lo >= hi) return hipSuccess;
     const bool lines = !SPLIT && fd_plan_lines(plan);
@@ -1133,122 +1144,120 @@ hipError_t run_P0(hp_ctx* c, const FDTables<T>& t, const Fields& in, const Field
     hipError_t e;
     LineArgs la{};
     PlaneArgs pa{};
-    for (int f = 0; f < 4; ++f) {
-        for (int d = 0; d < 3; ++d) la.dims[f][d] = pa.dims[f][d] = (int)c->dims[f][d];
-        la.in[f] = pa.in[f] = in.f[f];
-        la.sin[f] = pa.sin[f] = in.stride[f];
-        la.out[f] = pa.out[f] = tmp1 + c->off[f];
-        la.sout[f] = pa.sout[f] = N;
+    T* tmp[2][2];
+    for (int i = 0; i < nsets; ++i) {
+        tmp[i][0] = reinterpret_cast<T*>(sets[i].ws + ops_ws_stride(c) * (long long)c->opts.max_rhs);
+        tmp[i][1] = tmp[i][0] + N * (long long)c->opts.max_rhs;
     }
+    la.nr = pa.nr = nrhs;
     la.fields_lo = pa.fields_lo = lo;
     la.nf = pa.nf = hi - lo;
     la.two_nu = 2.0 * c->nu;
     la.omega = c->opts.p0_scale;
     la.pscale = 1.0;
-    auto between = [&](T* src, T* dst) {  // both buffers are intermediates
-        for (int f = 0; f < 4; ++f) {
-            la.in[f] = src + c->off[f];
-            la.sin[f] = N;
-            la.out[f] = dst + c->off[f];
-            la.sout[f] = N;
-        }
+    // the sets' vectors: scratch 0 or 1, or the caller's (-1)
+    auto bind = [&](FieldIO (&io)[2][4], int src, int dst) {
+        for (int i = 0; i < nsets; ++i)
+            for (int f = 0; f < 4; ++f) {
+                const Fields &in = sets[i].in, &out = sets[i].out;
+                FieldIO& w = io[i][f];
+                w.in = src < 0 ? (const void*)in.f[f] : tmp[i][src] + c->off[f];
+                w.sin = src < 0 ? in.stride[f] : N;
+                w.out = dst < 0 ? (void*)out.f[f] : tmp[i][dst] + c->off[f];
+                w.sout = dst < 0 ? out.stride[f] : N;
+                w.dw = nullptr;
+                for (int d = 0; d < 3; ++d) w.dims[d] = (int)c->dims[f][d];
+                w.add = dst < 0 && sets[i].acc_vel;
+            }
     };
-    T *cur = tmp1, *nxt = tmp2;
+    int cur = 0;  // the scratch that holds the forward modes 1 and 2
     if (lines) {
-        if (comb)
-            for (int f = lo; f < hi; ++f) {
-                if (!comb->b.f[f]) continue;
-                // one field per call (the pressure): the operator workspace
-                // holds n_Q per right-hand side
-                const long long n = c->dims[f][0] * c->dims[f][1] * c->dims[f][2];
-                e = vec_axpbypcz(st, n, nrhs, comb->ca, in.f[f], in.stride[f], comb->cb,
-                                 comb->b.f[f], comb->b.stride[f], comb->cc, comb->c.f[f],
-                                 comb->c.stride[f], c->ws, ops_ws_stride(c));
-                if (e != hipSuccess) return e;
-                la.in[f] = c->ws;
-                la.sin[f] = ops_ws_stride(c);
-            }
-        if ((e = launch_lines<T, double, T, false, false>(st, la, t, ct, nrhs)) != hipSuccess) return e;
-        between(tmp1, tmp2);
+        bind(la.io, -1, 0);
+        if (comb && pres) {
+            // the operator workspace holds n_Q per right-hand side
+            const Fields &in = sets[0].in, &cb = comb->b, &cc = comb->c;
+            e = vec_axpbypcz(st, c->nQ, nrhs, comb->ca, in.f[3], in.stride[3], comb->cb, cb.f[3],
+                             cb.stride[3], comb->cc, cc.f[3], cc.stride[3], sets[0].ws,
+                             ops_ws_stride(c));
+            if (e != hipSuccess) return e;
+            la.io[0][3].in = sets[0].ws;
+            la.io[0][3].sin = ops_ws_stride(c);
+        }
+        if ((e = launch_lines<T, double, T, false, false>(st, la, t, ct, nsets)) != hipSuccess) return e;
+        bind(la.io, 0, 1);
         la.dir = 1;
-        if ((e = launch_lines<T, T, T, false, true>(st, la, t, ct, nrhs)) != hipSuccess) return e;
-        cur = tmp2;
-        nxt = tmp1;
+        if ((e = launch_lines<T, T, T, false, true>(st, la, t, ct, nsets)) != hipSuccess) return e;
+        cur = 1;
     } else {
+        bind(pa.io, -1, 0);
         if (comb) {
-            for (int f = lo; f < hi; ++f) {
-                pa.inb[f] = comb->b.f[f];
-                pa.inc[f] = comb->c.f[f];
-                pa.sinb[f] = comb->b.stride[f];
-                pa.sinc[f] = comb->c.stride[f];
-            }
+            pa.comb = 1;
+            pa.inb = comb->b.f[3];
+            pa.inc = comb->c.f[3];
+            pa.sinb = comb->b.stride[3];
+            pa.sinc = comb->c.stride[3];
             pa.ca = comb->ca;
             pa.cb = comb->cb;
             pa.cc = comb->cc;
         }
-        if ((e = launch_plane<T, double, T, SPLIT>(st, pa, t, nrhs)) != hipSuccess) return e;
+        if ((e = launch_plane<T, double, T, SPLIT>(st, pa, t, nsets)) != hipSuccess) return e;
     }
-    between(cur, nxt);
+    bind(la.io, cur, cur ^ 1);
     la.dir = 2;
     la.fused = 1;
     la.pscale = la.omega * la.two_nu;
     // the pressure's mode-3 step writes the final output; the velocity's
     // feeds the inverse modes 2 and 1
-    la.out[3] = out.f[3];
-    la.sout[3] = out.stride[3];
-    la.accumulate = accumulate ? (1 << 3) : 0;
+    for (int i = 0; i < nsets; ++i) {
+        FieldIO& w = la.io[i][3];
+        w.out = sets[i].out.f[3];
+        w.sout = sets[i].out.stride[3];
+        w.add = sets[i].acc_pres;
+    }
+    if (qdot) {
+        la.io[0][3].dw = qdot->with + c->off[3];
+        la.dpart = qdot->part;
+        la.dp_stride = fd_dot_count(c, false);
+    }
     if (vel && pres && std::is_same<T, double>::value) {
-        if ((e = launch_lines<T, T, double, SPLIT, true>(st, la, t, ct, nrhs)) != hipSuccess) return e;
+        if ((e = launch_lines<T, T, double, SPLIT, true>(st, la, t, ct, nsets)) != hipSuccess) return e;
     } else {
         if (vel) {
             la.fields_lo = 0;
             la.nf = 3;
-            if ((e = launch_lines<T, T, T, SPLIT, true>(st, la, t, ct, nrhs)) != hipSuccess) return e;
+            if ((e = launch_lines<T, T, T, SPLIT, true>(st, la, t, ct, nsets)) != hipSuccess) return e;
         }
         if (pres) {
             LineArgs lp = la;
             lp.fields_lo = 3;
             lp.nf = 1;
-            if (dot && !vel) {
-                lp.dw = dot->with + c->off[3];
-                lp.dpart = dot->part;
-                lp.dp_stride = fd_dot_count(c, false);
-            }
-            if ((e = launch_lines<T, T, double, SPLIT, true>(st, lp, t, ct, nrhs)) != hipSuccess) return e;
+            if ((e = launch_lines<T, T, double, SPLIT, true>(st, lp, t, ct, nsets)) != hipSuccess) return e;
         }
     }
     if (!vel) return hipSuccess;
-    la.fields_lo = 0;
-    la.nf = 3;
-    la.inverse = 1;
-    la.fused = 0;
-    la.accumulate = accumulate ? 7 : 0;
+    const Fields& out = sets[0].out;
     if (lines) {
-        LineArgs lm = la;
-        for (int f = 0; f < 3; ++f) {
-            lm.in[f] = nxt + c->off[f];
-            lm.out[f] = cur + c->off[f];
-        }
-        lm.dir = 1;
-        lm.accumulate = 0;
-        if ((e = launch_lines<T, T, T, false, true>(st, lm, t, ct, nrhs)) != hipSuccess) return e;
-        for (int f = 0; f < 3; ++f) {
-            la.in[f] = cur + c->off[f];
-            la.out[f] = out.f[f];
-            la.sout[f] = out.stride[f];
-        }
+        la.fields_lo = 0;
+        la.nf = 3;
+        la.inverse = 1;
+        la.fused = 0;
+        la.dpart = nullptr;
+        bind(la.io, cur ^ 1, cur);
+        la.dir = 1;
+        if ((e = launch_lines<T, T, T, false, true>(st, la, t, ct, nsets)) != hipSuccess) return e;
+        bind(la.io, cur, -1);
         la.dir = 0;
-        if ((e = launch_lines<T, T, double, false, false>(st, la, t, ct, nrhs)) != hipSuccess) return e;
-        if (dot) {
+        if ((e = launch_lines<T, T, double, false, false>(st, la, t, ct, nsets)) != hipSuccess) return e;
+        if (vdot) {
             DotArgs da{};
             for (int f = 0; f < 3; ++f) {
                 da.y[f] = out.f[f];
-                da.w[f] = dot->with + c->off[f];
+                da.w[f] = vdot->with + c->off[f];
                 da.stride[f] = out.stride[f];
                 da.plane[f] = c->dims[f][0] * c->dims[f][1];
                 da.planes[f] = (int)c->dims[f][2];
             }
-            da.part = dot->part;
+            da.part = vdot->part;
             da.dp_stride = fd_dot_count(c, true);
             da.nM = c->nM;
             hipLaunchKernelGGL(k_fd_dot_vel, dim3(c->nM, 3, nrhs), dim3(256), 0, st, da);
@@ -1256,23 +1265,17 @@ hipError_t run_P0(hp_ctx* c, const FDTables<T>& t, const Fields& in, const Field
         return hipGetLastError();
     }
     PlaneArgs pi{};
-    for (int f = 0; f < 3; ++f) {
-        for (int d = 0; d < 3; ++d) pi.dims[f][d] = (int)c->dims[f][d];
-        pi.in[f] = nxt + c->off[f];
-        pi.sin[f] = N;
-        pi.out[f] = out.f[f];
-        pi.sout[f] = out.stride[f];
-        if (dot) pi.dw[f] = dot->with + c->off[f];
-    }
+    bind(pi.io, cur ^ 1, -1);
+    pi.nr = nrhs;
     pi.nf = 3;
     pi.inverse = 1;
-    pi.accumulate = accumulate ? 1 : 0;
-    if (dot) {
-        pi.dpart = dot->part;
+    if (vdot) {
+        for (int f = 0; f < 3; ++f) pi.io[0][f].dw = vdot->with + c->off[f];
+        pi.dpart = vdot->part;
         pi.dp_stride = fd_dot_count(c, true);
         pi.dp_planes = c->nM;
     }
-    return launch_plane<T, T, double, SPLIT>(st, pi, t, nrhs);
+    return launch_plane<T, T, double, SPLIT>(st, pi, t, nsets);
 }
 
 // dynamic LDS up to the CU's 160 KiB for every instantiation
@@ -1389,17 +1392,27 @@ long long fd_dot_capacity(const hp_ctx* c, bool vel) {
     return vel ? 3 * nM : (nM * nM + 15) / 16;
 }
 
+hipError_t launch_P0_sets(hp_ctx* c, const P0Set* sets, int nsets, bool vel, bool pres,
+                          int precision, int nrhs, const FdDot* vdot, const FdDot* qdot,
+                          const FdComb* comb) {
+    if ((vdot || qdot) && (precision != HP_PREC_FP64 || nsets != 1)) return hipErrorInvalidValue;
+    if (nsets < 1 || nsets > 2 || (comb && nsets != 1)) return hipErrorInvalidValue;
+    const int plan = fd_plan_in_use(c, precision);
+    if (precision == HP_PREC_FP64)
+        return run_P0<double>(c, c->fd64, sets, nsets, vel, pres, plan, nrhs, vdot, qdot, comb);
+    // split BF16 takes FP32 products in the direction passes
+    if (precision == HP_PREC_BF16X3 && !fd_plan_lines(plan))
+        return run_P0<float, true>(c, c->fd32, sets, nsets, vel, pres, plan, nrhs, nullptr, nullptr, comb);
+    return run_P0<float>(c, c->fd32, sets, nsets, vel, pres, plan, nrhs, nullptr, nullptr, comb);
+}
+
 hipError_t launch_P0(hp_ctx* c, const Fields& in, const Fields& out, bool vel, bool pres,
                      bool accumulate, int precision, int nrhs, const FdDot* dot,
                      const FdComb* comb) {
-    if (dot && (precision != HP_PREC_FP64 || (vel && pres))) return hipErrorInvalidValue;
-    const int plan = fd_plan_in_use(c, precision);
-    if (precision == HP_PREC_FP64)
-        return run_P0<double>(c, c->fd64, in, out, vel, pres, accumulate, plan, nrhs, dot, comb);
-    // split BF16 takes FP32 products in the direction passes
-    if (precision == HP_PREC_BF16X3 && !fd_plan_lines(plan))
-        return run_P0<float, true>(c, c->fd32, in, out, vel, pres, accumulate, plan, nrhs, nullptr, comb);
-    return run_P0<float>(c, c->fd32, in, out, vel, pres, accumulate, plan, nrhs, nullptr, comb);
+    if (dot && vel && pres) return hipErrorInvalidValue;
+    const P0Set set{in, out, c->ws, accumulate, accumulate};
+    return launch_P0_sets(c, &set, 1, vel, pres, precision, nrhs, vel ? dot : nullptr,
+                          vel ? nullptr : dot, comb);
 }
 
 }  // namespace hp

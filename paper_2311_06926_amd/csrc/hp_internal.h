@@ -138,6 +138,12 @@ enum OpMode { OP_K = 0, OP_A = 1, OP_B = 2, OP_BT = 3, OP_MV = 4, OP_DT = 5 };
 hipError_t launch_operator(hp_ctx* c, OpMode mode, const Fields& in, const Fields& out,
                            double alpha, double beta, const Fields* src, int nrhs);
 
+// y = src - A u (velocity, operator OP_A with alpha = -1, beta = 1) and
+// t = B^T v, the two pressure chains in one launch where the shape allows
+// (w of the first in c->ws; u, v, y, t, src must not overlap).
+hipError_t launch_residual_and_Bt(hp_ctx* c, const Fields& u, const Fields& y, const Fields& src,
+                                  const Fields& v, const Fields& t, int nrhs);
+
 hipError_t ops_init_attributes();
 
 // ---- quadrature-based forward operator (quad.hip) ---------------------------
@@ -167,7 +173,7 @@ hipError_t fd_init_attributes();
 // dot->part[r * fd_dot_count(c, vel) + i] -- velocity: one per (field,
 // i3-plane), i = f nM + k (slots of planes a field lacks are never written:
 // kept zero by the caller); pressure: one per workgroup of its mode-3 launch.
-// comb (FP64, may be null): the input is ca in + cb comb->b + cc comb->c,
+// comb (may be null): the pressure's input is ca in + cb comb->b + cc comb->c,
 // formed where the first launch reads it (as k_axpbypcz would).
 struct FdDot {
     const double* with;  // full vector, same layout and rhs stride as the output's
@@ -180,6 +186,19 @@ struct FdComb {
 hipError_t launch_P0(hp_ctx* c, const Fields& in, const Fields& out, bool vel, bool pres,
                      bool accumulate, int precision, int nrhs, const FdDot* dot = nullptr,
                      const FdComb* comb = nullptr);
+// One or two sets of nrhs right-hand sides through the same launches (two: the
+// velocity blocks only, no dot, no comb), each with its vectors, the
+// workspace that holds its intermediates and whether the velocity and the
+// pressure are added to their outputs.  vdot, qdot: the velocity and the
+// pressure part of the dot.
+struct P0Set {
+    Fields in, out;
+    double* ws;
+    bool acc_vel, acc_pres;
+};
+hipError_t launch_P0_sets(hp_ctx* c, const P0Set* sets, int nsets, bool vel, bool pres,
+                          int precision, int nrhs, const FdDot* vdot = nullptr,
+                          const FdDot* qdot = nullptr, const FdComb* comb = nullptr);
 long long fd_dot_count(const hp_ctx* c, bool vel);
 // the largest fd_dot_count over the plans (the partial buffers' size)
 long long fd_dot_capacity(const hp_ctx* c, bool vel);

@@ -66,6 +66,31 @@ struct OpArgs {
     int kbase, klim;     // i3-planes [kbase, klim) of this launch (a slab)
 };
 
+// A second pressure chain in a launch of k_pres / k_pres_all: the workgroups
+// from a.nblocks on take its vectors and mode (nblocks of them, the same
+// shape; mode < 0: none).
+struct PresJob {
+    const double* u[3];
+    const double* p;
+    long long su, sp;
+    double* yp;
+    long long syp;
+    int mode;
+};
+// the workgroup's job; returns its index within the job
+__device__ __forceinline__ int pick_job(OpArgs& a, double*& yp, long long& syp, const PresJob& b) {
+    const int blk = (int)blockIdx.x;
+    if (blk < a.nblocks) return blk;
+    for (int i = 0; i < 3; ++i) a.u[i] = b.u[i];
+    a.p = b.p;
+    a.su = b.su;
+    a.sp = b.sp;
+    a.mode = b.mode;
+    yp = b.yp;
+    syp = b.syp;
+    return blk - a.nblocks;
+}
+
 // Workgroups are dealt round-robin to the 8 XCDs in launch order.  Renumber
 // them so that XCD x receives one contiguous range of logical block ids.
 __device__ __forceinline__ int xcd_block(int L, int total) {
@@ -147,14 +172,14 @@ constexpr int waves_for() {
 }
 
 template <int P, int PT1, int PT2>
-__global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves_for<P>()))) void k_pres(OpArgs a, double* yp, long long syp) {
+__global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves_for<P>()))) void k_pres(OpArgs a, double* yp, long long syp, PresJob job) {
     constexpr int PNT = PT1 * PT2;
     constexpr int W = P - 1;
     constexpr int SW = PT1 + 2 * W, SR = PT2 + 2 * W;
     constexpr int NS = (SR * SW + PNT - 1) / PNT;  // staging slots per thread
     __shared__ double gs[SR * SW], zs[SR * SW], pg[SR * PT1], pz[SR * PT1];
     const int nM = a.nM, nN = a.nN;
-    int id = xcd_block(blockIdx.x, a.nblocks);
+    int id = xcd_block(pick_job(a, yp, syp, job), a.nblocks);
     const int t1 = id % a.ntile1;
     id /= a.ntile1;
     const int t2 = id % a.ntile2;
@@ -332,7 +357,7 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
 // output as k_pres (bitwise-identical results), every mode k_pres serves.
 // KC = kchunk (2 or 4), degrees 2 and 3.
 template <int P, int KC>
-__global__ __launch_bounds__(NT) void k_pres_all(OpArgs a, double* yp, long long syp) {
+__global__ __launch_bounds__(NT) void k_pres_all(OpArgs a, double* yp, long long syp, PresJob job) {
     constexpr int W = P - 1;
     constexpr int SW = T1 + 2 * W, SR = T2 + 2 * W;
     constexpr int NS = (SR * SW + NT - 1) / NT;
@@ -343,7 +368,7 @@ __global__ __launch_bounds__(NT) void k_pres_all(OpArgs a, double* yp, long long
     double* pg = zs + NP * SR * SW;      // NP x SR x T1
     double* pz = pg + NP * SR * T1;
     const int nM = a.nM, nN = a.nN;
-    int id = xcd_block(blockIdx.x, a.nblocks);
+    int id = xcd_block(pick_job(a, yp, syp, job), a.nblocks);
     const int t1 = id % a.ntile1;
     id /= a.ntile1;
     const int t2 = id % a.ntile2;
@@ -1385,15 +1410,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 }
 
 template <int P>
-void launch_pres(dim3 grid, hipStream_t st, const OpArgs& a, double* yp, long long syp) {
-    hipLaunchKernelGGL((k_pres<P, T1, T2>), grid, dim3(NT), 0, st, a, yp, syp);
+void launch_pres(dim3 grid, hipStream_t st, const OpArgs& a, double* yp, long long syp,
+                 const PresJob& job) {
+    hipLaunchKernelGGL((k_pres<P, T1, T2>), grid, dim3(NT), 0, st, a, yp, syp, job);
 }
 // the pressure chain on 32 x 8 tiles: less halo per point (36 x 12 staged
 // values per 256 outputs against 20 x 12 per 128), larger workgroups
 constexpr int PW1 = 32, PW2 = 8;
 template <int P>
-void launch_pres_wide(dim3 grid, hipStream_t st, const OpArgs& a, double* yp, long long syp) {
-    hipLaunchKernelGGL((k_pres<P, PW1, PW2>), grid, dim3(PW1 * PW2), 0, st, a, yp, syp);
+void launch_pres_wide(dim3 grid, hipStream_t st, const OpArgs& a, double* yp, long long syp,
+                      const PresJob& job) {
+    hipLaunchKernelGGL((k_pres<P, PW1, PW2>), grid, dim3(PW1 * PW2), 0, st, a, yp, syp, job);
 }
 
 template <int P>
@@ -1422,7 +1449,7 @@ const FusedLaunch fused_launch[FUSED_PMAX + 1] = {nullptr, nullptr, launch_fused
                                                   launch_fused<3>, launch_fused<4>};
 
 // instantiations per degree 2..8 (index = degree)
-using PresLaunch = void (*)(dim3, hipStream_t, const OpArgs&, double*, long long);
+using PresLaunch = void (*)(dim3, hipStream_t, const OpArgs&, double*, long long, const PresJob&);
 using VelLaunch = void (*)(dim3, hipStream_t, const OpArgs&, const Fields&, const Fields&, double,
                            double);
 constexpr int PMAX = 8;
@@ -1453,9 +1480,10 @@ hipError_t vel_all_attr() {
                                (int)(sizeof(double) * vel_all_lds_doubles<P, KC>()));
 }
 template <int P, int KC>
-void launch_pres_all(dim3 grid, hipStream_t st, const OpArgs& a, double* yp, long long syp) {
+void launch_pres_all(dim3 grid, hipStream_t st, const OpArgs& a, double* yp, long long syp,
+                     const PresJob& job) {
     constexpr size_t shm = sizeof(double) * pres_all_lds_doubles<P, KC>();
-    hipLaunchKernelGGL((k_pres_all<P, KC>), grid, dim3(NT), shm, st, a, yp, syp);
+    hipLaunchKernelGGL((k_pres_all<P, KC>), grid, dim3(NT), shm, st, a, yp, syp, job);
 }
 template <int P, int KC>
 hipError_t pres_all_attr() {
@@ -1540,8 +1568,12 @@ OpShape op_shape(const hp_ctx* c, int nrhs) {
     return sh;
 }
 
-hipError_t launch_operator(hp_ctx* c, OpMode mode, const Fields& in, const Fields& out,
-                           double alpha, double beta, const Fields* src, int nrhs) {
+// bt_in, bt_out (modes OP_K and OP_A; may be null): also t = B^T v; false in
+// *merged if the shape in use has no common launch for it (nothing of it is done)
+static hipError_t run_operator(hp_ctx* c, OpMode mode, const Fields& in, const Fields& out,
+                               double alpha, double beta, const Fields* src, int nrhs,
+                               const Fields* bt_in, const Fields* bt_out, bool* merged) {
+    if (merged) *merged = false;
     if (c->p < 2 || c->p > PMAX || nrhs < 1) return hipErrorInvalidValue;
     OpArgs a{};
     a.bt = c->band;
@@ -1570,6 +1602,8 @@ hipError_t launch_operator(hp_ctx* c, OpMode mode, const Fields& in, const Field
     const long long syp = out.stride[3];
     const PresLaunch pall = sh.staged ? pres_all_launch(P, a.kchunk) : nullptr;
     const bool pwide = !pall && sh.pwide;
+    PresJob job{};
+    job.mode = -1;
     auto pres = [&](int lo, int hi) {
         a.kbase = lo;
         a.klim = hi;
@@ -1579,9 +1613,9 @@ hipError_t launch_operator(hp_ctx* c, OpMode mode, const Fields& in, const Field
             a.ntile2 = (nM + PW2 - 1) / PW2;
         }
         a.nblocks = a.ntile1 * a.ntile2 * a.nchunk * nrhs;
-        dim3 grid(a.nblocks);
+        dim3 grid(job.mode < 0 ? a.nblocks : 2 * a.nblocks);
         (pall ? pall : (pwide ? pres_wide_launch[P] : pres_launch[P]))(grid, c->stream, a, yp,
-                                                                       syp);
+                                                                       syp, job);
         a.ntile1 = (nM + T1 - 1) / T1;  // the velocity kernels' tiles
         a.ntile2 = (nM + T2 - 1) / T2;
     };
@@ -1620,6 +1654,14 @@ hipError_t launch_operator(hp_ctx* c, OpMode mode, const Fields& in, const Field
         // Cache; the pressure launch of a slab also produces w on the first
         // plane of the next slab, which D_3^T needs
         const int S = std::max(1, std::min(sh.slabs, nM));
+        if (bt_in && S == 1) {
+            for (int i = 0; i < 3; ++i) job.u[i] = bt_in->f[i];
+            job.su = bt_in->stride[0];
+            job.yp = bt_out->f[3];
+            job.syp = bt_out->stride[3];
+            job.mode = OP_BT;
+            *merged = true;
+        }
         for (int sl = 0; sl < S; ++sl) {
             const int lo = (int)((long long)nM * sl / S), hi = (int)((long long)nM * (sl + 1) / S);
             if (hi <= lo) continue;
@@ -1628,6 +1670,19 @@ hipError_t launch_operator(hp_ctx* c, OpMode mode, const Fields& in, const Field
         }
     }
     return hipGetLastError();
+}
+
+hipError_t launch_operator(hp_ctx* c, OpMode mode, const Fields& in, const Fields& out,
+                           double alpha, double beta, const Fields* src, int nrhs) {
+    return run_operator(c, mode, in, out, alpha, beta, src, nrhs, nullptr, nullptr, nullptr);
+}
+
+hipError_t launch_residual_and_Bt(hp_ctx* c, const Fields& u, const Fields& y, const Fields& src,
+                                  const Fields& v, const Fields& t, int nrhs) {
+    bool merged;
+    const hipError_t e = run_operator(c, OP_A, u, y, -1.0, 1.0, &src, nrhs, &v, &t, &merged);
+    if (e != hipSuccess || merged) return e;
+    return launch_operator(c, OP_BT, v, t, 1.0, 0.0, nullptr, nrhs);
 }
 
 }  // namespace hp
