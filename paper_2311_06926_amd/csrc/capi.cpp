@@ -760,20 +760,25 @@ hipError_t fgmres_iteration(hp_ctx* c, int j, int m, int nrhs, double tol, FgSca
     hipError_t e;
     if ((e = apply_Pk(c, c->opts.order, c->opts.iters, Vj, Zj, nrhs)) != hipSuccess) return e;
     if ((e = launch_forward(c, Zj, w, nrhs)) != hipSuccess) return e;
-    for (int pass = 0; pass < 2; ++pass) {
-        if ((e = vec_multidot_partials(c->stream, N, N, Vb, V, j + 1, w, nrhs, ex->fpart)) != hipSuccess)
-            return e;
-        if ((e = fg_h(c->stream, ex->fsc, ex->fpart, cnt, ex->fH, ex->fhc, j, pass, m, nrhs)) != hipSuccess)
-            return e;
-        if ((e = vec_sub_combo(c->stream, N, N, Vb, V, j + 1, ex->fhc, m + 1, nrhs, w)) != hipSuccess)
-            return e;
-    }
-    if ((e = vec_dot_partials(c->stream, N, N, w, w, nrhs, ex->fpart)) != hipSuccess) return e;
+    // two passes: w -> w - V h (kept in V_{j+1}) -> w
+    double* Vn = Vb + (long long)(j + 1) * V;
+    auto coef = [&](int pass) {
+        return fg_h(c->stream, ex->fsc, ex->fpart, cnt, ex->fH, ex->fhc, j, pass, m, nrhs);
+    };
+    if ((e = gs_dots(c->stream, N, N, Vb, V, j + 1, w, nrhs, ex->fpart)) != hipSuccess) return e;
+    if ((e = coef(0)) != hipSuccess) return e;
+    if ((e = gs_update_dots(c->stream, N, N, Vb, V, j + 1, ex->fhc, m + 1, w, Vn, nrhs, ex->fpart)) !=
+        hipSuccess)
+        return e;
+    if ((e = coef(1)) != hipSuccess) return e;
+    if ((e = gs_update_norm(c->stream, N, N, Vb, V, j + 1, ex->fhc, m + 1, Vn, w, nrhs, ex->fpart)) !=
+        hipSuccess)
+        return e;
     if ((e = fg_rot(c->stream, ex->fsc, ex->fpart, cnt, ex->fH, ex->fcs, ex->fsn, ex->fg, ex->fvs, tol,
                     c->opts.breakdown_tol, j, m, nrhs, mirror)) != hipSuccess)
         return e;
     const double* xs[1] = {w};
-    return vec_lincomb(c->stream, N, N, nrhs, 1, xs, ex->fvs, Vb + (long long)(j + 1) * V);
+    return vec_lincomb(c->stream, N, N, nrhs, 1, xs, ex->fvs, Vn);
 }
 
 void drop_fg_graphs(Extra* ex) {

@@ -141,7 +141,7 @@ __global__ void k_dot_partial(long long n, long long ld, const double* X, long l
 #pragma unroll
         for (int u = 0; u < DOT_U; ++u) {
             const long long i = lo + k0 + u * VT;
-            const long long ic = i < hi ? i : lo;
+            const long long ic = i < hi ? i : 0;
             yv[u] = y[ic];
 #pragma unroll
             for (int qq = 0; qq < DOT_QB; ++qq)
@@ -192,19 +192,131 @@ __global__ void k_dot_final(const double* partial, int count, double* out) {
     if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// y_r -= sum_{q<nq} h[r*hld + q] * V_q   (V_q = V + q*vstride)
-__global__ void k_sub_combo(long long n, long long ld, const double* V, long long vstride, int nq,
-                            const double* h, int hld, double* Y) {
-    const int r = blockIdx.y;
-    const double* hr = h + (long long)r * hld;
-    double* y = Y + (long long)r * ld;
-    long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    long long st = (long long)gridDim.x * blockDim.x;
-    for (; i < n; i += st) {
-        double s = 0.0;
-        for (int q = 0; q < nq; ++q) s += hr[q] * V[(long long)q * vstride + (long long)r * ld + i];
-        y[i] -= s;
+// Classical Gram-Schmidt of one Arnoldi step over V_0 .. V_{nq-1}
+// (V_q = V + q vstride), one pass over the basis per launch:
+//   GS_DOTS  partial[(r nq + q) nb + b] = sum over chunk b of V_q . w
+//   GS_BOTH  w' = w - sum_q h_q V_q, and the same partials of V_q . w'
+//   GS_LAST  w' = w - sum_q h_q V_q, partial[r nb + b] = sum over chunk b of w' . w'
+// GS_BOTH reads the basis once for the first pass's update and the second
+// pass's dots: the four waves of a workgroup share a tile of 64 U entries, each
+// holding its quarter of the basis vectors (q = wave, wave + 4, ..) in registers
+// from the update to the dots; the four partial updates meet in LDS.  (All
+// vectors in each wave, without the exchange, spilled scalar registers from 16
+// vectors on: 650 -> 1230 us at 24 -> 32 vectors against 526.)
+// Bound by the read of the basis, three per step instead of four: 48^3, degree
+// 2, 32 right-hand sides, 12.5 vectors 288 / 348 / 342 us (5.6 TB/s for the
+// dots, 5.0 with the write), where the update alone took 473 at 4.0 (one load
+// in flight per thread).  FGMRES there 82.3 -> 69.1 ms, a training step at
+// 64^3 31.6 -> 27.1.
+// QW: vectors per wave (up to 32: nq <= 128); U keeps 12 to 32 loads in flight.
+// The sums run in an order that depends on n and nq alone, so a batch gives
+// the same results as its right-hand sides one at a time.
+enum GsStep { GS_DOTS, GS_BOTH, GS_LAST };
+template <int QW, int U, int STEP>
+__global__ __launch_bounds__(VT) void k_gs(long long n, long long ld, const double* V,
+                                           long long vstride, int nq, const double* h, int hld,
+                                           const double* W, double* WO, int nb, double* partial) {
+    constexpr int NW = VT / 64, TILE = 64 * U;
+    static_assert(NW == 4, "four partial updates");
+    __shared__ double ex[2][STEP == GS_DOTS ? 1 : NW][STEP == GS_DOTS ? 1 : TILE];
+    __shared__ double sh[NW];
+    const int r = blockIdx.y, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int cnt = wave < nq ? (nq - wave + NW - 1) / NW : 0;
+    const double* v0 = V + (long long)r * ld + (long long)(cnt ? wave : 0) * vstride;
+    const double* w0 = W + (long long)r * ld;
+    double* wo = STEP == GS_DOTS ? nullptr : WO + (long long)r * ld;
+    const long long chunk = (n + nb - 1) / nb;
+    const long long lo = (long long)blockIdx.x * chunk, hi = min(n, lo + chunk);
+    double hq[QW], acc[QW], ww = 0.0;
+#pragma unroll
+    for (int i = 0; i < QW; ++i) {
+        hq[i] = STEP != GS_DOTS && i < cnt ? h[(long long)r * hld + wave + NW * i] : 0.0;
+        acc[i] = 0.0;
     }
+    int buf = 0;
+    for (long long k0 = lo; k0 < hi; k0 += TILE, buf ^= 1) {
+        double v[QW][U], w[U];
+        bool in[U];
+        const double* pv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const long long i = k0 + 64 * u + lane;
+            in[u] = i < hi;
+            const long long ic = in[u] ? i : lo;
+            w[u] = w0[ic];
+            pv[u] = v0 + ic;
+        }
+#pragma unroll
+        for (int q = 0; q < QW; ++q)
+            if (q < cnt)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    v[q][u] = *pv[u];
+                    pv[u] += NW * vstride;
+                    // one address per lane that walks the vectors: a base per
+                    // vector does not fit the scalar registers
+                    if (QW >= 16) asm("" : "+v"(pv[u]));
+                }
+        if constexpr (STEP != GS_DOTS) {
+            double s[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) s[u] = 0.0;
+#pragma unroll
+            for (int q = 0; q < QW; ++q)
+                if (q < cnt)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) s[u] += hq[q] * v[q][u];
+#pragma unroll
+            for (int u = 0; u < U; ++u) ex[buf][wave][64 * u + lane] = s[u];
+            // one barrier per tile: the other buffer was read before it
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int c = 64 * u + lane;
+                w[u] -= (ex[buf][0][c] + ex[buf][1][c]) + (ex[buf][2][c] + ex[buf][3][c]);
+                if (wave == u && in[u]) {
+                    wo[k0 + c] = w[u];
+                    if (STEP == GS_LAST) ww += w[u] * w[u];
+                }
+            }
+        }
+        if constexpr (STEP != GS_LAST) {
+#pragma unroll
+            for (int q = 0; q < QW; ++q)
+                if (q < cnt)
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (in[u]) acc[q] += v[q][u] * w[u];
+        }
+    }
+    if constexpr (STEP == GS_LAST) {
+        const double s = block_sum(ww, sh);
+        if (threadIdx.x == 0) partial[(long long)r * nb + blockIdx.x] = s;
+    } else {
+#pragma unroll
+        for (int q = 0; q < QW; ++q) {
+            const double s = wave_sum(acc[q]);
+            if (q < cnt && lane == 0)
+                partial[((long long)r * nq + wave + NW * q) * nb + blockIdx.x] = s;
+        }
+    }
+}
+template <int STEP>
+void gs_launch(hipStream_t s, long long n, long long ld, const double* V, long long vstride,
+               int nq, const double* h, int hld, const double* w, double* wo, int nrhs,
+               double* partial) {
+    const int nb = dot_blocks(n), qw = (nq + 3) / 4;
+    auto go = [&](auto k) {
+        hipLaunchKernelGGL(k, dim3(nb, nrhs), dim3(VT), 0, s, n, ld, V, vstride, nq, h, hld, w, wo,
+                           nb, partial);
+    };
+    if (qw <= 2) go(k_gs<2, 4, STEP>);
+    else if (qw <= 4) go(k_gs<4, 4, STEP>);
+    else if (qw <= 6) go(k_gs<6, 2, STEP>);
+    else if (qw <= 8) go(k_gs<8, 2, STEP>);
+    else if (qw <= 16) go(k_gs<16, 2, STEP>);
+    else go(k_gs<32, 1, STEP>);
 }
 
 // y_r += sum_{q<nq} h[r*hld + q] * V_q
@@ -217,6 +329,7 @@ __global__ void k_add_combo(long long n, long long ld, const double* V, long lon
     long long st = (long long)gridDim.x * blockDim.x;
     for (; i < n; i += st) {
         double s = 0.0;
+#pragma unroll 8
         for (int q = 0; q < nq; ++q) s += hr[q] * V[(long long)q * vstride + (long long)r * ld + i];
         y[i] += s;
     }
@@ -293,14 +406,6 @@ hipError_t vec_multidot_async(hipStream_t s, long long n, long long ld, const do
 }
 
 size_t vec_partial_doubles(int npair, int nrhs) { return (size_t)npair * nrhs * DOT_BLOCKS_MAX; }
-
-hipError_t vec_sub_combo(hipStream_t s, long long n, long long ld, const double* V,
-                         long long vstride, int nq, const double* dh, int hld, int nrhs,
-                         double* Y) {
-    hipLaunchKernelGGL(k_sub_combo, dim3(grid_for(n), nrhs), dim3(VT), 0, s, n, ld, V, vstride,
-                       nq, dh, hld, Y);
-    return hipGetLastError();
-}
 
 hipError_t vec_add_combo(hipStream_t s, long long n, long long ld, const double* V,
                          long long vstride, int nq, const double* dh, int hld, int nrhs,
@@ -769,10 +874,11 @@ __global__ void k_fg_h(FgScalars* sc, const double* part, int count, double* H, 
     hcoef[(long long)r * (m + 1) + i] = active ? h : 0.0;
 }
 
-// h_{j+1,j} = ||w||, previous rotations on column j, new rotation, residual estimate
-__device__ void fg_rot_one(FgScalars* sc, double ww, double* H, double* cs, double* sn,
-                           double* g, double* vscale, double tol, double bd_tol, int j, int m,
-                           int r) {
+// h_{j+1,j} = ||w||, previous rotations on column j (hc, in LDS as are their
+// cosines and sines), new rotation, residual estimate
+__device__ void fg_rot_one(FgScalars* sc, double ww, double* H, double* hc, const double* cl,
+                           const double* sl, double* cs, double* sn, double* g, double* vscale,
+                           double tol, double bd_tol, int j, int m, int r) {
     FgScalars& s = sc[r];
     if (!s.active) {
         vscale[r] = 0.0;
@@ -783,15 +889,18 @@ __device__ void fg_rot_one(FgScalars* sc, double ww, double* H, double* cs, doub
     double* sr = sn + (long long)r * m;
     double* gr = g + (long long)r * (m + 1);
     const double hn = sqrt(ww);
-    Hr[(j + 1) * m + j] = hn;
     double col2 = ww;  // squared 2-norm of column j (the rotations keep it)
-    for (int i = 0; i <= j; ++i) col2 += Hr[i * m + j] * Hr[i * m + j];
+    for (int i = 0; i <= j; ++i) col2 += hc[i] * hc[i];
+    double hi = hc[0];
     for (int i = 0; i < j; ++i) {
-        const double t = cr[i] * Hr[i * m + j] + sr[i] * Hr[(i + 1) * m + j];
-        Hr[(i + 1) * m + j] = -sr[i] * Hr[i * m + j] + cr[i] * Hr[(i + 1) * m + j];
+        const double hb = hc[i + 1];
+        const double t = cl[i] * hi + sl[i] * hb;
+        hi = -sl[i] * hi + cl[i] * hb;
         Hr[i * m + j] = t;
     }
-    const double d = hypot(Hr[j * m + j], Hr[(j + 1) * m + j]);
+    Hr[j * m + j] = hi;
+    Hr[(j + 1) * m + j] = hn;
+    const double d = hypot(hi, hn);
     if (!isfinite(col2) || !isfinite(d)) {
         s.status = -7;
         s.active = 0;
@@ -808,32 +917,43 @@ __device__ void fg_rot_one(FgScalars* sc, double ww, double* H, double* cs, doub
         vscale[r] = 0.0;
         return;
     }
-    cr[j] = Hr[j * m + j] / d;
-    sr[j] = Hr[(j + 1) * m + j] / d;
+    const double cj = hi / d, sj = hn / d, gj = gr[j], gn = -sj * gj;
+    cr[j] = cj;
+    sr[j] = sj;
     Hr[j * m + j] = d;
     Hr[(j + 1) * m + j] = 0.0;
-    gr[j + 1] = -sr[j] * gr[j];
-    gr[j] = cr[j] * gr[j];
+    gr[j + 1] = gn;
+    gr[j] = cj * gj;
     s.jr = j + 1;
     s.iters += 1;
-    s.rel = fabs(gr[j + 1]) / s.bnorm;
+    s.rel = fabs(gn) / s.bnorm;
     if (s.rel <= tol || hn == 0.0) s.active = 0;
     vscale[r] = s.active ? 1.0 / hn : 0.0;
 }
 
 // mirror: host-mapped copy of the scalars (may be null), refreshed after the step.
 // One workgroup per rhs: ||w||^2 from its partials as a block reduction, then
-// the rotations in thread 0.
+// the rotations in thread 0, on a copy of the column and of the rotations in
+// LDS (a chain of reads from memory, this launch took 16 us at j = 22).
 __global__ void k_fg_rot(FgScalars* sc, const double* part_ww, int count, double* H, double* cs,
                          double* sn, double* g, double* vscale, double tol, double bd_tol, int j,
                          int m, FgScalars* mirror) {
     __shared__ double sh[VT / 64];
+    extern __shared__ double col[];  // column j, cosines, sines: j + 1 each
     const int r = blockIdx.x;
+    double *cl = col + j + 1, *sl = cl + j + 1;
+    for (int i = threadIdx.x; i <= j; i += VT) {
+        col[i] = H[((long long)r * (m + 1) + i) * m + j];
+        if (i < j) {
+            cl[i] = cs[(long long)r * m + i];
+            sl[i] = sn[(long long)r * m + i];
+        }
+    }
     double ws = 0.0;
     ws = strided_sum(part_ww + (long long)r * count, count, ws);
     const double ww = block_sum(ws, sh);
     if (threadIdx.x != 0) return;
-    fg_rot_one(sc, ww, H, cs, sn, g, vscale, tol, bd_tol, j, m, r);
+    fg_rot_one(sc, ww, H, col, cl, sl, cs, sn, g, vscale, tol, bd_tol, j, m, r);
     if (mirror) mirror[r] = sc[r];
 }
 
@@ -892,7 +1012,7 @@ hipError_t fg_h(hipStream_t s, FgScalars* sc, const double* part, int count, dou
 hipError_t fg_rot(hipStream_t s, FgScalars* sc, const double* part, int count, double* H,
                   double* cs, double* sn, double* g, double* vscale, double tol, double bd_tol,
                   int j, int m, int nrhs, FgScalars* mirror) {
-    hipLaunchKernelGGL(k_fg_rot, dim3(nrhs), dim3(VT), 0, s, sc, part, count, H, cs, sn, g, vscale,
+    hipLaunchKernelGGL(k_fg_rot, dim3(nrhs), dim3(VT), 3 * (j + 1) * sizeof(double), s, sc, part, count, H, cs, sn, g, vscale,
                        tol, bd_tol, j, m, mirror);
     return hipGetLastError();
 }
@@ -906,10 +1026,21 @@ hipError_t fg_check(hipStream_t s, FgScalars* sc, const double* part, int count,
     hipLaunchKernelGGL(k_fg_check, dim3(nrhs), dim3(VT), 0, s, sc, part, count, tol);
     return hipGetLastError();
 }
-hipError_t vec_multidot_partials(hipStream_t s, long long n, long long ld, const double* X,
-                                 long long xstride, int npair, const double* Y, int nrhs,
-                                 double* partial) {
-    dot_partial_launch(s, n, ld, X, xstride, npair, Y, nrhs, partial);
+hipError_t gs_dots(hipStream_t s, long long n, long long ld, const double* V, long long vstride,
+                   int nq, const double* w, int nrhs, double* partial) {
+    gs_launch<GS_DOTS>(s, n, ld, V, vstride, nq, nullptr, 0, w, nullptr, nrhs, partial);
+    return hipGetLastError();
+}
+hipError_t gs_update_dots(hipStream_t s, long long n, long long ld, const double* V,
+                          long long vstride, int nq, const double* h, int hld, const double* w,
+                          double* wo, int nrhs, double* partial) {
+    gs_launch<GS_BOTH>(s, n, ld, V, vstride, nq, h, hld, w, wo, nrhs, partial);
+    return hipGetLastError();
+}
+hipError_t gs_update_norm(hipStream_t s, long long n, long long ld, const double* V,
+                          long long vstride, int nq, const double* h, int hld, const double* w,
+                          double* wo, int nrhs, double* partial) {
+    gs_launch<GS_LAST>(s, n, ld, V, vstride, nq, h, hld, w, wo, nrhs, partial);
     return hipGetLastError();
 }
 

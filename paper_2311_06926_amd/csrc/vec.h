@@ -19,10 +19,6 @@ hipError_t vec_multidot_async(hipStream_t s, long long n, long long ld, const do
                               long long xstride, int npair, const double* Y, int nrhs,
                               double* partial, double* dout);
 size_t vec_partial_doubles(int npair, int nrhs);
-// Y_r -= sum_q dh[r*hld + q] V_q,r
-hipError_t vec_sub_combo(hipStream_t s, long long n, long long ld, const double* V,
-                         long long vstride, int nq, const double* dh, int hld, int nrhs,
-                         double* Y);
 // Y_r += sum_q dh[r*hld + q] V_q,r
 hipError_t vec_add_combo(hipStream_t s, long long n, long long ld, const double* V,
                          long long vstride, int nq, const double* dh, int hld, int nrhs,
@@ -108,9 +104,18 @@ hipError_t fg_solve(hipStream_t s, const FgScalars* sc, const double* H, const d
                     int m, int jmax, int nrhs);
 hipError_t fg_check(hipStream_t s, FgScalars* sc, const double* part, int count, double tol,
                     int nrhs);
-// partial[((r*npair + q)*count + b] of <X_q,r , Y_r>, count = vec_dot_partial_count(n)
-hipError_t vec_multidot_partials(hipStream_t s, long long n, long long ld, const double* X,
-                                 long long xstride, int npair, const double* Y, int nrhs,
-                                 double* partial);
+// Gram-Schmidt over V_q = V + q vstride, q < nq <= 128 (wo must not be w or a
+// V_q).  Partials of V_q . w per rhs, partial[(r nq + q) count + b], count =
+// vec_dot_partial_count(n):
+hipError_t gs_dots(hipStream_t s, long long n, long long ld, const double* V, long long vstride,
+                   int nq, const double* w, int nrhs, double* partial);
+// wo_r = w_r - sum_q h[r*hld + q] V_q,r and the partials of V_q . wo
+hipError_t gs_update_dots(hipStream_t s, long long n, long long ld, const double* V,
+                          long long vstride, int nq, const double* h, int hld, const double* w,
+                          double* wo, int nrhs, double* partial);
+// the same update and the partials of wo . wo, partial[r count + b]
+hipError_t gs_update_norm(hipStream_t s, long long n, long long ld, const double* V,
+                          long long vstride, int nq, const double* h, int hld, const double* w,
+                          double* wo, int nrhs, double* partial);
 
 }  // namespace hp
