@@ -155,6 +155,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 __device__ __forceinline__ double bload(__amdgpu_buffer_rsrc_t r, uint32_t off) {
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
 }
+// Two neighbours: a load instruction occupies the vector memory path for 16
+// cycles whether its lanes take 8 or 16 bytes (7.3 ns per CU; 70 and 140 B/ns
+// measured), at any alignment.  The range is checked per dword.
+struct Pair {
+    double a, b;
+};
+__device__ __forceinline__ Pair bload2(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+    return Pair{__builtin_bit_cast(double, (uint64_t)v.x | ((uint64_t)v.y << 32)),
+                __builtin_bit_cast(double, (uint64_t)v.z | ((uint64_t)v.w << 32))};
+}
 __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, uint32_t off, double v) {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, 0);
@@ -162,8 +174,10 @@ __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, uint32_t off, d
 
 // ---- pressure chain --------------------------------------------------------------------
 // Staged per plane kk: g = D u and z = nu g + p (z = p for B) on the tile and
-// a halo of W = p-1.  u3 at plane kk-1 is the previous plane's u3 value of the
-// same staging slot, so each plane reads u3 once.
+// a halo of W = p-1, two neighbours per thread and load (single values: twelve
+// loads per thread and plane on 32 x 8 tiles at degree 3 instead of six).  u3
+// at plane kk-1 is the previous plane's u3 value of the same staging slot, so
+// each plane reads u3 once.
 // waves per SIMD the register budget allows: the band rows and the windows
 // grow with the degree
 template <int P>
@@ -175,9 +189,11 @@ template <int P, int PT1, int PT2>
 __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves_for<P>()))) void k_pres(OpArgs a, double* yp, long long syp, PresJob job) {
     constexpr int PNT = PT1 * PT2;
     constexpr int W = P - 1;
-    constexpr int SW = PT1 + 2 * W, SR = PT2 + 2 * W;
-    constexpr int NS = (SR * SW + PNT - 1) / PNT;  // staging slots per thread
-    __shared__ double gs[SR * SW], zs[SR * SW], pg[SR * PT1], pz[SR * PT1];
+    constexpr int WE = (W + 1) & ~1;  // pairs start at even columns
+    constexpr int SW = PT1 + 2 * WE, SR = PT2 + 2 * W, PR = SW / 2;
+    constexpr int NS = (SR * PR + PNT - 1) / PNT;  // staging slots (pairs) per thread
+    __shared__ alignas(16) double gs[SR * SW], zs[SR * SW];
+    __shared__ double pg[SR * PT1], pz[SR * PT1];
     const int nM = a.nM, nN = a.nN;
     int id = xcd_block(pick_job(a, yp, syp, job), a.nblocks);
     const int t1 = id % a.ntile1;
@@ -209,20 +225,25 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
     const long long P3 = (long long)nM * nM;   // plane of u3 (nM, nM, nN) and of p
     const uint32_t B1 = use_u ? 8u * (uint32_t)P1 : 0u, B2 = use_u ? 8u * (uint32_t)P2 : 0u;
     const uint32_t B3 = use_u ? 8u * (uint32_t)P3 : 0u, BP = use_p ? 8u * (uint32_t)P3 : 0u;
-    // staging slots: byte offsets of u1[ii], u1[ii-1], u2[jj], u2[jj-1], and
-    // of u3/p, each OOB where the value lies outside its field
+    // staging slots: pairs (ii, ii + 1) of a row, ii even; byte offsets of
+    // u1[ii..], u1[ii-1], u2[jj], u2[jj-1], and of u3/p, each OOB where the
+    // first value lies outside its field; a second value outside is dropped
+    // (v1: of u1, v2: of the pressure points)
     uint32_t oa[NS], ob[NS], oc[NS], od[NS], oe[NS];
+    bool v1[NS], v2[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int idx = threadIdx.x + s * PNT;
-        const int rr = idx / SW, cc = idx - rr * SW;
-        const int jj = j0 - W + rr, ii = i0 - W + cc;
-        const bool ok = idx < SR * SW && jj >= 0 && jj < nM && ii >= 0 && ii < nM;
+        const int rr = idx / PR, cc = 2 * (idx - rr * PR);
+        const int jj = j0 - W + rr, ii = i0 - WE + cc;
+        const bool ok = idx < SR * PR && jj >= 0 && jj < nM && ii >= 0 && ii < nM;
         oa[s] = (ok && ii < nN) ? 8u * (nN * jj + ii) : OOB;
         ob[s] = (ok && ii >= 1) ? 8u * (nN * jj + ii - 1) : OOB;
         oc[s] = (ok && jj < nN) ? 8u * (ii + nM * jj) : OOB;
         od[s] = (ok && jj >= 1) ? 8u * (ii + nM * (jj - 1)) : OOB;
         oe[s] = ok ? 8u * (ii + nM * jj) : OOB;
+        v1[s] = ii + 1 < nN;
+        v2[s] = ii + 1 < nM;
     }
     // Plane addresses advanced by one plane per step (one 64-bit add each
     // instead of a product per plane); a plane outside the mesh gets a
@@ -234,7 +255,11 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
     const uint64_t Q1 = 8ull * (uint64_t)P1, Q2 = 8ull * (uint64_t)P2, Q3 = 8ull * (uint64_t)P3;
     // raw values of plane kk (zero outside the mesh) from the plane addresses
     // a[0..3] of u1, u2, u3 and p at kk
-    auto fetch = [&](int kk, const uint64_t (&ad)[4], double (&v)[NS][6]) {
+    struct Raw {
+        Pair u1, u2, u2m, u3, p;
+        double u1m;
+    };
+    auto fetch = [&](int kk, const uint64_t (&ad)[4], Raw (&v)[NS]) {
         const bool kin = kk >= 0 && kk < nM;
         const bool k3in = kk >= 0 && kk < nN;
         const auto r1 = make_rsrc(ptr(ad[0]), kin ? B1 : 0u);
@@ -243,12 +268,12 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
         const auto rp = make_rsrc(ptr(ad[3]), kin ? BP : 0u);
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            v[s][0] = bload(r1, oa[s]);
-            v[s][1] = bload(r1, ob[s]);
-            v[s][2] = bload(r2, oc[s]);
-            v[s][3] = bload(r2, od[s]);
-            v[s][4] = bload(r3, oe[s]);
-            v[s][5] = bload(rp, oe[s]);
+            v[s].u1 = bload2(r1, oa[s]);
+            v[s].u1m = bload(r1, ob[s]);
+            v[s].u2 = bload2(r2, oc[s]);
+            v[s].u2m = bload2(r2, od[s]);
+            v[s].u3 = bload2(r3, oe[s]);
+            v[s].p = bload2(rp, oe[s]);
         }
     };
     double c1[2 * W + 1], c2[2 * W + 1];
@@ -264,14 +289,15 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
         ad[2] = addr(u3, P3 * kk);
         ad[3] = addr(pp, P3 * kk);
     };
-    double buf[PF][NS][6], a3prev[NS];
+    Raw buf[PF][NS];
+    Pair a3prev[NS];
     {
-        double t[NS][6];
+        Raw t[NS];
         uint64_t ad[4];
         planes(k0 - W - 1, ad);
         fetch(k0 - W - 1, ad, t);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) a3prev[s] = t[s][4];
+        for (int s = 0; s < NS; ++s) a3prev[s] = t[s].u3;
     }
 #pragma unroll
     for (int d = 0; d < PF; ++d) {
@@ -287,16 +313,20 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
     uint64_t ayo = addr(ypr, P3 * (k0 - 2 * W - 1)), awo = addr(wv, P3 * (k0 - 2 * W - 1));
     // one step: consume plane kk, store the pending output, refill the
     // registers with plane kk + PF, then process plane kk
-    auto step = [&](int kk, double (&b)[NS][6]) {
+    auto step = [&](int kk, Raw (&b)[NS]) {
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int idx = threadIdx.x + s * PNT;
-            if (idx < SR * SW) {
-                const double gv = (b[s][0] - b[s][1]) + (b[s][2] - b[s][3]) + (b[s][4] - a3prev[s]);
-                gs[idx] = gv;
-                zs[idx] = zg * gv + b[s][5];
+            const Raw& q = b[s];
+            const double u1b = v1[s] ? q.u1.b : 0.0;
+            if (idx < SR * PR) {
+                const double ga = (q.u1.a - q.u1m) + (q.u2.a - q.u2m.a) + (q.u3.a - a3prev[s].a);
+                const double gb = (u1b - q.u1.a) + (q.u2.b - q.u2m.b) + (q.u3.b - a3prev[s].b);
+                const double zb = zg * gb + q.p.b;
+                *reinterpret_cast<double2*>(gs + 2 * idx) = double2{ga, v2[s] ? gb : 0.0};
+                *reinterpret_cast<double2*>(zs + 2 * idx) = double2{zg * ga + q.p.a, v2[s] ? zb : 0.0};
             }
-            a3prev[s] = b[s][4];
+            a3prev[s] = q.u3;
         }
         {
             const bool on = pk >= 0;
@@ -315,8 +345,8 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
             double sg = 0.0, sz = 0.0;
 #pragma unroll
             for (int t = 0; t <= 2 * W; ++t) {
-                sg += c1[t] * gs[rr * SW + c + t];
-                sz += c1[t] * zs[rr * SW + c + t];
+                sg += c1[t] * gs[rr * SW + c + t + WE - W];
+                sz += c1[t] * zs[rr * SW + c + t + WE - W];
             }
             pg[rr * PT1 + c] = sg;
             pz[rr * PT1 + c] = sz;
@@ -726,27 +756,34 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_for<P>
 // registers: its waves wait on memory most of the time, and deeper register
 // prefetch costs more occupancy than it adds.  This variant stages the tile
 // and halo of each plane with buffer loads that write LDS directly
-// (buffer_load_dword ... lds, no registers), into a ring of three LDS
-// slots, so two planes are in flight.  The staged array is the same SR x SW
-// doubles as xs, filled as 2 SR SW dwords by consecutive lanes (lane l of
-// load s of wave w writes dword s NT + 64 w + l; lanes past the array write
-// into the slot's padding, so every load of a plane is issued by every
-// lane and the count per plane is fixed).  Each slot is its own __shared__
-// array so that the compiler's wait for the loads into one slot leaves the
-// later slots' loads in flight; a read of the thread's own element of the
-// slot before the barrier makes the compiler wait for this wave's loads of
-// that plane there, and the barrier (with only an LDS wait, no fence: a
+// (buffer_load_dwordx4 ... lds, no registers), into a ring of three LDS
+// slots, so two planes are in flight.  The staged array is SR x SW doubles,
+// SW rounded up so that a pair starts at an even column; lane l of load s of
+// wave w writes pair s NT + 64 w + l, and lanes past the array write into the
+// slot's padding, so every load of a plane is issued by every lane and the
+// count per plane is fixed.  A pair whose second value is the first of the
+// next row has it overwritten with zero once it has arrived.  Each slot is its
+// own __shared__ array so that the compiler's wait for the loads into one slot
+// leaves the later slots' loads in flight; a read of the thread's own element
+// of the slot before the barrier makes the compiler wait for this wave's loads
+// of that plane there, and the barrier (with only an LDS wait, no fence: a
 // fence would wait for every load in flight) then orders every wave's.  The
 // arithmetic per output is vel_component's, so the results agree bit for bit.
+// Loads that cost the vector memory path half as much per byte (16 bytes a
+// lane here, w and its neighbour in one, no load of an absent source) took
+// K at 192^3 from 301 to 276 us at degree 3 and from 272 to 231 at degree 2
+// together with k_pres's pairs.  Not kept, with no gain: a ring of four, the
+// coupling three planes ahead, two rows per thread, sums in flight in place of
+// the windows.
 template <int P, int C>
-constexpr int dma_dwords() {
+constexpr int dma_pairs() {  // pairs of doubles of a staged plane, to whole loads
     constexpr int W1 = (C == 0) ? P : P - 1, W2 = (C == 1) ? P : P - 1;
-    return ((2 * (T2 + 2 * W2) * (T1 + 2 * W1) + NT - 1) / NT) * NT;
+    return ((T2 + 2 * W2) * ((T1 + 2 * ((W1 + 1) & ~1)) / 2) + NT - 1) / NT * NT;
 }
 template <int P>
 constexpr int dma_slot_doubles() {
-    constexpr int a = dma_dwords<P, 0>(), b = dma_dwords<P, 1>(), c = dma_dwords<P, 2>();
-    return (a > b ? (a > c ? a : c) : (b > c ? b : c)) / 2;
+    constexpr int a = dma_pairs<P, 0>(), b = dma_pairs<P, 1>(), c = dma_pairs<P, 2>();
+    return 2 * (a > b ? (a > c ? a : c) : (b > c ? b : c));
 }
 typedef __attribute__((address_space(3))) void* lds_vptr;
 __device__ __forceinline__ void lds_barrier() {
@@ -760,8 +797,9 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
     constexpr int W1 = (C == 0) ? P : P - 1;
     constexpr int W2 = (C == 1) ? P : P - 1;
     constexpr int W3 = (C == 2) ? P : P - 1;
-    constexpr int SW = T1 + 2 * W1, SR = T2 + 2 * W2;
-    constexpr int ND = dma_dwords<P, C>() / NT;  // dword loads per thread and plane
+    constexpr int WE = (W1 + 1) & ~1;  // pairs start at even columns
+    constexpr int SW = T1 + 2 * WE, SR = T2 + 2 * W2, PR = SW / 2;
+    constexpr int ND = dma_pairs<P, C>() / NT;  // loads per thread and plane
     const int n1 = a.dims[C][0], n2 = a.dims[C][1], n3 = a.dims[C][2];
     if (i0 >= n1 || j0 >= n2 || k0 >= n3) return;
     const int kend = min(min(k0 + a.kchunk, a.klim), n3);
@@ -779,10 +817,9 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
     double* y = out.f[C] + (long long)r * out.stride[C];
     const bool has_src = beta != 0.0;
     const double* sv = has_src ? src.f[C] + (long long)r * src.stride[C] : y;
-    const uint32_t SB = has_src ? YB : 0u;
     const uint32_t WBm = mv ? 0u : WB;
     const uint32_t wo = act ? 8u * (i + nM * j) : OOB;
-    const uint32_t wo1 = act ? wo + (C == 0 ? 8u : C == 1 ? 8u * nM : 0u) : OOB;
+    const uint32_t wo1 = act && C == 1 ? wo + 8u * nM : OOB;
     const uint32_t yo = act ? 8u * (i + n1 * j) : OOB;
     double* pa = pab;
     double* pb = pab + SR * T1;
@@ -793,18 +830,21 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
     const double* ta = a.bt.ptr[C == 2 ? (mv ? BM_N : BK_N) : BM_C];
     const double* tb = a.bt.ptr[C == 2 ? BM_N : BT_C];
     const double* x = a.u[C] + (long long)r * a.su;
-    // byte offsets of this thread's dwords of the staged plane (OOB outside
-    // the component and in the padding)
+    // byte offsets of this thread's pairs of the staged plane (OOB outside the
+    // component and in the padding); drop: pairs whose second value lies past
+    // the end of its row
     uint32_t so[ND];
+    uint32_t drop = 0;
 #pragma unroll
     for (int s = 0; s < ND; ++s) {
-        const int d = threadIdx.x + s * NT;
-        const int idx = d >> 1;
-        const int rr = idx / SW, cc = idx - rr * SW;
-        const int jj = j0 - W2 + rr, ii = i0 - W1 + cc;
-        const bool ok = idx < SR * SW && jj >= 0 && jj < n2 && ii >= 0 && ii < n1;
-        so[s] = ok ? 8u * (jj * n1 + ii) + 4u * (d & 1) : OOB;
+        const int idx = threadIdx.x + s * NT;
+        const int rr = idx / PR, cc = 2 * (idx - rr * PR);
+        const int jj = j0 - W2 + rr, ii = i0 - WE + cc;
+        const bool ok = idx < SR * PR && jj >= 0 && jj < n2 && ii >= 0 && ii < n1;
+        so[s] = ok ? 8u * (jj * n1 + ii) : OOB;
+        if (ok && ii + 1 >= n1) drop |= 1u << s;
     }
+    const bool edge = (n1 & 1) && i0 - WE + SW > n1;  // uniform: some pair is dropped
     // The planes a step touches, as byte addresses advanced by one plane per
     // step (one 64-bit add each instead of a product per plane); a plane
     // outside the field gets a zero-size resource, so its address, which may
@@ -817,17 +857,29 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
     auto fetch_x = [&](int kk, uint64_t ax, double* slot) {
         const bool kin = kk >= 0 && kk < n3;
         const auto rx = make_rsrc(ptr(ax), kin ? YB : 0u);
-        uint32_t* base = reinterpret_cast<uint32_t*>(slot) + 64 * wave;
+        double* base = slot + 128 * wave;
 #pragma unroll
         for (int s = 0; s < ND; ++s)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_vptr)(base + s * NT), 4, so[s], 0, 0,
-                                                     0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_vptr)(base + 2 * s * NT), 16, so[s],
+                                                     0, 0, 0);
     };
+    // w at the point and its +1 neighbour and the source, for output plane k
+    // (C == 2: the neighbour becomes the next plane's point)
     auto fetch_out = [&](int k, uint64_t aw, uint64_t as, double& w0, double& w1, double& sd) {
         const bool kin = k >= 0 && k < n3;
-        w0 = bload(make_rsrc(ptr(aw), kin ? WBm : 0u), wo);
-        w1 = bload(make_rsrc(ptr(C == 2 ? aw + PW : aw), kin ? WBm : 0u), wo1);
-        sd = bload(make_rsrc(ptr(as), kin ? SB : 0u), yo);
+        if constexpr (C == 0) {
+            const Pair w = bload2(make_rsrc(ptr(aw), kin ? WBm : 0u), wo);
+            w0 = w.a;
+            w1 = w.b;
+        } else if constexpr (C == 1) {
+            const auto rw = make_rsrc(ptr(aw), kin ? WBm : 0u);
+            w0 = bload(rw, wo);
+            w1 = bload(rw, wo1);
+        } else {
+            w0 = w1;
+            w1 = bload(make_rsrc(ptr(aw + PW), k + 1 >= 0 && k + 1 < nM ? WBm : 0u), wo);
+        }
+        if (has_src) sd = bload(make_rsrc(ptr(as), kin ? YB : 0u), yo);
     };
     double ca[2 * W1 + 1], cb[2 * W1 + 1], cm[2 * W2 + 1], ck[2 * W2 + 1];
     load_band_row<W1>(t1a, i, i < n1, ca);
@@ -837,9 +889,10 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
     Window<W3> wa, wb;
     wa.clear();
     wb.clear();
-    double fw0, fw1, fsd;
+    double fw0 = 0.0, fw1 = 0.0, fsd = 0.0;
     fetch_x(k0 - W3, addr(x, plane * (k0 - W3)), s0);
     fetch_x(k0 - W3 + 1, addr(x, plane * (k0 - W3 + 1)), s1);
+    // (C == 2: w of output plane k0 arrives as a neighbour, W3 >= 1 steps later)
     fetch_out(k0 - 2 * W3, addr(wv, wplane * (k0 - 2 * W3)), addr(sv, plane * (k0 - 2 * W3)), fw0,
               fw1, fsd);
     int pk = -1;
@@ -857,6 +910,10 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
             const double probe = cur[threadIdx.x];
             asm volatile("" ::"v"(probe));
         }
+        if (edge)
+#pragma unroll
+            for (int s = 0; s < ND; ++s)
+                if (drop >> s & 1) cur[2 * (threadIdx.x + s * NT) + 1] = 0.0;
         lds_barrier();
         fetch_x(kk + 2, ax, nxt);
         ax += PY;
@@ -872,7 +929,7 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
                 double sa = 0.0, sb = 0.0;
 #pragma unroll
                 for (int t = 0; t <= 2 * W1; ++t) {
-                    const double xv = cur[rr * SW + c + t];
+                    const double xv = cur[rr * SW + c + t + WE - W1];
                     sa += ca[t] * xv;
                     sb += cb[t] * xv;
                 }
@@ -931,7 +988,8 @@ template <int P>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_for<P>()))) void k_vel_dma(
     OpArgs a, Fields out, Fields src, double alpha, double beta) {
     constexpr int SL = dma_slot_doubles<P>();
-    __shared__ double s0[SL], s1[SL], s2[SL], pab[2 * (T2 + 2 * P) * T1];
+    __shared__ alignas(16) double s0[SL], s1[SL], s2[SL];
+    __shared__ double pab[2 * (T2 + 2 * P) * T1];
     int id = xcd_block(blockIdx.x, a.nblocks);
     int comp;
     if (a.comp_fast) {
