@@ -122,7 +122,49 @@ struct Window {
         for (int t = 0; t <= 2 * W; ++t) s += row[t] * v[t];
         return s;
     }
+    __device__ __forceinline__ double dot(const double (&row)[2 * W + 1]) const {
+        double s = 0.0;
+#pragma unroll
+        for (int t = 0; t <= 2 * W; ++t) s += row[t] * v[t];
+        return s;
+    }
 };
+
+struct Pair {
+    double a, b;
+};
+
+// Band row of a uniform index, read through the scalar cache.
+template <int W>
+__device__ __forceinline__ void load_uniform_row(const double* tab, int row,
+                                                 double (&c)[2 * W + 1]) {
+    const auto* r = reinterpret_cast<const __attribute__((address_space(4))) double*>(
+                        reinterpret_cast<uintptr_t>(tab)) + row * (2 * W + 1);
+#pragma unroll
+    for (int t = 0; t <= 2 * W; ++t) c[t] = r[t];
+}
+// use(t, read(t)) for t < N, the reads from LDS.  Left alone the compiler reads
+// two or three operands, waits, uses them and reads the next into the same
+// registers: a chain of some ten waits per velocity step.  FIRST: all reads
+// stand before all uses (the kernels then also load the band rows of the step's
+// output beside them).  K at 192^3, degree 4, 363 -> 345 us; 96^3, degree 5,
+// 108 -> 91.  Not in the velocity kernel at degrees 2 and 3, where the operands
+// cost the fourth wave per SIMD or spill (192^3, degree 3: 267 -> 283 or 310),
+// nor from degree 7 on, where they do not fit.
+template <bool FIRST, int N, typename R, typename F>
+__device__ __forceinline__ void band_pass(R read, F use) {
+    if constexpr (FIRST) {
+        decltype(read(0)) v[N];
+#pragma unroll
+        for (int t = 0; t < N; ++t) v[t] = read(t);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < N; ++t) use(t, v[t]);
+    } else {
+#pragma unroll
+        for (int t = 0; t < N; ++t) use(t, read(t));
+    }
+}
 
 template <int W>
 __device__ __forceinline__ void load_band_row(const double* tab, int row, bool ok,
@@ -155,12 +197,23 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 __device__ __forceinline__ double bload(__amdgpu_buffer_rsrc_t r, uint32_t off) {
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
 }
+// Planes of a field from plane kb on, as one resource that stays in scalar
+// registers; the lanes' offsets advance by a plane per step.  A plane before
+// kb is a negative offset, which reads as one beyond the resource, and so does
+// OOB however far it has advanced: the launch limits the planes per workgroup
+// so that offsets stay below 2^31.  (A resource per plane and access was 41 of
+// the 77 scalar instructions of a velocity step: K at 64^3, degree 3, 30.6 ->
+// 27.8 us without.)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t planes_rsrc(const double* field, long long plane,
+                                                             int kb, int planes, int most,
+                                                             bool used = true) {
+    const int n = used ? min(planes - kb, most) : 0;
+    return make_rsrc(field + plane * kb, n > 0 ? 8u * (uint32_t)plane * (uint32_t)n : 0u);
+}
+
 // Two neighbours: a load instruction occupies the vector memory path for 16
 // cycles whether its lanes take 8 or 16 bytes (7.3 ns per CU; 70 and 140 B/ns
 // measured), at any alignment.  The range is checked per dword.
-struct Pair {
-    double a, b;
-};
 __device__ __forceinline__ Pair bload2(__amdgpu_buffer_rsrc_t r, uint32_t off) {
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
     const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
@@ -189,6 +242,7 @@ template <int P, int PT1, int PT2>
 __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves_for<P>()))) void k_pres(OpArgs a, double* yp, long long syp, PresJob job) {
     constexpr int PNT = PT1 * PT2;
     constexpr int W = P - 1;
+    constexpr bool FIRST = P <= 6;
     constexpr int WE = (W + 1) & ~1;  // pairs start at even columns
     constexpr int SW = PT1 + 2 * WE, SR = PT2 + 2 * W, PR = SW / 2;
     constexpr int NS = (SR * PR + PNT - 1) / PNT;  // staging slots (pairs) per thread
@@ -223,8 +277,15 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
     const long long P1 = (long long)nN * nM;   // plane of u1 (nN, nM, nM)
     const long long P2 = (long long)nM * nN;   // plane of u2 (nM, nN, nM)
     const long long P3 = (long long)nM * nM;   // plane of u3 (nM, nM, nN) and of p
-    const uint32_t B1 = use_u ? 8u * (uint32_t)P1 : 0u, B2 = use_u ? 8u * (uint32_t)P2 : 0u;
-    const uint32_t B3 = use_u ? 8u * (uint32_t)P3 : 0u, BP = use_p ? 8u * (uint32_t)P3 : 0u;
+    const uint32_t Q1 = 8u * (uint32_t)P1, Q2 = 8u * (uint32_t)P2, Q3 = 8u * (uint32_t)P3;
+    // planes k0 - W - 1 .. kend + W of the inputs, k0 .. kend - 1 of the outputs
+    const int kb = max(0, k0 - W - 1), km = a.kchunk + 2 * W + 2 + PF;
+    const auto r1 = planes_rsrc(u1, P1, kb, nM, km, use_u);
+    const auto r2 = planes_rsrc(u2, P2, kb, nM, km, use_u);
+    const auto r3 = planes_rsrc(u3, P3, kb, nN, km, use_u);
+    const auto rp = planes_rsrc(pp, P3, kb, nM, km, use_p);
+    const auto ry = planes_rsrc(ypr, P3, kb, nM, km, need_g);
+    const auto rw = planes_rsrc(wv, P3, kb, nM, km, need_z);
     // staging slots: pairs (ii, ii + 1) of a row, ii even; byte offsets of
     // u1[ii..], u1[ii-1], u2[jj], u2[jj-1], and of u3/p, each OOB where the
     // first value lies outside its field; a second value outside is dropped
@@ -237,35 +298,21 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
         const int rr = idx / PR, cc = 2 * (idx - rr * PR);
         const int jj = j0 - W + rr, ii = i0 - WE + cc;
         const bool ok = idx < SR * PR && jj >= 0 && jj < nM && ii >= 0 && ii < nM;
-        oa[s] = (ok && ii < nN) ? 8u * (nN * jj + ii) : OOB;
-        ob[s] = (ok && ii >= 1) ? 8u * (nN * jj + ii - 1) : OOB;
-        oc[s] = (ok && jj < nN) ? 8u * (ii + nM * jj) : OOB;
-        od[s] = (ok && jj >= 1) ? 8u * (ii + nM * (jj - 1)) : OOB;
-        oe[s] = ok ? 8u * (ii + nM * jj) : OOB;
+        const uint32_t kf = (uint32_t)(k0 - W - kb);  // the first plane of all
+        oa[s] = (ok && ii < nN) ? 8u * (nN * jj + ii) + kf * Q1 : OOB;
+        ob[s] = (ok && ii >= 1) ? 8u * (nN * jj + ii - 1) + kf * Q1 : OOB;
+        oc[s] = (ok && jj < nN) ? 8u * (ii + nM * jj) + kf * Q2 : OOB;
+        od[s] = (ok && jj >= 1) ? 8u * (ii + nM * (jj - 1)) + kf * Q2 : OOB;
+        oe[s] = ok ? 8u * (ii + nM * jj) + kf * Q3 : OOB;
         v1[s] = ii + 1 < nN;
         v2[s] = ii + 1 < nM;
     }
-    // Plane addresses advanced by one plane per step (one 64-bit add each
-    // instead of a product per plane); a plane outside the mesh gets a
-    // zero-size resource, so its address is never dereferenced.
-    auto addr = [](const double* base, long long elems) {
-        return reinterpret_cast<uint64_t>(base) + (uint64_t)(elems * 8);
-    };
-    auto ptr = [](uint64_t a) { return reinterpret_cast<const double*>(a); };
-    const uint64_t Q1 = 8ull * (uint64_t)P1, Q2 = 8ull * (uint64_t)P2, Q3 = 8ull * (uint64_t)P3;
-    // raw values of plane kk (zero outside the mesh) from the plane addresses
-    // a[0..3] of u1, u2, u3 and p at kk
+    // raw values of the next plane (zero outside the mesh)
     struct Raw {
         Pair u1, u2, u2m, u3, p;
         double u1m;
     };
-    auto fetch = [&](int kk, const uint64_t (&ad)[4], Raw (&v)[NS]) {
-        const bool kin = kk >= 0 && kk < nM;
-        const bool k3in = kk >= 0 && kk < nN;
-        const auto r1 = make_rsrc(ptr(ad[0]), kin ? B1 : 0u);
-        const auto r2 = make_rsrc(ptr(ad[1]), kin ? B2 : 0u);
-        const auto r3 = make_rsrc(ptr(ad[2]), k3in ? B3 : 0u);
-        const auto rp = make_rsrc(ptr(ad[3]), kin ? BP : 0u);
+    auto fetch = [&](Raw (&v)[NS]) {
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             v[s].u1 = bload2(r1, oa[s]);
@@ -274,43 +321,29 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
             v[s].u2m = bload2(r2, od[s]);
             v[s].u3 = bload2(r3, oe[s]);
             v[s].p = bload2(rp, oe[s]);
+            oa[s] += Q1;
+            ob[s] += Q1;
+            oc[s] += Q2;
+            od[s] += Q2;
+            oe[s] += Q3;
         }
     };
     double c1[2 * W + 1], c2[2 * W + 1];
     load_band_row<W>(tm, i, i < nM, c1);
     load_band_row<W>(tm, j, j < nM, c2);
-    const uint32_t oo = act ? 8u * (i + nM * j) : OOB;  // this thread's output
+    // this thread's output, at the first pending plane (k0 - 2 W - 1)
+    uint32_t oo = act ? 8u * (i + nM * j) + (uint32_t)(k0 - 2 * W - 1 - kb) * Q3 : OOB;
     Window<W> wg, wz;
     wg.clear();
     wz.clear();
-    auto planes = [&](int kk, uint64_t (&ad)[4]) {
-        ad[0] = addr(u1, P1 * kk);
-        ad[1] = addr(u2, P2 * kk);
-        ad[2] = addr(u3, P3 * kk);
-        ad[3] = addr(pp, P3 * kk);
-    };
     Raw buf[PF][NS];
     Pair a3prev[NS];
-    {
-        Raw t[NS];
-        uint64_t ad[4];
-        planes(k0 - W - 1, ad);
-        fetch(k0 - W - 1, ad, t);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) a3prev[s] = t[s].u3;
-    }
+    for (int s = 0; s < NS; ++s) a3prev[s] = bload2(r3, oe[s] == OOB ? OOB : oe[s] - Q3);
 #pragma unroll
-    for (int d = 0; d < PF; ++d) {
-        uint64_t ad[4];
-        planes(k0 - W + d, ad);
-        fetch(k0 - W + d, ad, buf[d]);
-    }
+    for (int d = 0; d < PF; ++d) fetch(buf[d]);
     int pk = -1;  // plane of the pending output (none yet)
     double py = 0.0, pw = 0.0;
-    // at the first step kk = k0 - W: input plane kk + PF, pending output kk - W - 1
-    uint64_t an[4];
-    planes(k0 - W + PF, an);
-    uint64_t ayo = addr(ypr, P3 * (k0 - 2 * W - 1)), awo = addr(wv, P3 * (k0 - 2 * W - 1));
     // one step: consume plane kk, store the pending output, refill the
     // registers with plane kk + PF, then process plane kk
     auto step = [&](int kk, Raw (&b)[NS]) {
@@ -328,44 +361,44 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
             }
             a3prev[s] = q.u3;
         }
-        {
-            const bool on = pk >= 0;
-            bstore(make_rsrc(ptr(ayo), (on && need_g) ? 8u * (uint32_t)P3 : 0u), oo, py);
-            bstore(make_rsrc(ptr(awo), (on && need_z) ? 8u * (uint32_t)P3 : 0u), oo, pw);
-            ayo += Q3;
-            awo += Q3;
-        }
-        fetch(kk + PF, an, b);
-        an[0] += Q1;
-        an[1] += Q2;
-        an[2] += Q3;
-        an[3] += Q3;
+        bstore(ry, pk >= 0 ? oo : OOB, py);
+        bstore(rw, pk >= 0 ? oo : OOB, pw);
+        if (act) oo += Q3;
+        fetch(b);
         __syncthreads();
         for (int rr = g; rr < SR; rr += PT2) {
             double sg = 0.0, sz = 0.0;
-#pragma unroll
-            for (int t = 0; t <= 2 * W; ++t) {
-                sg += c1[t] * gs[rr * SW + c + t + WE - W];
-                sz += c1[t] * zs[rr * SW + c + t + WE - W];
-            }
+            band_pass<FIRST, 2 * W + 1>(
+                [&](int t) {
+                    const int o = rr * SW + c + t + WE - W;
+                    return Pair{gs[o], zs[o]};
+                },
+                [&](int t, Pair v) {
+                    sg += c1[t] * v.a;
+                    sz += c1[t] * v.b;
+                });
             pg[rr * PT1 + c] = sg;
             pz[rr * PT1 + c] = sz;
         }
         __syncthreads();
-        double sg = 0.0, sz = 0.0;
-#pragma unroll
-        for (int t = 0; t <= 2 * W; ++t) {
-            sg += c2[t] * pg[(g + t) * PT1 + c];
-            sz += c2[t] * pz[(g + t) * PT1 + c];
-        }
+        const int k = kk - W;
+        double c3[2 * W + 1], sg = 0.0, sz = 0.0;
+        if (FIRST) load_uniform_row<W>(tm, min(max(k, 0), nM - 1), c3);
+        band_pass<FIRST, 2 * W + 1>(
+            [&](int t) { return Pair{pg[(g + t) * PT1 + c], pz[(g + t) * PT1 + c]}; },
+            [&](int t, Pair v) {
+                sg += c2[t] * v.a;
+                sz += c2[t] * v.b;
+            });
         wg.push(sg);
         wz.push(sz);
-        const int k = kk - W;
         pk = (k >= k0 && k < kend) ? k : -1;
-        if (pk >= 0) {
-            const double* rm = tm + k * (2 * W + 1);
-            py = wg.dot(rm);
-            pw = wz.dot(rm);
+        if (FIRST) {
+            py = wg.dot(c3);
+            pw = wz.dot(c3);
+        } else if (pk >= 0) {
+            py = wg.dot(tm + k * (2 * W + 1));
+            pw = wz.dot(tm + k * (2 * W + 1));
         }
     };
     // steps past kend + W - 1 (when the count is not a multiple of PF) output nothing
@@ -374,8 +407,8 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
         for (int d = 0; d < PF; ++d) step(kk + d, buf[d]);
     }
     if (pk >= 0) {
-        bstore(make_rsrc(ypr + P3 * pk, need_g ? 8u * (uint32_t)P3 : 0u), oo, py);
-        bstore(make_rsrc(wv + P3 * pk, need_z ? 8u * (uint32_t)P3 : 0u), oo, pw);
+        bstore(ry, oo, py);
+        bstore(rw, oo, pw);
     }
 }
 
@@ -797,6 +830,7 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
     constexpr int W1 = (C == 0) ? P : P - 1;
     constexpr int W2 = (C == 1) ? P : P - 1;
     constexpr int W3 = (C == 2) ? P : P - 1;
+    constexpr bool FIRST = P >= 4 && P <= 6;
     constexpr int WE = (W1 + 1) & ~1;  // pairs start at even columns
     constexpr int SW = T1 + 2 * WE, SR = T2 + 2 * W2, PR = SW / 2;
     constexpr int ND = dma_pairs<P, C>() / NT;  // loads per thread and plane
@@ -813,14 +847,24 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
     const double* wv = a.ws + (long long)r * a.ws_stride;
     const long long plane = (long long)n1 * n2;
     const long long wplane = (long long)nM * nM;
-    const uint32_t YB = 8u * (uint32_t)plane, WB = 8u * (uint32_t)wplane;
+    const uint32_t PY = 8u * (uint32_t)plane, PW = 8u * (uint32_t)wplane;
     double* y = out.f[C] + (long long)r * out.stride[C];
     const bool has_src = beta != 0.0;
     const double* sv = has_src ? src.f[C] + (long long)r * src.stride[C] : y;
-    const uint32_t WBm = mv ? 0u : WB;
-    const uint32_t wo = act ? 8u * (i + nM * j) : OOB;
-    const uint32_t wo1 = act && C == 1 ? wo + 8u * nM : OOB;
-    const uint32_t yo = act ? 8u * (i + n1 * j) : OOB;
+    // planes k0 - W3 .. kend + W3 of the input, k0 .. kend of w, k0 .. kend - 1
+    // of the output and the source
+    const int kb = max(0, k0 - W3), km = a.kchunk + 2 * W3 + 4;
+    const auto rx = planes_rsrc(a.u[C] + (long long)r * a.su, plane, kb, n3, km);
+    const auto rw = planes_rsrc(wv, wplane, kb, nM, km, !mv);
+    const auto ry = planes_rsrc(y, plane, kb, n3, km);
+    const auto rs = planes_rsrc(sv, plane, kb, n3, km, has_src);
+    // this thread's w, its +1 neighbour (C == 1) and source at output plane
+    // k0 - 2 W3, and its output one plane before
+    const uint32_t kf = (uint32_t)(k0 - 2 * W3 - kb);
+    uint32_t wo = act ? 8u * (i + nM * j) + kf * PW : OOB;
+    uint32_t wo1 = act ? wo + (C == 1 ? 8u * nM : PW) : OOB;  // (C == 2: the next plane's)
+    uint32_t yo = act ? 8u * (i + n1 * j) + (kf - 1) * PY : OOB;
+    uint32_t ys = act ? yo + PY : OOB;
     double* pa = pab;
     double* pb = pab + SR * T1;
     const double* t1a = a.bt.ptr[C == 0 ? (mv ? BM_N : BK_N) : BM_C];
@@ -829,7 +873,6 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
     const double* k2t = a.bt.ptr[C == 1 ? BK_N : BT_C];
     const double* ta = a.bt.ptr[C == 2 ? (mv ? BM_N : BK_N) : BM_C];
     const double* tb = a.bt.ptr[C == 2 ? BM_N : BT_C];
-    const double* x = a.u[C] + (long long)r * a.su;
     // byte offsets of this thread's pairs of the staged plane (OOB outside the
     // component and in the padding); drop: pairs whose second value lies past
     // the end of its row
@@ -841,45 +884,41 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
         const int rr = idx / PR, cc = 2 * (idx - rr * PR);
         const int jj = j0 - W2 + rr, ii = i0 - WE + cc;
         const bool ok = idx < SR * PR && jj >= 0 && jj < n2 && ii >= 0 && ii < n1;
-        so[s] = ok ? 8u * (jj * n1 + ii) : OOB;
+        so[s] = ok ? 8u * (jj * n1 + ii) + (uint32_t)(k0 - W3 - kb) * PY : OOB;
         if (ok && ii + 1 >= n1) drop |= 1u << s;
     }
     const bool edge = (n1 & 1) && i0 - WE + SW > n1;  // uniform: some pair is dropped
-    // The planes a step touches, as byte addresses advanced by one plane per
-    // step (one 64-bit add each instead of a product per plane); a plane
-    // outside the field gets a zero-size resource, so its address, which may
-    // lie outside the field, is never dereferenced.
-    const uint64_t PY = 8ull * (uint64_t)plane, PW = 8ull * (uint64_t)wplane;
-    auto addr = [](const double* base, long long elems) {
-        return reinterpret_cast<uint64_t>(base) + (uint64_t)(elems * 8);
-    };
-    auto ptr = [](uint64_t a) { return reinterpret_cast<const double*>(a); };
-    auto fetch_x = [&](int kk, uint64_t ax, double* slot) {
-        const bool kin = kk >= 0 && kk < n3;
-        const auto rx = make_rsrc(ptr(ax), kin ? YB : 0u);
+    auto fetch_x = [&](double* slot) {  // the next plane
         double* base = slot + 128 * wave;
 #pragma unroll
-        for (int s = 0; s < ND; ++s)
+        for (int s = 0; s < ND; ++s) {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_vptr)(base + 2 * s * NT), 16, so[s],
                                                      0, 0, 0);
+            so[s] += PY;
+        }
     };
-    // w at the point and its +1 neighbour and the source, for output plane k
-    // (C == 2: the neighbour becomes the next plane's point)
-    auto fetch_out = [&](int k, uint64_t aw, uint64_t as, double& w0, double& w1, double& sd) {
-        const bool kin = k >= 0 && k < n3;
+    // w at the point and its +1 neighbour and the source, for the next output
+    // plane (C == 2: the neighbour becomes the next plane's point)
+    auto fetch_out = [&](double& w0, double& w1, double& sd) {
         if constexpr (C == 0) {
-            const Pair w = bload2(make_rsrc(ptr(aw), kin ? WBm : 0u), wo);
+            const Pair w = bload2(rw, wo);
             w0 = w.a;
             w1 = w.b;
+            wo += PW;
         } else if constexpr (C == 1) {
-            const auto rw = make_rsrc(ptr(aw), kin ? WBm : 0u);
             w0 = bload(rw, wo);
             w1 = bload(rw, wo1);
+            wo += PW;
+            wo1 += PW;
         } else {
             w0 = w1;
-            w1 = bload(make_rsrc(ptr(aw + PW), k + 1 >= 0 && k + 1 < nM ? WBm : 0u), wo);
+            w1 = bload(rw, wo1);
+            wo1 += PW;
         }
-        if (has_src) sd = bload(make_rsrc(ptr(as), kin ? YB : 0u), yo);
+        if (has_src) {
+            sd = bload(rs, ys);
+            ys += PY;
+        }
     };
     double ca[2 * W1 + 1], cb[2 * W1 + 1], cm[2 * W2 + 1], ck[2 * W2 + 1];
     load_band_row<W1>(t1a, i, i < n1, ca);
@@ -890,19 +929,12 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
     wa.clear();
     wb.clear();
     double fw0 = 0.0, fw1 = 0.0, fsd = 0.0;
-    fetch_x(k0 - W3, addr(x, plane * (k0 - W3)), s0);
-    fetch_x(k0 - W3 + 1, addr(x, plane * (k0 - W3 + 1)), s1);
+    fetch_x(s0);
+    fetch_x(s1);
     // (C == 2: w of output plane k0 arrives as a neighbour, W3 >= 1 steps later)
-    fetch_out(k0 - 2 * W3, addr(wv, wplane * (k0 - 2 * W3)), addr(sv, plane * (k0 - 2 * W3)), fw0,
-              fw1, fsd);
+    fetch_out(fw0, fw1, fsd);
     int pk = -1;
     double pv = 0.0;
-    // at the first step kk = k0 - W3: x plane kk + 2, output plane kk - W3 - 1,
-    // coupling and source planes kk - W3 + 1
-    uint64_t ax = addr(x, plane * (k0 - W3 + 2));
-    uint64_t ay = addr(y, plane * (k0 - 2 * W3 - 1));
-    uint64_t aw = addr(wv, wplane * (k0 - 2 * W3 + 1));
-    uint64_t as = addr(sv, plane * (k0 - 2 * W3 + 1));
     // one step: wait for plane kk (slot cur), start plane kk + 2 into the
     // slot plane kk - 1 used, store the pending output, process plane kk
     auto step = [&](int kk, double* cur, double* nxt) {
@@ -915,11 +947,10 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
             for (int s = 0; s < ND; ++s)
                 if (drop >> s & 1) cur[2 * (threadIdx.x + s * NT) + 1] = 0.0;
         lds_barrier();
-        fetch_x(kk + 2, ax, nxt);
-        ax += PY;
+        fetch_x(nxt);
         // the pending output (plane kk - W3 - 1, if it is one)
-        bstore(make_rsrc(ptr(ay), pk >= 0 ? YB : 0u), yo, pv);
-        ay += PY;
+        bstore(ry, pk >= 0 ? yo : OOB, pv);
+        yo += PY;
         // direction 1 over rows g, g + T2, ... (unrolled: a loop would make the
         // compiler wait for every load into LDS at its header)
 #pragma unroll
@@ -927,26 +958,32 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
             const int rr = g + m * T2;
             if (rr < SR) {
                 double sa = 0.0, sb = 0.0;
-#pragma unroll
-                for (int t = 0; t <= 2 * W1; ++t) {
-                    const double xv = cur[rr * SW + c + t + WE - W1];
-                    sa += ca[t] * xv;
-                    sb += cb[t] * xv;
-                }
+                band_pass<FIRST, 2 * W1 + 1>(
+                    [&](int t) { return cur[rr * SW + c + t + WE - W1]; },
+                    [&](int t, double xv) {
+                        sa += ca[t] * xv;
+                        sb += cb[t] * xv;
+                    });
                 pa[rr * T1 + c] = sa;
                 pb[rr * T1 + c] = sb;
             }
         }
         lds_barrier();
-        double am = 0.0, ak = 0.0, bm = 0.0, bk = 0.0;
-#pragma unroll
-        for (int t = 0; t <= 2 * W2; ++t) {
-            const double va = pa[(g + t) * T1 + c], vb = pb[(g + t) * T1 + c];
-            am += cm[t] * va;
-            ak += ck[t] * va;
-            bm += cm[t] * vb;
-            bk += ck[t] * vb;
+        const int k = kk - W3;
+        double ra[2 * W3 + 1], rb[2 * W3 + 1];
+        if (FIRST) {
+            load_uniform_row<W3>(ta, min(max(k, 0), n3 - 1), ra);
+            load_uniform_row<W3>(tb, min(max(k, 0), n3 - 1), rb);
         }
+        double am = 0.0, ak = 0.0, bm = 0.0, bk = 0.0;
+        band_pass<FIRST, 2 * W2 + 1>(
+            [&](int t) { return Pair{pa[(g + t) * T1 + c], pb[(g + t) * T1 + c]}; },
+            [&](int t, Pair v) {
+                am += cm[t] * v.a;
+                ak += ck[t] * v.a;
+                bm += cm[t] * v.b;
+                bk += ck[t] * v.b;
+            });
         double ga, gb = 0.0;
         if (mv) {
             ga = am;
@@ -962,24 +999,24 @@ __device__ void vel_component_dma(const OpArgs& a, const Fields& out, const Fiel
         }
         wa.push(ga);
         wb.push(gb);
-        const int k = kk - W3;
         pk = (k >= k0 && k < kend) ? k : -1;
-        if (pk >= 0) {
+        if (FIRST) {
+            const double sa = wa.dot(ra), sb = wb.dot(rb);
+            pv = alpha * (mv ? sa : a.nu * (sa + sb) + (fw0 - fw1)) + beta * fsd;
+        } else if (pk >= 0) {
             double v;
             if (mv) v = wa.dot(ta + k * (2 * W3 + 1));
             else v = a.nu * (wa.dot(ta + k * (2 * W3 + 1)) + wb.dot(tb + k * (2 * W3 + 1))) + (fw0 - fw1);
             pv = alpha * v + beta * fsd;
         }
-        fetch_out(k + 1, aw, as, fw0, fw1, fsd);
-        aw += PW;
-        as += PY;
+        fetch_out(fw0, fw1, fsd);
     };
     for (int kk = k0 - W3; kk < kend + W3; kk += 3) {
         step(kk, s0, s2);
         step(kk + 1, s1, s0);
         step(kk + 2, s2, s1);
     }
-    if (pk >= 0) bstore(make_rsrc(y + plane * pk, YB), yo, pv);
+    if (pk >= 0) bstore(ry, yo, pv);
     // no load into LDS may outlive the workgroup
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
@@ -1652,7 +1689,9 @@ static hipError_t run_operator(hp_ctx* c, OpMode mode, const Fields& in, const F
     a.ntile1 = (nM + T1 - 1) / T1;
     a.ntile2 = (nM + T2 - 1) / T2;
     const OpShape sh = op_shape(c, nrhs);
-    a.kchunk = std::max(1, std::min(sh.kchunk, nM));
+    // (the streaming kernels' offsets span kchunk + 4 p + 16 planes below 2^31 bytes)
+    const long long kmax = (1LL << 31) / (8LL * nM * nM) - 4 * P - 16;
+    a.kchunk = (int)std::max(1LL, std::min<long long>({sh.kchunk, nM, kmax}));
     a.comp_fast = sh.comp_fast;
     Fields s = src ? *src : out;
     if (!src) beta = 0.0;
