@@ -554,8 +554,10 @@ struct LineArgs {
     double omega;     // damping factor of P_0^{-1} (1: the plain base preconditioner)
     double pscale;    // the pressure's product is multiplied by this
     FieldIO io[2][4];
-    // FP64 output: partial sums of (stored pressure) . dw per tile to
-    // dpart[r * dp_stride + tile]
+    // FP64 output: partial sums of (stored pressure) . dw per tile, or per 16
+    // columns (dp_cols: the same sums for tiles of 16 and of 32), to
+    // dpart[r * dp_stride + index]
+    int dp_cols;
     double* dpart;
     long long dp_stride;
 };
@@ -823,7 +825,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_line(LineArgs a, FDTables<T> t
     const bool dot = std::is_same<TO, double>::value && pres && a.dpart != nullptr;
     const double* dw = dot ? io.dw + (long long)r * io.sout + ofs : nullptr;
     const double ps = pres ? a.pscale : 1.0;
-    double sum = 0.0;
+    double sum[CT] = {};
 #pragma unroll
     for (int q = 0; q < U; ++q) {
         const int u = tile_u(q);
@@ -868,15 +870,28 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_line(LineArgs a, FDTables<T> t
                     TO s = pres ? (TO)(ps * (double)z[h]) : (TO)z[h];
                     if (add) s += yv[i][h];
                     bstore(y + ro[i][h], o[i][h], s);
-                    if (dot) sum += o[i][h] != OOB ? (double)s * wv[i][h] : 0.0;
+                    if (dot) sum[c] += o[i][h] != OOB ? (double)s * wv[i][h] : 0.0;
                 }
             }
         }
     }
     if (dot) {
-        __syncthreads();
-        const double s = wg_sum(sum, reinterpret_cast<double*>(smem_raw));
-        if (threadIdx.x == 0) a.dpart[(long long)r * a.dp_stride + w.c] = s;
+        double* red = reinterpret_cast<double*>(smem_raw);
+        double* part = a.dpart + (long long)r * a.dp_stride;
+        if (!a.dp_cols) {
+            for (int c = 1; c < CT; ++c) sum[0] += sum[c];
+            __syncthreads();
+            const double s = wg_sum(sum[0], red);
+            if (threadIdx.x == 0) part[w.c] = s;
+            return;
+        }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            __syncthreads();
+            const double s = wg_sum(sum[c], red);
+            const int o = CT * w.c + c;
+            if (threadIdx.x == 0 && o < a.dp_stride) part[o] = s;
+        }
     }
 }
 
@@ -1218,6 +1233,7 @@ hipError_t run_P0(hp_ctx* c, const FDTables<T>& t, const P0Set* sets, int nsets,
         la.io[0][3].dw = qdot->with + c->off[3];
         la.dpart = qdot->part;
         la.dp_stride = fd_dot_count(c, false);
+        la.dp_cols = !fd_plan_lines(plan);
     }
     if (vel && pres && std::is_same<T, double>::value) {
         if ((e = launch_lines<T, T, double, SPLIT, true>(st, la, t, ct, nsets)) != hipSuccess) return e;
@@ -1382,8 +1398,10 @@ int fd_plan_in_use(const hp_ctx* c, int precision) {
 long long fd_dot_count(const hp_ctx* c, bool vel) {
     const long long nM = c->nM;
     if (vel) return 3 * nM;
-    // workgroups of the pressure's mode-3 launch
-    const int ct = line_ct(fd_plan_in_use(c, HP_PREC_FP64), c->nM);
+    // 16 columns each for the plane plans, so that a solve does not depend on
+    // which of them the tuner took; otherwise the mode-3 launch's workgroups
+    const int plan = fd_plan_in_use(c, HP_PREC_FP64);
+    const int ct = fd_plan_lines(plan) ? line_ct(plan, c->nM) : 1;
     return (nM * nM + 16 * ct - 1) / (16 * ct);
 }
 

@@ -172,7 +172,8 @@ hipError_t fd_init_attributes();
 // the last launch also writes partial sums of (final output) . dot->with to
 // dot->part[r * fd_dot_count(c, vel) + i] -- velocity: one per (field,
 // i3-plane), i = f nM + k (slots of planes a field lacks are never written:
-// kept zero by the caller); pressure: one per workgroup of its mode-3 launch.
+// kept zero by the caller); pressure: one per workgroup of its mode-3 launch,
+// or per 16 columns of it (plane plans).
 // comb (may be null): the pressure's input is ca in + cb comb->b + cc comb->c,
 // formed where the first launch reads it (as k_axpbypcz would).
 struct FdDot {
@@ -206,7 +207,7 @@ long long fd_dot_capacity(const hp_ctx* c, bool vel);
 // workgroup's LDS (directions up to 128), mode 3 on 32 columns per workgroup;
 // FD_PLAN_SMALL = the same with 16 columns (twice the workgroups, for small
 // meshes); FD_PLAN_PASSES and FD_PLAN_LINES = one direction per pass, up to
-// 128 and at any length (the only plan beyond; the tuner takes the former).
+// 128 and at any length (the only plan beyond; not tuned up to there).
 // The plane plans agree with each other bit for bit, and so do the two
 // others; between them the folds are rounded in another order.  Whether plan
 // `plan` exists for this mesh and `precision`, and the plan launch_P0 uses

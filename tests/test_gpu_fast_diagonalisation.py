@@ -132,3 +132,20 @@ def test_solve_with_direction_passes(dev):
     assert float((xa - xb).abs().max() / xa.abs().max()) <= 1e-10
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("E,p,krylov", [(6, 3, "minres"), (17, 2, "minres"), (31, 4, "minres"),
+                                        (40, 3, "minres"), (100, 2, "minres"), (9, 3, "fgmres")])
+def test_solve_does_not_depend_on_the_plane_plan(dev, E, p, krylov):
+    """The two plane plans (tiles of 32 and of 16 columns in mode 3) give the
+    same bits, and so do the dots that their launches leave for MINRES: equal
+    solutions and counts, whichever the tuner takes."""
+    from paper_2311_06926_amd.solver import Solver
+    out = []
+    for plan in (1, 9):
+        s = Solver(E, p, 1.0, iters=1, krylov=krylov, max_rhs=2, fd_plan=plan, autotune=False)
+        x, info = s.solve(s.build_rhs([1.0, 0.7]), 1e-8)
+        out.append((x, list(info.iters_per_rhs[:2])))
+        s.close()
+    assert out[0][1] == out[1][1]
+    assert torch.equal(out[0][0], out[1][0])
