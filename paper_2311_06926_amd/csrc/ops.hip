@@ -166,11 +166,26 @@ __device__ __forceinline__ void band_pass(R read, F use) {
     }
 }
 
-template <int W>
-__device__ __forceinline__ void load_band_row(const double* tab, int row, bool ok,
-                                              double (&c)[2 * W + 1]) {
+
+// Direction 1 of the all-planes kernels: rows g, g + T2, .. of all staged
+// planes as one list, B rows at a time with their reads before their uses
+// (read(row, t), use(b, t, value), done(b, row)).
+template <int ROWS, int N, int B, typename R, typename F, typename D>
+__device__ __forceinline__ void band_rows(int g, R read, F use, D done) {
+    for (int m0 = g; m0 < ROWS; m0 += B * T2) {
+        decltype(read(0, 0)) v[B][N];
 #pragma unroll
-    for (int t = 0; t <= 2 * W; ++t) c[t] = ok ? tab[row * (2 * W + 1) + t] : 0.0;
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int t = 0; t < N; ++t) v[b][t] = read(min(m0 + b * T2, ROWS - 1), t);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+#pragma unroll
+            for (int t = 0; t < N; ++t) use(b, t, v[b][t]);
+            if (m0 + b * T2 < ROWS) done(b, m0 + b * T2);
+        }
+    }
 }
 
 // ---- memory access ---------------------------------------------------------------------
@@ -223,6 +238,29 @@ __device__ __forceinline__ Pair bload2(__amdgpu_buffer_rsrc_t r, uint32_t off) {
 __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, uint32_t off, double v) {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, 0);
+}
+// This lane's band row (zeros unless ok).
+template <int W>
+__device__ __forceinline__ void load_band_row(const double* tab, int row, bool ok,
+                                              double (&c)[2 * W + 1]) {
+#pragma unroll
+    for (int t = 0; t <= 2 * W; ++t) c[t] = ok ? tab[row * (2 * W + 1) + t] : 0.0;
+}
+// Two values a load, for the all-planes kernels, whose few waves wait for it
+// (in the streaming kernels, where it overlaps the first planes, single values
+// were faster: K at 45^3, degree 4, 24.6 us, pairs 25.2).
+template <int W>
+__device__ __forceinline__ void load_band_pairs(const double* tab, int row, bool ok,
+                                                double (&c)[2 * W + 1]) {
+    const auto r = make_rsrc(tab, 0x7fffffffu);  // (row is within the table)
+    const uint32_t o = ok ? 8u * (uint32_t)(row * (2 * W + 1)) : OOB;
+#pragma unroll
+    for (int t = 0; t < 2 * W; t += 2) {
+        const Pair v = bload2(r, o + 8u * t);
+        c[t] = v.a;
+        c[t + 1] = v.b;
+    }
+    c[2 * W] = bload(r, o + 16u * W);
 }
 
 // ---- pressure chain --------------------------------------------------------------------
@@ -418,14 +456,19 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
 // LDS, directions 1 and 2 are one pass each over all planes and direction 3
 // reads the thread's column from registers.  Same operation sequence per
 // output as k_pres (bitwise-identical results), every mode k_pres serves.
-// KC = kchunk (2 or 4), degrees 2 and 3.
+// KC = kchunk (2 or 4), degrees 2 and 3.  Few waves run and each is a chain of
+// latencies, so loads come in pairs (half as many to issue), the rows of
+// direction 1 are one list over all planes, three at a time, and a pass's LDS
+// reads stand before its uses: with the same in k_vel_all K at 8^3, degree 2,
+// 10.0 -> 8.7 us, at 16^3 11.3 -> 8.8, at 32^3, degree 3, 14.4 -> 12.1.
 template <int P, int KC>
 __global__ __launch_bounds__(NT) void k_pres_all(OpArgs a, double* yp, long long syp, PresJob job) {
     constexpr int W = P - 1;
-    constexpr int SW = T1 + 2 * W, SR = T2 + 2 * W;
-    constexpr int NS = (SR * SW + NT - 1) / NT;
+    constexpr int WE = (W + 1) & ~1;  // pairs start at even columns
+    constexpr int SW = T1 + 2 * WE, SR = T2 + 2 * W, PR = SW / 2;
+    constexpr int NS = (SR * PR + NT - 1) / NT;
     constexpr int NP = KC + 2 * W;  // planes k0 - W .. k0 + KC + W - 1
-    extern __shared__ double lds_p[];
+    extern __shared__ __align__(16) double lds_p[];
     double* gs = lds_p;                  // NP x SR x SW
     double* zs = gs + NP * SR * SW;
     double* pg = zs + NP * SR * SW;      // NP x SR x T1
@@ -459,90 +502,103 @@ __global__ __launch_bounds__(NT) void k_pres_all(OpArgs a, double* yp, long long
     const long long P1 = (long long)nN * nM;
     const long long P2 = (long long)nM * nN;
     const long long P3 = (long long)nM * nM;
-    const uint32_t B1 = use_u ? 8u * (uint32_t)P1 : 0u, B2 = use_u ? 8u * (uint32_t)P2 : 0u;
-    const uint32_t B3 = use_u ? 8u * (uint32_t)P3 : 0u, BP = use_p ? 8u * (uint32_t)P3 : 0u;
-    uint32_t oa[NS], ob[NS], oc[NS], od[NS], oe[NS];
+    const uint32_t Q1 = 8u * (uint32_t)P1, Q2 = 8u * (uint32_t)P2, Q3 = 8u * (uint32_t)P3;
+    const int kb = max(0, k0 - W - 1), km = NP + 2;
+    const auto r1 = planes_rsrc(u1, P1, kb, nM, km, use_u);
+    const auto r2 = planes_rsrc(u2, P2, kb, nM, km, use_u);
+    const auto r3 = planes_rsrc(u3, P3, kb, nN, km, use_u);
+    const auto rp = planes_rsrc(pp, P3, kb, nM, km, use_p);
+    uint32_t oa[NS], ob[NS], oc[NS], od[NS], oe[NS];  // as in k_pres
+    bool v1[NS], v2[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int idx = threadIdx.x + s * NT;
-        const int rr = idx / SW, cc = idx - rr * SW;
-        const int jj = j0 - W + rr, ii = i0 - W + cc;
-        const bool ok = idx < SR * SW && jj >= 0 && jj < nM && ii >= 0 && ii < nM;
-        oa[s] = (ok && ii < nN) ? 8u * (nN * jj + ii) : OOB;
-        ob[s] = (ok && ii >= 1) ? 8u * (nN * jj + ii - 1) : OOB;
-        oc[s] = (ok && jj < nN) ? 8u * (ii + nM * jj) : OOB;
-        od[s] = (ok && jj >= 1) ? 8u * (ii + nM * (jj - 1)) : OOB;
-        oe[s] = ok ? 8u * (ii + nM * jj) : OOB;
+        const int rr = idx / PR, cc = 2 * (idx - rr * PR);
+        const int jj = j0 - W + rr, ii = i0 - WE + cc;
+        const bool ok = idx < SR * PR && jj >= 0 && jj < nM && ii >= 0 && ii < nM;
+        const uint32_t kf = (uint32_t)(k0 - W - kb);
+        oa[s] = (ok && ii < nN) ? 8u * (nN * jj + ii) + kf * Q1 : OOB;
+        ob[s] = (ok && ii >= 1) ? 8u * (nN * jj + ii - 1) + kf * Q1 : OOB;
+        oc[s] = (ok && jj < nN) ? 8u * (ii + nM * jj) + kf * Q2 : OOB;
+        od[s] = (ok && jj >= 1) ? 8u * (ii + nM * (jj - 1)) + kf * Q2 : OOB;
+        oe[s] = ok ? 8u * (ii + nM * jj) + kf * Q3 : OOB;
+        v1[s] = ii + 1 < nN;
+        v2[s] = ii + 1 < nM;
     }
     // every load of the workgroup first: u3 from plane k0 - W - 1 on, the
     // other values from plane k0 - W on
-    double v1a[NP][NS], v1b[NP][NS], v2c[NP][NS], v2d[NP][NS], vp[NP][NS], v3[NP + 1][NS];
+    struct Raw {
+        Pair u1, u2, u2m, p;
+        double u1m;
+    };
+    Raw raw[NP][NS];
+    Pair v3[NP + 1][NS];
 #pragma unroll
-    for (int q = 0; q <= NP; ++q) {
-        const int kk = k0 - W - 1 + q;
-        const bool k3in = kk >= 0 && kk < nN;
-        const auto r3 = make_rsrc(u3 + P3 * (k3in ? kk : 0), k3in ? B3 : 0u);
+    for (int s = 0; s < NS; ++s) {
+        v3[0][s] = bload2(r3, oe[s] == OOB ? OOB : oe[s] - Q3);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) v3[q][s] = bload(r3, oe[s]);
-    }
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
-        const int kk = k0 - W + q;
-        const bool kin = kk >= 0 && kk < nM;
-        const int kc = kin ? kk : 0;
-        const auto r1 = make_rsrc(u1 + P1 * kc, kin ? B1 : 0u);
-        const auto r2 = make_rsrc(u2 + P2 * kc, kin ? B2 : 0u);
-        const auto rp = make_rsrc(pp + P3 * kc, kin ? BP : 0u);
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            v1a[q][s] = bload(r1, oa[s]);
-            v1b[q][s] = bload(r1, ob[s]);
-            v2c[q][s] = bload(r2, oc[s]);
-            v2d[q][s] = bload(r2, od[s]);
-            vp[q][s] = bload(rp, oe[s]);
+        for (int q = 0; q < NP; ++q) {
+            Raw& v = raw[q][s];
+            v.u1 = bload2(r1, oa[s] + q * Q1);
+            v.u1m = bload(r1, ob[s] + q * Q1);
+            v.u2 = bload2(r2, oc[s] + q * Q2);
+            v.u2m = bload2(r2, od[s] + q * Q2);
+            v3[q + 1][s] = bload2(r3, oe[s] + q * Q3);
+            v.p = bload2(rp, oe[s] + q * Q3);
         }
     }
     double c1[2 * W + 1], c2[2 * W + 1];
-    load_band_row<W>(tm, i, i < nM, c1);
-    load_band_row<W>(tm, j, j < nM, c2);
+    load_band_pairs<W>(tm, i, i < nM, c1);
+    load_band_pairs<W>(tm, j, j < nM, c2);
     const uint32_t oo = act ? 8u * (i + nM * j) : OOB;
 #pragma unroll
     for (int q = 0; q < NP; ++q)
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int idx = threadIdx.x + s * NT;
-            if (idx < SR * SW) {
-                const double gv = (v1a[q][s] - v1b[q][s]) + (v2c[q][s] - v2d[q][s]) +
-                                  (v3[q + 1][s] - v3[q][s]);
-                gs[q * SR * SW + idx] = gv;
-                zs[q * SR * SW + idx] = zg * gv + vp[q][s];
+            const Raw& v = raw[q][s];
+            const Pair &n3 = v3[q + 1][s], &o3 = v3[q][s];
+            const double u1b = v1[s] ? v.u1.b : 0.0;
+            if (idx < SR * PR) {
+                const double ga = (v.u1.a - v.u1m) + (v.u2.a - v.u2m.a) + (n3.a - o3.a);
+                const double gb = (u1b - v.u1.a) + (v.u2.b - v.u2m.b) + (n3.b - o3.b);
+                const double zb = zg * gb + v.p.b;
+                const int o = q * SR * SW + 2 * idx;
+                *reinterpret_cast<double2*>(gs + o) = double2{ga, v2[s] ? gb : 0.0};
+                *reinterpret_cast<double2*>(zs + o) = double2{zg * ga + v.p.a, v2[s] ? zb : 0.0};
             }
         }
     __syncthreads();
-    for (int q = 0; q < NP; ++q) {
-        const double* gq = gs + q * SR * SW;
-        const double* zq = zs + q * SR * SW;
-        for (int rr = g; rr < SR; rr += T2) {
-            double sg = 0.0, sz = 0.0;
-#pragma unroll
-            for (int t = 0; t <= 2 * W; ++t) {
-                sg += c1[t] * gq[rr * SW + c + t];
-                sz += c1[t] * zq[rr * SW + c + t];
-            }
-            pg[q * SR * T1 + rr * T1 + c] = sg;
-            pz[q * SR * T1 + rr * T1 + c] = sz;
-        }
-    }
+    constexpr int B = 3;
+    double sg1[B], sz1[B];
+    band_rows<NP * SR, 2 * W + 1, B>(
+        g,
+        [&](int row, int t) {
+            const int o = row * SW + c + t + WE - W;
+            return Pair{gs[o], zs[o]};
+        },
+        [&](int q, int t, Pair v) {
+            sg1[q] = (t == 0 ? 0.0 : sg1[q]) + c1[t] * v.a;
+            sz1[q] = (t == 0 ? 0.0 : sz1[q]) + c1[t] * v.b;
+        },
+        [&](int q, int row) {
+            pg[row * T1 + c] = sg1[q];
+            pz[row * T1 + c] = sz1[q];
+        });
     __syncthreads();
     double sgv[NP], szv[NP];
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
         double sg = 0.0, sz = 0.0;
-#pragma unroll
-        for (int t = 0; t <= 2 * W; ++t) {
-            sg += c2[t] * pg[q * SR * T1 + (g + t) * T1 + c];
-            sz += c2[t] * pz[q * SR * T1 + (g + t) * T1 + c];
-        }
+        band_pass<true, 2 * W + 1>(
+            [&](int t) {
+                const int o = (q * SR + g + t) * T1 + c;
+                return Pair{pg[o], pz[o]};
+            },
+            [&](int t, Pair v) {
+                sg += c2[t] * v.a;
+                sz += c2[t] * v.b;
+            });
         sgv[q] = sg;
         szv[q] = sz;
     }
@@ -567,7 +623,7 @@ __global__ __launch_bounds__(NT) void k_pres_all(OpArgs a, double* yp, long long
 
 template <int P, int KC>
 constexpr int pres_all_lds_doubles() {
-    constexpr int W = P - 1, SW = T1 + 2 * W, SR = T2 + 2 * W, NP = KC + 2 * W;
+    constexpr int W = P - 1, SW = T1 + 2 * ((W + 1) & ~1), SR = T2 + 2 * W, NP = KC + 2 * W;
     return NP * (2 * SR * SW + 2 * SR * T1);
 }
 
@@ -1073,8 +1129,9 @@ __device__ void vel_component_all(const OpArgs& a, const Fields& out, const Fiel
     constexpr int W1 = (C == 0) ? P : P - 1;
     constexpr int W2 = (C == 1) ? P : P - 1;
     constexpr int W3 = (C == 2) ? P : P - 1;
-    constexpr int SW = T1 + 2 * W1, SR = T2 + 2 * W2;
-    constexpr int NS = (SR * SW + NT - 1) / NT;
+    constexpr int WE = (W1 + 1) & ~1;  // pairs start at even columns
+    constexpr int SW = T1 + 2 * WE, SR = T2 + 2 * W2, PR = SW / 2;
+    constexpr int NS = (SR * PR + NT - 1) / NT;
     constexpr int NP = KC + 2 * W3;  // staged planes k0 - W3 .. k0 + KC + W3 - 1
     const int n1 = a.dims[C][0], n2 = a.dims[C][1], n3 = a.dims[C][2];
     if (i0 >= n1 || j0 >= n2 || k0 >= n3) return;
@@ -1090,40 +1147,52 @@ __device__ void vel_component_all(const OpArgs& a, const Fields& out, const Fiel
     double* y = out.f[C] + (long long)r * out.stride[C];
     const bool has_src = beta != 0.0;
     const double* sv = has_src ? src.f[C] + (long long)r * src.stride[C] : y;
-    const uint32_t SB = has_src ? YB : 0u;
+    const uint32_t PY = YB, PW = WB;
     const uint32_t wo = act ? 8u * (i + nM * j) : OOB;
-    const uint32_t wo1 = act ? wo + (C == 0 ? 8u : C == 1 ? 8u * nM : 0u) : OOB;
     const uint32_t yo = act ? 8u * (i + n1 * j) : OOB;
-    const double* x = a.u[C] + (long long)r * a.su;
-    uint32_t so[NS];  // staging byte offsets, OOB outside the component
+    const int kb = max(0, k0 - W3);
+    const auto rx = planes_rsrc(a.u[C] + (long long)r * a.su, plane, kb, n3, NP + 1);
+    const auto rw = planes_rsrc(wv, wplane, k0, nM, KC + 1);
+    const auto rs = planes_rsrc(sv, plane, k0, n3, KC, has_src);
+    uint32_t so[NS];  // staging byte offsets of pairs, OOB outside the component
+    bool v2[NS];      // the second value lies in the row
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int idx = threadIdx.x + s * NT;
-        const int rr = idx / SW, cc = idx - rr * SW;
-        const int jj = j0 - W2 + rr, ii = i0 - W1 + cc;
-        const bool ok = idx < SR * SW && jj >= 0 && jj < n2 && ii >= 0 && ii < n1;
-        so[s] = ok ? 8u * (jj * n1 + ii) : OOB;
+        const int rr = idx / PR, cc = 2 * (idx - rr * PR);
+        const int jj = j0 - W2 + rr, ii = i0 - WE + cc;
+        const bool ok = idx < SR * PR && jj >= 0 && jj < n2 && ii >= 0 && ii < n1;
+        so[s] = ok ? 8u * (jj * n1 + ii) + (uint32_t)(k0 - W3 - kb) * PY : OOB;
+        v2[s] = ii + 1 < n1;
     }
     // every load of the workgroup, issued before the first is used
-    double xr[NP][NS];
+    Pair xr[NP][NS];
 #pragma unroll
-    for (int q = 0; q < NP; ++q) {
-        const int kk = k0 - W3 + q;
-        const bool kin = kk >= 0 && kk < n3;
-        const auto rx = make_rsrc(x + plane * (kin ? kk : 0), kin ? YB : 0u);
+    for (int q = 0; q < NP; ++q)
 #pragma unroll
-        for (int s = 0; s < NS; ++s) xr[q][s] = bload(rx, so[s]);
-    }
-    double w0[KC], w1[KC], sd[KC];
+        for (int s = 0; s < NS; ++s) xr[q][s] = bload2(rx, so[s] + q * PY);
+    // (planes past the chunk are read where the mesh has them, and not used)
+    double w0[KC + 1], w1[KC], sd[KC];
 #pragma unroll
     for (int o = 0; o < KC; ++o) {
-        const int k = k0 + o;
-        const bool on = k < kend;
-        const int kc = on ? k : k0;
-        w0[o] = bload(make_rsrc(wv + wplane * kc, on ? WB : 0u), wo);
-        w1[o] = bload(make_rsrc(wv + wplane * (C == 2 ? kc + 1 : kc), on ? WB : 0u), wo1);
-        sd[o] = bload(make_rsrc(sv + plane * kc, on ? SB : 0u), yo);
+        if constexpr (C == 0) {
+            const Pair w = bload2(rw, wo + o * PW);
+            w0[o] = w.a;
+            w1[o] = w.b;
+        } else {
+            w0[o] = bload(rw, wo + o * PW);
+            if (C == 1) w1[o] = bload(rw, wo + o * PW + 8u * nM);
+        }
+        sd[o] = 0.0;
     }
+    if (C == 2) {
+        w0[KC] = bload(rw, wo + KC * PW);
+#pragma unroll
+        for (int o = 0; o < KC; ++o) w1[o] = w0[o + 1];
+    }
+    if (has_src)
+#pragma unroll
+        for (int o = 0; o < KC; ++o) sd[o] = bload(rs, yo + o * PY);
     const double* t1a = a.bt.ptr[C == 0 ? BK_N : BM_C];
     const double* t1b = a.bt.ptr[C == 0 ? BM_N : BT_C];
     const double* m2t = a.bt.ptr[C == 1 ? BM_N : BM_C];
@@ -1131,10 +1200,10 @@ __device__ void vel_component_all(const OpArgs& a, const Fields& out, const Fiel
     const double* ta = a.bt.ptr[C == 2 ? BK_N : BM_C];
     const double* tb = a.bt.ptr[C == 2 ? BM_N : BT_C];
     double ca[2 * W1 + 1], cb[2 * W1 + 1], cm[2 * W2 + 1], ck[2 * W2 + 1];
-    load_band_row<W1>(t1a, i, i < n1, ca);
-    load_band_row<W1>(t1b, i, i < n1, cb);
-    load_band_row<W2>(m2t, j, j < n2, cm);
-    load_band_row<W2>(k2t, j, j < n2, ck);
+    load_band_pairs<W1>(t1a, i, i < n1, ca);
+    load_band_pairs<W1>(t1b, i, i < n1, cb);
+    load_band_pairs<W2>(m2t, j, j < n2, cm);
+    load_band_pairs<W2>(k2t, j, j < n2, ck);
     double* xs = lds;                    // NP x SR x SW
     double* pa = xs + NP * SR * SW;      // NP x SR x T1
     double* pb = pa + NP * SR * T1;
@@ -1143,40 +1212,42 @@ __device__ void vel_component_all(const OpArgs& a, const Fields& out, const Fiel
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int idx = threadIdx.x + s * NT;
-            if (idx < SR * SW) xs[q * SR * SW + idx] = xr[q][s];
+            const Pair& v = xr[q][s];
+            if (idx < SR * PR)
+                *reinterpret_cast<double2*>(xs + q * SR * SW + 2 * idx) =
+                    double2{v.a, v2[s] ? v.b : 0.0};
         }
     __syncthreads();
     // direction 1 over the tile rows and halo rows of every plane
-    for (int q = 0; q < NP; ++q) {
-        const double* xq = xs + q * SR * SW;
-        for (int rr = g; rr < SR; rr += T2) {
-            double sa = 0.0, sb = 0.0;
-#pragma unroll
-            for (int t = 0; t <= 2 * W1; ++t) {
-                const double xv = xq[rr * SW + c + t];
-                sa += ca[t] * xv;
-                sb += cb[t] * xv;
-            }
-            pa[q * SR * T1 + rr * T1 + c] = sa;
-            pb[q * SR * T1 + rr * T1 + c] = sb;
-        }
-    }
+    constexpr int B = 3;
+    double sa[B], sb[B];
+    band_rows<NP * SR, 2 * W1 + 1, B>(
+        g, [&](int row, int t) { return xs[row * SW + c + t + WE - W1]; },
+        [&](int q, int t, double v) {
+            sa[q] = (t == 0 ? 0.0 : sa[q]) + ca[t] * v;
+            sb[q] = (t == 0 ? 0.0 : sb[q]) + cb[t] * v;
+        },
+        [&](int q, int row) {
+            pa[row * T1 + c] = sa[q];
+            pb[row * T1 + c] = sb[q];
+        });
     __syncthreads();
     // direction 2 at the thread's point of every plane
     double gav[NP], gbv[NP];
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
-        const double* paq = pa + q * SR * T1;
-        const double* pbq = pb + q * SR * T1;
         double am = 0.0, ak = 0.0, bm = 0.0, bk = 0.0;
-#pragma unroll
-        for (int t = 0; t <= 2 * W2; ++t) {
-            const double va = paq[(g + t) * T1 + c], vb = pbq[(g + t) * T1 + c];
-            am += cm[t] * va;
-            ak += ck[t] * va;
-            bm += cm[t] * vb;
-            bk += ck[t] * vb;
-        }
+        band_pass<true, 2 * W2 + 1>(
+            [&](int t) {
+                const int o = (q * SR + g + t) * T1 + c;
+                return Pair{pa[o], pb[o]};
+            },
+            [&](int t, Pair v) {
+                am += cm[t] * v.a;
+                ak += ck[t] * v.a;
+                bm += cm[t] * v.b;
+                bk += ck[t] * v.b;
+            });
         double ga, gb = 0.0;
         if (C == 0) {
             ga = am + 2.0 * bk;
@@ -1216,7 +1287,7 @@ constexpr int vel_all_lds_doubles() {
     int m = 0;
     for (int C = 0; C < 3; ++C) {
         const int W1 = (C == 0) ? P : P - 1, W2 = (C == 1) ? P : P - 1, W3 = (C == 2) ? P : P - 1;
-        const int SW = T1 + 2 * W1, SR = T2 + 2 * W2, NP = KC + 2 * W3;
+        const int SW = T1 + 2 * ((W1 + 1) & ~1), SR = T2 + 2 * W2, NP = KC + 2 * W3;
         const int d = NP * (SR * SW + 2 * SR * T1);
         m = d > m ? d : m;
     }
@@ -1226,7 +1297,7 @@ constexpr int vel_all_lds_doubles() {
 template <int P, int KC>
 __global__ __launch_bounds__(NT) void k_vel_all(OpArgs a, Fields out, Fields src, double alpha,
                                                 double beta) {
-    extern __shared__ double lds_all[];
+    extern __shared__ __align__(16) double lds_all[];
     int id = xcd_block(blockIdx.x, a.nblocks);
     int comp;
     if (a.comp_fast) {
@@ -1697,7 +1768,15 @@ static hipError_t run_operator(hp_ctx* c, OpMode mode, const Fields& in, const F
     if (!src) beta = 0.0;
     double* yp = out.f[3];
     const long long syp = out.stride[3];
-    const PresLaunch pall = sh.staged ? pres_all_launch(P, a.kchunk) : nullptr;
+    // The all-planes kernels have the shorter chains, the streaming ones move
+    // less: with two pressure chains in a launch the latter win from two
+    // workgroups per CU on (P_1, degree 3, chunks of 4: 32^3 59.2 us against
+    // 63.4, 48^3 90.3 against 84.8, 61^3 101.7 against 96.5), while K alone is
+    // faster all planes at once up to there (21.3 against 22.8).
+    const long long chains =
+        (bt_in ? 2LL : 1LL) * a.ntile1 * a.ntile2 * ((nM + a.kchunk - 1) / a.kchunk) * nrhs;
+    const bool staged = sh.staged && (!bt_in || chains <= 512);
+    const PresLaunch pall = staged ? pres_all_launch(P, a.kchunk) : nullptr;
     const bool pwide = !pall && sh.pwide;
     PresJob job{};
     job.mode = -1;
@@ -1716,7 +1795,7 @@ static hipError_t run_operator(hp_ctx* c, OpMode mode, const Fields& in, const F
         a.ntile1 = (nM + T1 - 1) / T1;  // the velocity kernels' tiles
         a.ntile2 = (nM + T2 - 1) / T2;
     };
-    const VelLaunch vall = (sh.staged && (mode == OP_K || mode == OP_A))
+    const VelLaunch vall = (staged && (mode == OP_K || mode == OP_A))
                                ? vel_all_launch(P, a.kchunk) : nullptr;
     auto vel = [&](int lo, int hi) {
         a.kbase = lo;
