@@ -182,6 +182,24 @@ __device__ __forceinline__ T bload(const T* base, uint32_t off) {
     else
         return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(buffer_at(base), (int)off, 0, 0));
 }
+// Two neighbours of an array of `bytes` bytes; what lies beyond reads as zero.
+template <typename T>
+__device__ __forceinline__ void bload2(const T* base, uint32_t bytes, uint32_t off, T (&v)[2]) {
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), (short)0, (int)bytes,
+                                                     0x00020000);
+    if constexpr (sizeof(T) == 8) {
+        typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+        const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+        v[0] = __builtin_bit_cast(T, (uint64_t)w.x | ((uint64_t)w.y << 32));
+        v[1] = __builtin_bit_cast(T, (uint64_t)w.z | ((uint64_t)w.w << 32));
+    } else {
+        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
+        const unsigned int lo = w.x, hi = w.y;  // (a cast of w.y itself reads w.x)
+        v[0] = __builtin_bit_cast(T, lo);
+        v[1] = __builtin_bit_cast(T, hi);
+    }
+}
 template <typename T>
 __device__ __forceinline__ void bstore(T* base, uint32_t off, T v) {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -380,18 +398,28 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_plane(PlaneArgs a,
             }
         }
     } else {
-        const int n = n1 * n2;
-        for (int base = threadIdx.x; base < n; base += 4 * NTH) {
-            TI v[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) v[g] = x[min(base + g * NTH, n - 1)];
+        // Pairs, four in flight: lanes past the plane repeat its last pair, so
+        // that no load stands in a branch (the compiler moved each there, behind
+        // the wait for the one before: P_0 at 64^3 53.7 -> 52.6 us, FP32 42.6 ->
+        // 41.3).  The row of entry i is exact in FP32:
+        // the quotient's distance from an integer is 1/256 or more.
+        const int n = n1 * n2, np = (n + 1) >> 1;
+        const float rn = 1.0f / (float)n1;
+        for (int base = threadIdx.x; base < np; base += 4 * NTH) {
+            TI v[4][2];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const int idx = base + g * NTH;
-                if (idx < n) {
-                    const int j = idx / n1;
-                    S[j * ld + (idx - j * n1)] = (T)v[g];
-                }
+                const int i = 2 * min(base + g * NTH, np - 1);
+                bload2(x, (uint32_t)sizeof(TI) * n, (uint32_t)sizeof(TI) * i, v[g]);
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int i = 2 * min(base + g * NTH, np - 1);
+                const int j = (int)(((float)i + 0.5f) * rn), c = i - j * n1;
+                const int o0 = j * ld + c, o1 = o0 + (c + 1 < n1 ? 1 : ld - c);
+                const bool two = i + 1 < n;
+                S[o0] = (T)v[g][0];
+                S[two ? o1 : o0] = (T)(two ? v[g][1] : v[g][0]);
             }
         }
     }
