@@ -746,8 +746,11 @@ hp_status minres(hp_ctx* c, const double* b, double* x, int nrhs, double tol, hp
 constexpr int FG_MMAX = 128;
 
 // One Arnoldi step j of FGMRES(m); the updated scalars are also written to
-// the host mirror `mirror` (device address of pinned host memory).
-hipError_t fgmres_iteration(hp_ctx* c, int j, int m, int nrhs, double tol, FgScalars* mirror) {
+// the host mirror `mirror` (device address of pinned host memory).  polled (may
+// be null) is recorded where they are final, before the new basis vector is
+// scaled.
+hipError_t fgmres_iteration(hp_ctx* c, int j, int m, int nrhs, double tol, FgScalars* mirror,
+                            hipEvent_t polled = nullptr) {
     Extra* ex = extra_of(c);
     const long long N = c->N;
     const long long V = N * (long long)c->opts.max_rhs;
@@ -777,6 +780,7 @@ hipError_t fgmres_iteration(hp_ctx* c, int j, int m, int nrhs, double tol, FgSca
     if ((e = fg_rot(c->stream, ex->fsc, ex->fpart, cnt, ex->fH, ex->fcs, ex->fsn, ex->fg, ex->fvs, tol,
                     c->opts.breakdown_tol, j, m, nrhs, mirror)) != hipSuccess)
         return e;
+    if (polled && (e = hipEventRecord(polled, c->stream)) != hipSuccess) return e;
     const double* xs[1] = {w};
     return vec_lincomb(c->stream, N, N, nrhs, 1, xs, ex->fvs, Vn);
 }
@@ -846,6 +850,12 @@ hp_status fgmres(hp_ctx* c, const double* b, double* x, int nrhs, double tol, hp
     double* Zb = Vb + (long long)(m + 1) * V;
     double* w = Zb + (long long)m * V;
     const size_t sbytes = sizeof(FgScalars) * nrhs;
+    // The flags are read one step behind, so that the GPU never waits for the
+    // host, at the price of one step past convergence -- unless the scaling of
+    // the new vector alone, 2^22 entries in 15 us, covers the host's way back:
+    // then the step's own flags are waited for (48^3, degree 2, 32 right-hand
+    // sides: 28 steps of 2.3 ms instead of 29).
+    const bool wait = !graphs && N * (long long)nrhs >= (1LL << 22);
     HIPCHK(vec_dot_partials(c->stream, N, N, b, b, nrhs, ex->fpart));
     HIPCHK(fg_init(c->stream, ex->fsc, ex->fpart, (int)vec_dot_partial_count(N), nrhs));
     // x_0 = 0, or the x passed in (warm start): every cycle starts from b - K x
@@ -876,12 +886,16 @@ hp_status fgmres(hp_ctx* c, const double* b, double* x, int nrhs, double tol, hp
             if (graphs) {
                 HIPCHK(hipGraphLaunch(ex->f_exec[jl], c->stream));
             } else {
-                HIPCHK(fgmres_iteration(c, jl, m, nrhs, tol, ex->dfsc[(jl + 1) & 1]));
+                HIPCHK(fgmres_iteration(c, jl, m, nrhs, tol, ex->dfsc[(jl + 1) & 1],
+                                        ex->mev[(jl + 1) & 1]));
             }
             ++jl;
             ++total;
-            HIPCHK(hipEventRecord(ex->mev[jl & 1], c->stream));
-            if (jl >= 2) {
+            if (graphs) HIPCHK(hipEventRecord(ex->mev[jl & 1], c->stream));
+            if (wait) {
+                HIPCHK(hipEventSynchronize(ex->mev[jl & 1]));
+                stop = all(ex->hfsc[jl & 1], true);
+            } else if (jl >= 2) {
                 HIPCHK(hipEventSynchronize(ex->mev[(jl - 1) & 1]));
                 stop = all(ex->hfsc[(jl - 1) & 1], true);
             }
