@@ -35,7 +35,7 @@ struct Extra {
     // hyper-power temporaries
     double* hv = nullptr;  // 4 velocity vectors x max_rhs
     int pv_slot = 0;       // hv slot of the P_V Richardson residual (0: V block, 3: Q block)
-    // the Q block of P_k runs beside the V block: a second stream, fork/join
+    // the Q block of P_k (k > 1, eq. Pcq2, PCG) runs beside the V block: a second stream, fork/join
     // events and a second operator / fast-diagonalisation workspace
     hipStream_t side = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
@@ -342,7 +342,8 @@ hipError_t apply_PQ2(hp_ctx* c, int q, int level, const Fields& x, const Fields&
 }
 
 // P_k^{-1} = blockdiag(P_{V,k}^{-1}, P_{Q,k}^{-1}) (Sec. 4): the two blocks are
-// independent, so the Q block is issued on a second stream with its own
+// independent.  At k <= 1 they share their launches (apply_Pk_joint);
+// otherwise the Q block is issued on a second stream with its own
 // workspace and residual slot (fork/join through events, which also holds
 // under stream capture) while the V block runs on the context stream.
 // Optional dot product of the result with `with` (a full vector), as
