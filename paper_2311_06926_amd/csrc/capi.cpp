@@ -855,7 +855,7 @@ hp_status fgmres(hp_ctx* c, const double* b, double* x, int nrhs, double tol, hp
     // host, at the price of one step past convergence -- unless the scaling of
     // the new vector alone, 2^22 entries in 15 us, covers the host's way back:
     // then the step's own flags are waited for (48^3, degree 2, 32 right-hand
-    // sides: 28 steps of 2.3 ms instead of 29).
+    // sides: 30 steps of 2.2 ms instead of 31).
     const bool wait = !graphs && N * (long long)nrhs >= (1LL << 22);
     HIPCHK(vec_dot_partials(c->stream, N, N, b, b, nrhs, ex->fpart));
     HIPCHK(fg_init(c->stream, ex->fsc, ex->fpart, (int)vec_dot_partial_count(N), nrhs));
