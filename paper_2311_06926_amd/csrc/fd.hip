@@ -41,6 +41,7 @@
 #include <climits>
 #include <type_traits>
 
+#include "fd_layout.h"
 #include "hp_internal.h"
 #include "vec.h"
 
@@ -66,12 +67,8 @@ struct Mfma<double> {
     static __device__ __forceinline__ V mma(double a, double b, V c) {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
-    static __host__ __device__ constexpr int kmap(int lk, int i) { return lk + 4 * i; }
-    // MFMA steps of a 16-wide tile that holds `rem` contraction values (0, 1,
-    // 2 or 4: what tail_steps compiles)
-    static __device__ __forceinline__ int steps(int rem) {
-        return rem > 8 ? 4 : (rem > 4 ? 2 : (rem > 0 ? 1 : 0));
-    }
+    static __host__ __device__ constexpr int kmap(int lk, int i) { return mfma_row<double>(lk, i); }
+    static __device__ __forceinline__ int steps(int rem) { return mfma_steps<double>(rem); }
 };
 template <>
 struct Mfma<float> {
@@ -79,10 +76,8 @@ struct Mfma<float> {
     static __device__ __forceinline__ V mma(float a, float b, V c) {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
-    static __host__ __device__ constexpr int kmap(int lk, int i) { return 4 * lk + i; }
-    static __device__ __forceinline__ int steps(int rem) {
-        return rem > 2 ? 4 : max(rem, 0);
-    }
+    static __host__ __device__ constexpr int kmap(int lk, int i) { return mfma_row<float>(lk, i); }
+    static __device__ __forceinline__ int steps(int rem) { return mfma_steps<float>(rem); }
 };
 
 // Split-BF16 ("bf16x3") products for FP32 data: each operand is written as
@@ -255,22 +250,6 @@ struct PlaneArgs {
     long long sinb, sinc;
     double ca, cb, cc;
 };
-
-// Pitch of the folded plane in LDS: a row holds [even | odd] and is read up to
-// the end of the odd half's last MFMA step; odd, so that the 16 rows of an
-// operand fall in different banks.
-template <typename T>
-__host__ __device__ inline int plane_pitch(int n) {
-    const int he = (n + 1) >> 1, ho = n >> 1;
-    int w;
-    if (std::is_same<T, double>::value) {
-        const int a = (he + 3) & ~3, b = he + ((ho + 3) & ~3);
-        w = a > b ? a : b;
-    } else {
-        w = he + ((he + 15) & ~15);
-    }
-    return w | 1;
-}
 
 // NT: tiles per half direction (nM's).  Wave (a, u1): D1 = X^T L^T for the 16
 // outputs i' of parity a and tile u1 of direction 1 and every j (contraction
@@ -1382,7 +1361,7 @@ static void pack_half(std::vector<T>& out, int h, int nt, F A) {
             for (int l = 0; l < 64; ++l)
                 for (int i = 0; i < 4; ++i) {
                     const int lk = l / 16;
-                    const int k = 16 * t + (std::is_same<T, double>::value ? lk + 4 * i : 4 * lk + i);
+                    const int k = 16 * t + mfma_row<T>(lk, i);
                     const int m = 16 * u + l % 16;
                     out.push_back(m < h && k < h ? (T)A(m, k) : (T)0);
                 }
