@@ -69,7 +69,8 @@ typedef enum {
  * the intermediates); split BF16 (each FP32 operand as hi + lo BF16 halves,
  * three BF16 MFMA products accumulated in FP32: about 16 significant bits,
  * products good to ~1e-5 relative).  Split BF16 runs in the plane plans
- * (fd_plan 1 and 9); the direction passes take FP32 products for it. */
+ * (fd_plan 1 and 9); fd_plan 0 and 2, and directions beyond 128, take FP32
+ * products for it. */
 enum { HP_PREC_FP64 = 0, HP_PREC_FP32 = 1, HP_PREC_BF16X3 = 2 };
 /* Krylov method. MINRES needs an exactly symmetric preconditioner (FP64). */
 enum { HP_MINRES = 0, HP_FGMRES = 1 };
@@ -116,10 +117,11 @@ typedef struct hp_opts {
                            i3-plane in one workgroup's LDS and mode 3 on 32 columns per
                            workgroup (directions E + degree - 1 <= 128); 9 = the same with
                            16 columns (twice the workgroups, for small meshes); 0 = one
-                           direction per pass (<= 128; FP64/FP32); 8 = one direction per
-                           pass at any length (the plan used whenever E + degree - 1 > 128,
-                           where split BF16 falls back to FP32 products); 2..7 = the default
-                           (codes of former kernels) */
+                           direction per pass (<= 128; split BF16 takes FP32 products);
+                           8 = one direction per pass at any length (the plan used whenever
+                           E + degree - 1 > 128, where split BF16 takes FP32 products; up to
+                           128 not for split BF16, which takes the default); 2..7 = the
+                           default (codes of former kernels), but 2 = 0 for split BF16 */
     int op_slabs;       /* operator: i3-slabs run one after the other (pressure chain
                            then velocity per slab), 0 = tuned/model */
     int schur_level;    /* eq. Pcq2 only: the fixed P_{V,l} inside B' P_{V,l}^{-1} B,

@@ -1390,14 +1390,16 @@ template void fd_pack<float>(const std::vector<double>&, int, int, FdPack, std::
 
 // Whether plan `plan` exists for this mesh and precision (see hp_internal.h).
 bool fd_plan_valid(const hp_ctx* c, int precision, int plan) {
-    if (fd_plan_lines(plan) && precision == HP_PREC_BF16X3) return false;
-    if (plan == FD_PLAN_LINES) return true;
-    return (plan == FD_PLAN_PASSES || plan == FD_PLAN_PLANE || plan == FD_PLAN_SMALL) && c->nM <= FD_PLANE_MAX;
+    const bool planes = c->nM <= FD_PLANE_MAX;
+    if (plan == FD_PLAN_LINES) return precision != HP_PREC_BF16X3 || !planes;
+    return planes && (plan == FD_PLAN_PASSES || plan == FD_PLAN_PLANE || plan == FD_PLAN_SMALL);
 }
 
 int fd_plan_in_use(const hp_ctx* c, int precision) {
     if (c->fd_force >= 0) return c->fd_force;
-    if (c->opts.fd_plan >= 0 && fd_plan_valid(c, precision, c->opts.fd_plan)) return c->opts.fd_plan;
+    // codes 0 and 2 promise FP32 products to split BF16 (1e-7, the plane plans' 1e-5)
+    const int want = precision == HP_PREC_BF16X3 && c->opts.fd_plan == 2 ? FD_PLAN_PASSES : c->opts.fd_plan;
+    if (want >= 0 && fd_plan_valid(c, precision, want)) return want;
     if (c->nM > FD_PLANE_MAX) return FD_PLAN_LINES;
     return c->fd_tuned[precision] >= 0 ? c->fd_tuned[precision] : FD_PLAN_PLANE;
 }
