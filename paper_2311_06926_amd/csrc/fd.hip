@@ -129,15 +129,6 @@ __device__ __forceinline__ void tail_steps(int st, F fn) {
     else if (st == 1) fn(std::integral_constant<int, 1>{});
 }
 
-// 1 / x (x > 0, normal): the hardware estimate and two Newton steps, good to
-// about an ulp (a scaling by an eigenvalue sum needs no correctly rounded
-// division, which takes several times the instructions)
-__device__ __forceinline__ double recip(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return fma(fma(-x, r, 1.0), r, r);
-}
-
 // One direction of one field: its length, the sizes of the even and odd
 // halves and the fragment table (forward F, inverse V; for the pressure both
 // are M^^{-1}): nt x nt tiles of the even half, then of the odd half, with
@@ -688,7 +679,10 @@ struct HalfProduct {
 // Direction 2 or 3 of 16 CT columns: the columns are contiguous (the B
 // operand, [k][column] in LDS), the table is the A operand.  Mode 3 forward,
 // scaling by omega / (2 nu (l1 + l2 + l3)) and inverse run in one pass: the
-// scaled tiles of the first product replace its operand in LDS.
+// scaled tiles of the first product replace its operand in LDS.  The division
+// is the correctly rounded one, over the whole range of nu (an estimate with two
+// Newton steps: P_0 at 32^3 19.3 us instead of 19.6, but an ulp more and NaN
+// where the sum overflows).
 template <typename T, typename TI, typename TO, bool SPLIT, int CT, int NW>
 __global__ __launch_bounds__(64 * NW)
 __attribute__((amdgpu_waves_per_eu(4))) void k_fd_line(LineArgs a, FDTables<T> t) {
@@ -806,7 +800,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_fd_line(LineArgs a, FDTables<T> t
                     const double l3 = t3[min(h * he + m, n - 1)];
 #pragma unroll
                     for (int c = 0; c < CT; ++c)
-                        acc[q][h][c][i] = ok ? (T)(a.omega * recip(a.two_nu * (l12[c] + l3)) *
+                        acc[q][h][c][i] = ok ? (T)(a.omega / (a.two_nu * (l12[c] + l3)) *
                                                    (double)acc[q][h][c][i])
                                              : T(0);
                 }
