@@ -85,17 +85,17 @@ struct Points {
 };
 
 struct FaceWeights {
-    double v, d1, d2, d3;     // w nu at volume points and at points of the faces normal to 1, 2, 3
+    double d1, d2, d3;          // w nu at points of the faces normal to 1, 2, 3
     double s1, s2, s3, alpha2;  // outward signs, 2 alpha
 };
 
 // One point of a column: mode 3, the flux and the transposed mode 3.  tb: the
-// point's table row in direction 3 (scalar registers), wn = w nu at volume
+// point's table row in direction 3 (scalar registers), w: the weight at volume
 // points.  FACE: the point may lie on a face; the terms of every kind of point
 // are formed with their weights, so that no branch stands between updates of
 // the accumulators (branches made the compiler copy all of them).
 template <int P, bool FACE>
-__device__ __forceinline__ void quad_point(const double* tb, double wn, double inv_nu,
+__device__ __forceinline__ void quad_point(const double* tb, double w, double nu,
                                            const FaceWeights& fw, const double (&WM)[7][P],
                                            const double (&WN)[3][P + 1], double (&AM)[6][P],
                                            double (&AN)[3][P + 1]) {
@@ -124,7 +124,7 @@ __device__ __forceinline__ void quad_point(const double* tb, double wn, double i
     const double g13 = dotM(DM, WM[0]), g12 = dotM(VM, WM[1]), g11 = dotM(VM, WM[2]);
     const double g23 = dotM(DM, WM[3]), g22 = dotM(VM, WM[4]), g21 = dotM(VM, WM[5]);
     const double g33 = dotN(DN, WN[0]), g32 = dotN(VN, WN[1]), g31 = dotN(VN, WN[2]);
-    const double w = wn * inv_nu, wp = w * dotM(VM, WM[6]);
+    const double wn = w * nu, wp = w * dotM(VM, WM[6]);
     double s12 = wn * (g12 + g21), s13 = wn * (g13 + g31), s23 = wn * (g23 + g32);
     if constexpr (FACE) {
         const double v1 = dotM(VM, WM[0]), v2 = dotM(VM, WM[3]), v3 = dotN(VN, WN[0]);
@@ -445,19 +445,20 @@ __global__ __launch_bounds__(QT) __attribute__((amdgpu_waves_per_eu(quad_per_cu(
 #pragma unroll 1
             for (int g = g0; g < g1; ++g) {
                 const bool f3 = g == 0 || g == a.nq - 1;
-                const double w = w12 * sload(a.wq, g) * a.nu;
+                const double w = w12 * sload(a.wq, g), wn = w * a.nu;
                 const int faces = (int)f1 + (int)f2 + (int)f3;
-                // nu times the weight for each kind of point, zero for the others
-                const FaceWeights fw{faces == 0 ? w : 0.0, faces == 1 && f1 ? w : 0.0,
-                                     faces == 1 && f2 ? w : 0.0, faces == 1 && f3 ? w : 0.0,
-                                     s1, s2, g == 0 ? -1.0 : 1.0, 2.0 * a.alpha};
-                quad_point<P, true>(a.tab + (long long)g * 4 * W, fw.v, 1.0 / a.nu, fw, WM, WN, AM, AN);
+                // the weight for each kind of point, zero for the others
+                const FaceWeights fw{faces == 1 && f1 ? wn : 0.0, faces == 1 && f2 ? wn : 0.0,
+                                     faces == 1 && f3 ? wn : 0.0, s1, s2, g == 0 ? -1.0 : 1.0,
+                                     2.0 * a.alpha};
+                quad_point<P, true>(a.tab + (long long)g * 4 * W, faces == 0 ? w : 0.0, a.nu, fw, WM,
+                                    WN, AM, AN);
             }
         } else {
 #pragma unroll 1
             for (int g = g0; g < g1; ++g)
-                quad_point<P, false>(a.tab + (long long)g * 4 * W, w12 * sload(a.wq, g) * a.nu, 1.0 / a.nu,
-                                     FaceWeights{}, WM, WN, AM, AN);
+                quad_point<P, false>(a.tab + (long long)g * 4 * W, w12 * sload(a.wq, g), a.nu, FaceWeights{},
+                                     WM, WN, AM, AN);
         }
     }
 }
