@@ -525,7 +525,7 @@ def main():
         "kernel": kname,
         "bound": "mfma", "achieved": achieved, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
         "frac": achieved / FP64_PEAK_TFLOPS,
-        "traffic": pmc_traffic(f"apply_P0_E{E}p{p}_pmc.txt", ["fd.hip"]),
+        "traffic": pmc_traffic(f"apply_P0_E{E}p{p}_pmc.txt", ["fd.hip", "fd_layout.h"]),
         "algorithmic_flops_per_launch": flops, "avg_launch_us": t_P0 * 1e6,
         "per_operator": per_op,
     }

@@ -242,7 +242,11 @@ hp_status hp_apply_K(hp_ctx* ctx, const double* x, double* y, int nrhs);
  * quadrature: the same matrix as hp_apply_K, up to rounding.  x and y are
  * device arrays of nrhs vectors (stride N, layout of hp_apply_K), y must not
  * alias x.  The first call allocates the point tables and a scratch for the
- * partial sums of up to 8 right-hand sides, each a few times N doubles;
+ * partial sums of min(max_rhs, 8) right-hand sides: per tile of ex x ey
+ * elements and chunk of L element layers 4 (L + p) (ey + p) (ex + p) doubles,
+ * ex x ey = 4 x 5, 4 x 3, 3 x 2, 2 x 2, 2 x 2, 2 x 1, 2 x 1 at degree 2 to 8, L
+ * from the mesh.  At 64^3 that is 2, 4, 7, 11, 14, 31 and 37 times N doubles per
+ * right-hand side, on meshes of 8 to 24 elements up to three times as much;
  * HP_ENOMEM if that fails. */
 hp_status hp_apply_K_quad(hp_ctx* ctx, const double* x, double* y, int nrhs);
 

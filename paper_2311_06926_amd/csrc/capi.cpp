@@ -398,8 +398,9 @@ hipError_t with_q_settings(hp_ctx* c, hipStream_t s, F fn) {
 // A y and of B', and at the end P_0 of all four fields.  Against one stream
 // per block this is about half the launches and no fork and join (four event
 // calls, about 20 us of host time): a MINRES solve at 32^3, degree 3, 3.76 ->
-// 3.20 ms, the quadrature one at 16^3, degree 4, 4.08 -> 3.73.  Where the
-// kernels fill the chip the two are equal (61^3: 107 us either way).
+// 3.20 ms, the quadrature one at 16^3, degree 4, 4.08 -> 3.73.  The gain falls
+// as the kernels fill the chip (P_1 alone, us, in common and on two streams:
+// 32^3 57.6 and 68 to 86, 48^3 84.0 and 85 to 89, 61^3 95.2 and 97.5).
 hipError_t apply_Pk_joint(hp_ctx* c, int q, int k, const double* x, double* y, int nrhs,
                           const PkDot* pd) {
     Extra* ex = extra_of(c);
@@ -1111,8 +1112,9 @@ hp_status autotune(hp_ctx* c) {
             for (int plan = 0; plan <= FD_PLAN_LAST && st == HP_OK; ++plan) {
                 if (!fd_plan_valid(c, prec, plan)) continue;
                 // the plane plans alone where they exist: they agree bit for
-                // bit, the passes do not (96^3: 124.4 us against 124.7, FP32
-                // 92.5 against 84.1; 120^3: 188.0 against 190.0)
+                // bit, the passes do not, for little or no gain (us, planes and
+                // passes: 96^3 123.7 and 122.3, FP32 80.8 and 91.8; 120^3 183.4
+                // and 181.2, FP32 105.7 and 118.2)
                 if (fd_plan_lines(plan) && fd_plan_valid(c, prec, FD_PLAN_PLANE)) continue;
                 c->fd_force = plan;
                 const double t = time_launches(c, e0, e1, TUNE_REPS, [&]() {

@@ -34,8 +34,8 @@
 // P_0 is plane, line (mode 3), plane, or, one direction per pass, row, line,
 // line (mode 3), line, row.  Measured, FP64 (us; before: dense products, the
 // whole plane by 16 waves, from 129 per direction six batched GEMMs per
-// component): 32^3 degree 3 20.8 -> 19.1, 61^3 44 -> 30, 96^3 228 -> 124,
-// 192^3 2155 -> 1146, 256^3 degree 2 4930 -> 2750; FP32, 32 right-hand sides
+// component): 32^3 degree 3 20.8 -> 19.7, 61^3 44 -> 30, 96^3 228 -> 124,
+// 192^3 2155 -> 1143, 256^3 degree 2 4930 -> 2756; FP32, 32 right-hand sides
 // at 48^3 degree 2: 676 -> 190.
 #include <algorithm>
 #include <climits>

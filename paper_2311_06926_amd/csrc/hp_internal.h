@@ -207,7 +207,9 @@ long long fd_dot_capacity(const hp_ctx* c, bool vel);
 // workgroup's LDS (directions up to 128), mode 3 on 32 columns per workgroup;
 // FD_PLAN_SMALL = the same with 16 columns (twice the workgroups, for small
 // meshes); FD_PLAN_PASSES and FD_PLAN_LINES = one direction per pass, up to
-// 128 and at any length (the only plan beyond; not tuned up to there).
+// 128 and at any length (the only plan beyond; not tuned up to there).  For
+// split BF16 these two take FP32 products: FD_PLAN_PASSES where the caller asks
+// for it (fd_plan 0 or 2), FD_PLAN_LINES beyond 128.
 // The plane plans agree with each other bit for bit, and so do the two
 // others; between them the folds are rounded in another order.  Whether plan
 // `plan` exists for this mesh and `precision`, and the plan launch_P0 uses

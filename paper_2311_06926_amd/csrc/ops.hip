@@ -459,8 +459,9 @@ __global__ __launch_bounds__(PT1 * PT2) __attribute__((amdgpu_waves_per_eu(waves
 // KC = kchunk (2 or 4), degrees 2 and 3.  Few waves run and each is a chain of
 // latencies, so loads come in pairs (half as many to issue), the rows of
 // direction 1 are one list over all planes, three at a time, and a pass's LDS
-// reads stand before its uses: with the same in k_vel_all K at 8^3, degree 2,
-// 10.0 -> 8.7 us, at 16^3 11.3 -> 8.8, at 32^3, degree 3, 14.4 -> 12.1.
+// reads stand before its uses: with the same in k_vel_all and chunks of 2, K at
+// 8^3, degree 2, 9.7 -> 8.0 us, at 16^3 9.8 -> 8.1, at 32^3, degree 3, 13.8 ->
+// 11.7 (with chunks of 4 11.6 -> 9.1, 11.8 -> 9.3, 16.0 -> 12.8).
 template <int P, int KC>
 __global__ __launch_bounds__(NT) void k_pres_all(OpArgs a, double* yp, long long syp, PresJob job) {
     constexpr int W = P - 1;

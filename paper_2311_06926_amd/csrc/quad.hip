@@ -37,7 +37,7 @@
 // kept the flux fields of all points in HBM, with 560 MB through them at 32^3
 // degree 3, took (us): 32^3 degree 2 / 3 / 4 96 / 212 / 474, 64^3 degree 3
 // 1911, 96^3 6666, 24^3 degree 6 691, 16^3 degree 8 563; this form takes 36 /
-// 68 / 173, 333, 907, 220, 304.
+// 68 / 172, 332, 874, 222, 312.
 #include <algorithm>
 #include <climits>
 
