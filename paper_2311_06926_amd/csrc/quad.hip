@@ -40,6 +40,8 @@
 // 68 / 172, 332, 874, 222, 312.
 #include <algorithm>
 #include <climits>
+#include <new>
+#include <stdexcept>
 
 #include "hp_internal.h"
 
@@ -560,8 +562,7 @@ constexpr int QUAD_RHS = 8;
 
 }  // namespace
 
-hipError_t quad_setup(hp_ctx* c, QuadOp* q) {
-    if (q->ready) return hipSuccess;
+static hipError_t make_quad(hp_ctx* c, QuadOp* q) {
     const QuadTables1D Q = build_quad_tables(c->tab);
     const int p = c->p, W = p + 1, E = c->E, nq = Q.nq, nN = c->nN, nM = c->nM;
     q->nq = nq;
@@ -621,6 +622,20 @@ hipError_t quad_setup(hp_ctx* c, QuadOp* q) {
         return fail(e);
     q->ready = true;
     return hipSuccess;
+}
+
+// (no exception of the host tables may cross the C interface)
+hipError_t quad_setup(hp_ctx* c, QuadOp* q) {
+    if (q->ready) return hipSuccess;
+    try {
+        return make_quad(c, q);
+    } catch (const std::bad_alloc&) {
+        quad_free(q);
+        return hipErrorOutOfMemory;
+    } catch (const std::exception&) {
+        quad_free(q);
+        return hipErrorInvalidValue;
+    }
 }
 
 void quad_free(QuadOp* q) {
